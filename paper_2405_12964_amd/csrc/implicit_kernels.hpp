@@ -39,6 +39,14 @@ struct ImpArgs {
     T* s;              // per differential walk: (dg/dn - du/dn) / |grad h|, 0 if none
 };
 
+// a^2 + b^2 with the rounding spelled out (FP32: one fused product), so that
+// a walk does not depend on how the compiler pairs the two in a build.
+template <class T>
+__device__ __forceinline__ T sq_sum(T a, T b) {
+    if constexpr (std::is_same<T, float>::value) return __builtin_fmaf(a, a, b * b);
+    else return a * a + b * b;
+}
+
 // h and grad h at x.  The FP32 instantiation takes 1/r from the hardware
 // reciprocal square root and the monopole terms as products with it; the
 // FP64 one keeps the correctly rounded divisions of the plain formula.
@@ -177,8 +185,8 @@ __global__ void __launch_bounds__(kBlock) implicit_kernel(WalkArgs<T> a, ImpArgs
         key0 = (uint32_t)sd;
         key1 = (uint32_t)(sd >> 32);
     }
-    unsigned long long pool_next = 0, pool_end = 0;   // wave-uniform
-    bool done = false;
+    WalkPool pool = first_pool(a);
+    bool done = lane >= a.lanes;
     int64_t wid = -1;
     T x[D], xoff[D], xb_t[D];
     T acc = T(0), u_main = T(0), usum = T(0);
@@ -194,22 +202,7 @@ __global__ void __launch_bounds__(kBlock) implicit_kernel(WalkArgs<T> a, ImpArgs
         const bool need = (wid < 0) && !done;
         const unsigned long long mask = __ballot(need);
         if (mask) {
-            const int cnt = __popcll(mask);
-            const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-            const unsigned long long avail = pool_end - pool_next;
-            unsigned long long myid;
-            if (avail >= (unsigned long long)cnt) {
-                myid = pool_next + rank;
-                pool_next += cnt;
-            } else {
-                const int leader = __ffsll((long long)mask) - 1;
-                unsigned long long base = 0;
-                if (lane == leader) base = atomicAdd(a.queue, (unsigned long long)kQueueChunk);
-                base = bcast64(base, leader);
-                myid = (unsigned long long)rank < avail ? pool_next + rank : base + (rank - avail);
-                pool_next = base + (cnt - avail);
-                pool_end = base + kQueueChunk;
-            }
+            const unsigned long long myid = take_walks(a, pool, mask, lane);
             if (need) {
                 if (myid >= (unsigned long long)a.total) {
                     done = true;
@@ -244,7 +237,7 @@ __global__ void __launch_bounds__(kBlock) implicit_kernel(WalkArgs<T> a, ImpArgs
             wid = -1;
             continue;
         }
-        const T gn = sqrt(gr[0] * gr[0] + gr[1] * gr[1]);
+        const T gn = sqrt(sq_sum(gr[0], gr[1]));
         const bool shell = h <= gn * eps && h < -c;
         const bool cap = (int)(k + 1) >= a.prm.kmax;
         const bool nested = MODE == 1 && phase > 0;
@@ -258,7 +251,7 @@ __global__ void __launch_bounds__(kBlock) implicit_kernel(WalkArgs<T> a, ImpArgs
             if (MODE == 1 && phase == 0) {
                 T gb[2];
                 imp_h<T>(smono, n, c, xb, gb);
-                const T gbn = sqrt(gb[0] * gb[0] + gb[1] * gb[1]);
+                const T gbn = sqrt(sq_sum(gb[1], gb[0]));
                 const T nx = -gb[0] / gbn, ny = -gb[1] / gbn;
                 u_main = acc + g;
                 t_g = g;

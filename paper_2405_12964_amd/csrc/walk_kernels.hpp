@@ -103,7 +103,8 @@ struct WalkArgs {
     const unsigned long long* seed_ptr;   // if set, the key is seed + *seed_ptr
     unsigned long long* queue;
     int32_t park;            // lanes answered before a wavefront takes its step (1..64)
-    uint32_t chunk;          // walk ids taken per wavefront refill (multiple of 64)
+    uint32_t chunk;          // walk ids taken per wavefront refill (at least `lanes`)
+    int32_t lanes;           // lanes of each wavefront that take walks (1..64)
     Counters* cnt;           // this call
     Counters* tot;           // cumulative for this walk kind
     // records (indexed by logical id - wid_offset)
@@ -475,17 +476,17 @@ __device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView& 
 constexpr int kDescendTail = DWOS_DESCEND_TAIL;
 template <class T, int D, class Stack>
 __device__ __forceinline__ void query_round(const Scene<T>& s, const StageView& sv, const T* x, bool active,
-                                            Query<T, D>& q, QueryCount& qc, Stack& st) {
+                                            Query<T, D>& q, QueryCount& qc, Stack& st, int tail) {
     using Q = Query<T, D>;
     constexpr T slack = Slack<T>::v;
     // phase 1: expand nodes until this lane holds a leaf or is finished
 #pragma unroll 1
     while (true) {
         const bool go = active && !q.has_leaf && !q.done;
-        if (s.tail > 0) {
+        if (tail > 0) {
             const unsigned long long gm = __ballot(go);
             if (gm == 0ull) break;
-            if (__popcll(gm) <= s.tail && __ballot(active && q.has_leaf) != 0ull) break;
+            if (__popcll(gm) <= tail && __ballot(active && q.has_leaf) != 0ull) break;
             if (!go) continue;
         } else if (!go) {
             break;
@@ -558,7 +559,7 @@ __device__ __forceinline__ int32_t closest_leaf(const Scene<T>& s, const StageVi
     Query<T, D> q;
     query_begin<T, D>(s, sv, root, x, warm, q);
 #pragma unroll 1
-    while (!q.done) query_round<T, D>(s, sv, x, true, q, qc, st);
+    while (!q.done) query_round<T, D>(s, sv, x, true, q, qc, st, s.tail);
     best = q.best;
     return q.bleaf;
 }
@@ -580,7 +581,7 @@ __device__ __forceinline__ int32_t closest_leaf_within(const Scene<T>& s, const 
         q.best = bound2;
     }
 #pragma unroll 1
-    while (!q.done) query_round<T, D>(s, sv, x, true, q, qc, st);
+    while (!q.done) query_round<T, D>(s, sv, x, true, q, qc, st, s.tail);
     best = q.best;
     return q.bleaf;
 }
@@ -667,6 +668,65 @@ __device__ __forceinline__ unsigned long long bcast64(unsigned long long v, int 
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// The wavefront's share of the work queue: walk ids [next, end) in hand.  The
+// first chunk of a wavefront is its own by position, later ones come from the
+// global counter (which counts from the end of the first chunks); `more` is
+// false once the ids are used up, so that no lane of a launch with one chunk
+// per wavefront, and no lane of a finishing one, waits for an atomic.  All
+// wave-uniform.
+struct WalkPool { unsigned long long next, end, dyn; bool more; };
+
+template <class T>
+__device__ __forceinline__ WalkPool first_pool(const WalkArgs<T>& a) {
+    const unsigned wpb = blockDim.x >> 6;
+    const unsigned w = blockIdx.x * wpb + (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    WalkPool q;
+    q.next = (unsigned long long)w * a.chunk;
+    q.end = q.next + a.chunk;
+    q.dyn = (unsigned long long)gridDim.x * wpb * a.chunk;
+    q.more = q.dyn < (unsigned long long)a.total;
+    return q;
+}
+
+// A walk id for every lane of `mask` (at least a.total: none left).
+template <class T>
+__device__ __forceinline__ unsigned long long take_walks(const WalkArgs<T>& a, WalkPool& q,
+                                                         unsigned long long mask, int lane) {
+    const int n = __popcll(mask);
+    const int rank = __popcll(mask & ((1ull << lane) - 1ull));
+    const unsigned long long avail = q.end - q.next;
+    unsigned long long id;
+    if (avail >= (unsigned long long)n) {
+        id = q.next + rank;
+        q.next += n;
+    } else {
+        unsigned long long base = (unsigned long long)a.total;
+        if (q.more) {
+            const int leader = __ffsll((long long)mask) - 1;
+            if (lane == leader) base = atomicAdd(a.queue, (unsigned long long)a.chunk);
+            base = q.dyn + bcast64(base, leader);
+            q.more = base < (unsigned long long)a.total;
+        }
+        id = (unsigned long long)rank < avail ? q.next + rank : base + (rank - avail);
+        if (q.more) {
+            q.next = base + (n - avail);
+            q.end = base + a.chunk;
+        } else {
+            q.next = q.end = (unsigned long long)a.total;
+        }
+    }
+    return id;
+}
+
+// A lane count given for a full wavefront (park, tail), in proportion to the
+// lanes still live, at least lo: once the queue is empty, or where a launch
+// gives few walks to each wavefront, the count for 64 lanes would make every
+// step wait for the slowest of all lanes.
+__device__ __forceinline__ int live_share(int full, unsigned long long live, int lo) {
+    const int n = (full * __popcll(live) + 32) >> 6;
+    return n > lo ? n : lo;
+}
+
 // ---------------------------------------------------------------------------
 // the walk kernel
 //   MODE 0: Algorithm 1 (forward walks): rec_u = walk estimate
@@ -731,8 +791,8 @@ walk_kernel(WalkArgs<T> a) {
         key0 = (uint32_t)sd;
         key1 = (uint32_t)(sd >> 32);
     }
-    unsigned long long pool_next = 0, pool_end = 0;   // wave-uniform
-    bool done = false;
+    WalkPool pool = first_pool(a);
+    bool done = lane >= a.lanes;
     int64_t wid = -1;          // logical walk id (relative to wid_offset)
     // walk state
     T x[D], xoff[D];
@@ -771,22 +831,7 @@ walk_kernel(WalkArgs<T> a) {
         const bool need = (wid < 0) && !done;
         const unsigned long long mask = __ballot(need);
         if (mask) {
-            const int n = __popcll(mask);
-            const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-            const unsigned long long avail = pool_end - pool_next;
-            unsigned long long myid;
-            if (avail >= (unsigned long long)n) {
-                myid = pool_next + rank;
-                pool_next += n;
-            } else {
-                const int leader = __ffsll((long long)mask) - 1;
-                unsigned long long base = 0;
-                if (lane == leader) base = atomicAdd(a.queue, (unsigned long long)a.chunk);
-                base = bcast64(base, leader);
-                myid = (unsigned long long)rank < avail ? pool_next + rank : base + (rank - avail);
-                pool_next = base + (n - avail);
-                pool_end = base + a.chunk;
-            }
+            const unsigned long long myid = take_walks(a, pool, mask, lane);
             if (need) {
                 if (myid >= (unsigned long long)a.total) {
                     done = true;
@@ -823,8 +868,10 @@ walk_kernel(WalkArgs<T> a) {
                 }
             }
         }
-        if (__ballot(!done) == 0ull) break;
+        const unsigned long long live = __ballot(!done);
+        if (live == 0ull) break;
         if (done) continue;
+        const int park = live_share(a.park, live, 1), tail = live_share(a.s.tail, live, 0);
 
         // ---- one walk step: closest-point query -----------------------------
         // A lane without a query in progress starts one at x.  The wavefront
@@ -854,8 +901,8 @@ walk_kernel(WalkArgs<T> a) {
                 const bool searching = qpend && !q.done;
                 const unsigned long long sm = __ballot(searching);
                 const unsigned long long rm = __ballot(ready || (qpend && q.done));
-                if (sm == 0ull || __popcll(rm) >= a.park) break;
-                query_round<T, D>(a.s, sv, x, searching, q, qc, stack);
+                if (sm == 0ull || __popcll(rm) >= park) break;
+                query_round<T, D>(a.s, sv, x, searching, q, qc, stack, tail);
             }
             c_nodes += qc.nodes; c_prims += qc.prims;
             if (qc.overflow) count_rare(&Counters::overflow, qc.overflow);

@@ -613,8 +613,8 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
         key0 = (uint32_t)sd;
         key1 = (uint32_t)(sd >> 32);
     }
-    unsigned long long pool_next = 0, pool_end = 0;   // wave-uniform
-    bool done = false;
+    WalkPool pool = first_pool(a);
+    bool done = lane >= a.lanes;
     int64_t wid = -1;
     T x[D], xoff[D], nin[D];
     T acc = T(0), u_main = T(0), usum = T(0);
@@ -642,22 +642,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
         const bool need = (wid < 0) && !done;
         const unsigned long long mask = __ballot(need);
         if (mask) {
-            const int n = __popcll(mask);
-            const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-            const unsigned long long avail = pool_end - pool_next;
-            unsigned long long myid;
-            if (avail >= (unsigned long long)n) {
-                myid = pool_next + rank;
-                pool_next += n;
-            } else {
-                const int leader = __ffsll((long long)mask) - 1;
-                unsigned long long base = 0;
-                if (lane == leader) base = atomicAdd(a.queue, (unsigned long long)a.chunk);
-                base = bcast64(base, leader);
-                myid = (unsigned long long)rank < avail ? pool_next + rank : base + (rank - avail);
-                pool_next = base + (n - avail);
-                pool_end = base + a.chunk;
-            }
+            const unsigned long long myid = take_walks(a, pool, mask, lane);
             if (need) {
                 if (myid >= (unsigned long long)a.total) {
                     done = true;
@@ -689,8 +674,10 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                 }
             }
         }
-        if (__ballot(!done) == 0ull) break;
+        const unsigned long long live = __ballot(!done);
+        if (live == 0ull) break;
         if (done) continue;
+        const int park = live_share(a.park, live, 1), tail = live_share(a.s.tail, live, 0);
 
         QueryCount qc{0, 0, 0};
         bool finished = false;
@@ -806,8 +793,8 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                 const bool trav = spend && sq.have;
                 const unsigned long long sm = __ballot(trav);
                 const unsigned long long present = __ballot(true);
-                if (sm == 0ull || __popcll(present & ~sm) >= a.park) break;
-                if (trav) sil_round<T>(ref, x, on, nin, sq, qc, stack, a.s.tail);
+                if (sm == 0ull || __popcll(present & ~sm) >= park) break;
+                if (trav) sil_round<T>(ref, x, on, nin, sq, qc, stack, tail);
             }
         }
         if (spend && sq.have) {
