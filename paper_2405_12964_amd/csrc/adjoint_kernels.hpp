@@ -80,9 +80,9 @@ __device__ __forceinline__ T adj_uref(const AdjArgs<T>& a, const T* x) {
 // non-finite point.
 template <class T, int D>
 __device__ __forceinline__ int32_t adj_query(const AdjArgs<T>& a, const T* x, int32_t warm, T& d2, AdjCount& c) {
-    TravStack<T, false> st;
+    PrivateStack<T> st;
     QueryCount qc{0, 0, 0};
-    const StageView sv{0, -1};
+    const StageView<0> sv{0, -1};
     const int32_t leaf = closest_leaf<T, D>(a.s, sv, 0, x, warm, d2, qc, st);
     c.nodes += qc.nodes;
     c.prims += qc.prims;
@@ -93,7 +93,7 @@ __device__ __forceinline__ int32_t adj_query(const AdjArgs<T>& a, const T* x, in
 // Boundary value at the closest point of leaf `leaf` to x.
 template <class T, int D>
 __device__ __forceinline__ T adj_boundary(const AdjArgs<T>& a, int32_t leaf, const T* x) {
-    const StageView sv{0, -1};
+    const StageView<0> sv{0, -1};
     T P[9], bary[3];
     scene_prim<T, D>(a.s, sv, leaf, P);
     prim_closest<T, D>(P, x, bary);

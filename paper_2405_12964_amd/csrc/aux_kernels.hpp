@@ -336,13 +336,13 @@ template <class T, int D>
 __global__ void closest_kernel(Scene<T> s, int32_t root, const double* X, int64_t P, double* out) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= P) return;
-    const StageView sv{0, -1};
+    const StageView<0> sv{0, -1};
     T x[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) x[c] = T(X[p * D + c]);
     T d2;
     QueryCount qc{0, 0, 0};
-    TravStack<T, false> stack;
+    PrivateStack<T> stack;
     const int32_t leaf = closest_leaf<T, D>(s, sv, root, x, -1, d2, qc, stack);
     double* o = out + p * 8;
     if (leaf < 0) {
@@ -454,13 +454,13 @@ __global__ void first_query_kernel(Scene<T> s, const Instance<T>* inst, int32_t 
         const int mid = (lo + hi + 1) >> 1;
         if (inst[mid].point_begin <= g) lo = mid; else hi = mid - 1;
     }
-    const StageView sv{0, -1};
+    const StageView<0> sv{0, -1};
     T x[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) x[c] = T(X[r * D + c]);
     T d2;
     QueryCount qc{0, 0, 0};
-    TravStack<T, false> stack;
+    PrivateStack<T> stack;
     int32_t warm = -1;
     if (warm_in) {
         const int32_t w = warm_in[r];

@@ -198,6 +198,13 @@ dwos::Params<T> make_params(const dwos_problem& p) {
     return q;
 }
 
+// Traversal-stack entries a lane keeps in LDS: beside the staged tree (block
+// of 1024 threads) at least kStagedStack (the 4096-segment star: 2.73 ms a
+// step at 5 entries, 2.81 at 3, 2.84 at 2); without it as many as leave the
+// kernel its occupancy (15 entries of 8 bytes are 30 KB per 256-thread block:
+// five blocks, five wavefronts per SIMD, in the CU's 160 KB).
+constexpr int kStagedStack = 5, kMaxStack = 15;
+
 template <class T>
 dwos::Scene<T> make_scene(dwos_ctx* c) {
     dwos::Scene<T> s;
@@ -209,9 +216,10 @@ dwos::Scene<T> make_scene(dwos_ctx* c) {
     s.label = c->label.as<int32_t>();
     s.gvert = c->gvert.as<T>();
     s.n_prims = c->np;
-    // LDS staging plan: the whole BVH and all primitives if they fit, else a
-    // prefix of the (breadth-first ordered) nodes
-    const size_t budget = c->max_smem >= 1024 ? c->max_smem - 512 : 0;
+    // LDS staging plan: the whole BVH and all primitives if they fit beside
+    // the traversal stacks, else a prefix of the (breadth-first ordered) nodes
+    const size_t stacks = (size_t)kStagedStack * dwos::kBlockStaged * sizeof(dwos::StackEntry<T>);
+    const size_t budget = c->max_smem >= 1024 + stacks ? c->max_smem - 512 - stacks : 0;
     const size_t nb = (size_t)dwos::node_scalars(c->D) * sizeof(T);
     const size_t pb = (size_t)dwos::prim_scalars(c->D) * sizeof(T);
     const size_t all_nodes = (size_t)c->n_nodes * nb, all_prims = (size_t)c->np * pb;
@@ -712,13 +720,41 @@ Split split_walks(int64_t total, int block, int per_cu, int cu_count, int chunk,
     return {(int)lanes, (uint32_t)ids, (unsigned)(64 * wpb), (unsigned)((waves + wpb - 1) / wpb)};
 }
 
-template <class T, int D, int MODE, bool staged, bool cv>
+// Multiplier and shift of WalkArgs::w_magic: with 2^(L-1) < W <= 2^L and M =
+// floor(2^(31+L) / W) + 1, n M / 2^(31+L) exceeds n / W by less than 1 / W
+// for n < 2^31.
+template <class T>
+void set_div(dwos::WalkArgs<T>& a) {
+    a.w_magic = 0;
+    a.w_shift = 0;
+    if (a.total + a.wid_offset >= (int64_t(1) << 31)) return;
+    int L = 0;
+    while ((int64_t(1) << L) < a.W) ++L;
+    const uint64_t M = (uint64_t(1) << (31 + L)) / (uint64_t)a.W + 1;
+    a.w_magic = (uint32_t)M;
+    a.w_shift = 31 + L;
+}
+
+template <class T, int D, int MODE, int STAGE, bool cv>
 dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed);
 
-// Launch the persistent walk kernel over `total` walks.  FP32 uses the
-// LDS-staged kernel (one large block per CU); the FP64 debug build keeps
-// everything in global memory.  `tot` (cumulative counters of this walk
-// kind) defaults to the context's; an untimed launch records no events.
+// The launch shape of a build with or without the control variate: FP32 with
+// variant 0 stages the tree in LDS (all of it, or a prefix of its nodes); the
+// FP64 debug build keeps everything in global memory.
+template <class T, int D, int MODE, bool cv>
+dwos_status launch_variant(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
+    if constexpr (sizeof(T) == 4) {
+        if (c->variant == 0) {
+            if (a.s.stage_prims && a.s.n_stage_nodes == c->n_nodes) return launch_shape<T, D, MODE, 2, cv>(c, a, timed);
+            return launch_shape<T, D, MODE, 1, cv>(c, a, timed);
+        }
+    }
+    return launch_shape<T, D, MODE, 0, cv>(c, a, timed);
+}
+
+// Launch the persistent walk kernel over `total` walks.  `tot` (cumulative
+// counters of this walk kind) defaults to the context's; an untimed launch
+// records no events.
 template <class T, int D, int MODE>
 dwos_status launch_walks(dwos_ctx* c, dwos::WalkArgs<T>& a, dwos::Counters* tot = nullptr,
                          bool timed = true) {
@@ -726,29 +762,22 @@ dwos_status launch_walks(dwos_ctx* c, dwos::WalkArgs<T>& a, dwos::Counters* tot 
     a.tot = tot ? tot : c->totals.as<dwos::Counters>() + (MODE ? 1 : 0);
     hipLaunchKernelGGL(dwos::fill_u64_kernel, dim3(1), dim3(64), 0, s, a.queue, (int64_t)1);
     if constexpr (MODE >= 1) {
-        if (a.cv_run) {   // the build with the control variate's bookkeeping
-            if constexpr (sizeof(T) == 4) {
-                if (c->variant == 1) return launch_shape<T, D, MODE, false, true>(c, a, timed);
-                return launch_shape<T, D, MODE, true, true>(c, a, timed);
-            } else {
-                return launch_shape<T, D, MODE, false, true>(c, a, timed);
-            }
-        }
+        if (a.cv_run) return launch_variant<T, D, MODE, true>(c, a, timed);   // with the control variate's bookkeeping
     }
-    if constexpr (sizeof(T) == 4) {
-        if (c->variant == 1) return launch_shape<T, D, MODE, false, false>(c, a, timed);
-        return launch_shape<T, D, MODE, true, false>(c, a, timed);
-    } else {
-        return launch_shape<T, D, MODE, false, false>(c, a, timed);
-    }
+    return launch_variant<T, D, MODE, false>(c, a, timed);
 }
 
-template <class T, int D, int MODE, bool staged, bool cv>
+template <class T, int D, int MODE, int STAGE, bool cv>
 dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     hipStream_t s = c->stream;
-    constexpr int block = staged ? dwos::kBlockStaged : dwos::kBlock;
-    const size_t smem = staged ? stage_bytes<T>(a.s, D) : 0;
-    auto kern = dwos::walk_kernel<T, D, MODE, staged, cv>;
+    constexpr int block = STAGE ? dwos::kBlockStaged : dwos::kBlock;
+    constexpr size_t entry = sizeof(dwos::StackEntry<T>);
+    const size_t staged = STAGE ? stage_bytes<T>(a.s, D) : 0;
+    const size_t room = STAGE ? (c->max_smem - 512 - staged) / (block * entry) : kMaxStack * 8 / entry;
+    a.stack_off = (uint32_t)staged;
+    a.stack_lds = (int32_t)std::min<size_t>(kMaxStack, room);
+    const size_t smem = staged + (size_t)a.stack_lds * block * entry;
+    auto kern = dwos::walk_kernel<T, D, MODE, STAGE, cv>;
     // launch attributes and occupancy are computed once per kernel and LDS
     // size (no runtime queries on later, possibly captured, calls)
     static size_t attr_smem = 0;
@@ -767,6 +796,7 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     }
     const int per_cu = occ_per_cu;
     const Split sp = split_walks(a.total, block, per_cu, c->cu_count, c->chunk, 16);
+    set_div(a);
     a.lanes = sp.lanes;
     a.chunk = sp.chunk;
     const unsigned grid = sp.grid;
@@ -827,6 +857,7 @@ dwos_status launch_wost(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         occ_lds = lds;
     }
     const Split sp = split_walks(a.total, block, occ_per_cu, c->cu_count, c->chunk, 1);
+    set_div(a);
     a.lanes = sp.lanes;
     a.chunk = sp.chunk;
     const unsigned grid = sp.grid;
@@ -894,6 +925,7 @@ dwos_status launch_wost3(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         occ_lds = lds;
     }
     const Split sp = split_walks(a.total, block, occ_per_cu, c->cu_count, c->chunk, 1);
+    set_div(a);
     a.lanes = sp.lanes;
     a.chunk = sp.chunk;
     const unsigned grid = sp.grid;
@@ -1449,6 +1481,7 @@ dwos_status launch_imp(dwos_ctx* c, dwos::WalkArgs<T>& a) {
     HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, block, lds));
     per = std::max(1, per);
     const Split sp = split_walks(a.total, block, per, c->cu_count, c->chunk, 16);
+    set_div(a);
     a.lanes = sp.lanes;
     a.chunk = sp.chunk;
     const unsigned grid = sp.grid;

@@ -33,15 +33,11 @@ namespace dwos {
 #endif
 constexpr int kParkLanes = DWOS_PARK;
 
-#ifndef DWOS_LDS_STACK
-#define DWOS_LDS_STACK 0
-#endif
 constexpr int kBlock = DWOS_BLOCK;          // threads per walk-kernel block
 #ifndef DWOS_BLOCK_STAGED
 #define DWOS_BLOCK_STAGED 1024
 #endif
 constexpr int kBlockStaged = DWOS_BLOCK_STAGED;  // block of the LDS-staged walk kernel
-constexpr bool kLdsStack = DWOS_LDS_STACK;  // traversal stack in LDS (else private memory)
 constexpr int kMaxLabels = 16;
 constexpr int kMaxGauss = 8;
 constexpr uint32_t kQueueChunk = 128;   // default walk ids taken per wavefront refill
@@ -97,6 +93,7 @@ struct WalkArgs {
     int32_t n_inst;
     const double* X;         // points, rows point_begin.. of each instance
     int32_t W;
+    uint32_t w_magic, w_shift;   // floor(n / W) = n w_magic >> w_shift for n < 2^31 (0: divide)
     int64_t total;           // walks in this launch
     int64_t wid_offset;      // logical id of walk 0 of this launch
     uint32_t key0, key1;
@@ -105,6 +102,8 @@ struct WalkArgs {
     int32_t park;            // lanes answered before a wavefront takes its step (1..64)
     uint32_t chunk;          // walk ids taken per wavefront refill (at least `lanes`)
     int32_t lanes;           // lanes of each wavefront that take walks (1..64)
+    int32_t stack_lds;       // traversal-stack entries of a lane kept in LDS ...
+    uint32_t stack_off;      // ... from this byte of the block's dynamic LDS on
     Counters* cnt;           // this call
     Counters* tot;           // cumulative for this walk kind
     // records (indexed by logical id - wid_offset)
@@ -327,29 +326,33 @@ __device__ __forceinline__ T slab_d2(const T* n, T o, T t, const T* x) {
 extern __shared__ float4 g_stage[];
 
 // Where a traversal reads nodes and primitives: LDS below the staged prefix,
-// global memory otherwise.  prim_off4 < 0: primitives stay in global memory.
+// global memory otherwise (prim_off4 < 0: primitives stay in global memory).
+// STAGE is fixed per build of a kernel, so that a traversal that never (or
+// only) reads LDS carries no second path: 0 global memory, 1 a prefix of the
+// nodes and perhaps every primitive, 2 everything.
+template <int STAGE>
 struct StageView {
     int32_t n_lnodes;
     int64_t prim_off4;
 };
 
-template <class T, int D>
-__device__ __forceinline__ void scene_node(const Scene<T>& s, const StageView& v, int32_t i,
+template <class T, int D, int STAGE>
+__device__ __forceinline__ void scene_node(const Scene<T>& s, const StageView<STAGE>& v, int32_t i,
                                            NodeData<T, D>& nd) {
-    if constexpr (sizeof(T) == 4) {
-        if (i < v.n_lnodes) {
-            decode_node_f32<D>(g_stage + (int64_t)i * (node_scalars(D) / 4), nd);
+    if constexpr (sizeof(T) == 4 && STAGE > 0) {
+        if (STAGE == 2 || i < v.n_lnodes) {
+            decode_node_f32<D>(g_stage + i * (node_scalars(D) / 4), nd);
             return;
         }
     }
     load_node<T, D>(s.nodes, i, nd);
 }
 
-template <class T, int D>
-__device__ __forceinline__ void scene_prim(const Scene<T>& s, const StageView& v, int32_t i, T* P) {
-    if constexpr (sizeof(T) == 4) {
-        if (v.prim_off4 >= 0) {
-            const float4* q = g_stage + v.prim_off4 + (int64_t)i * (prim_scalars(D) / 4);
+template <class T, int D, int STAGE>
+__device__ __forceinline__ void scene_prim(const Scene<T>& s, const StageView<STAGE>& v, int32_t i, T* P) {
+    if constexpr (sizeof(T) == 4 && STAGE > 0) {
+        if (STAGE == 2 || v.prim_off4 >= 0) {
+            const float4* q = g_stage + (int32_t)v.prim_off4 + i * (prim_scalars(D) / 4);
             if constexpr (D == 2) {
                 const float4 a = q[0];
                 P[0] = a.x; P[1] = a.y; P[2] = a.z; P[3] = a.w;
@@ -366,22 +369,72 @@ __device__ __forceinline__ void scene_prim(const Scene<T>& s, const StageView& v
 
 struct QueryCount { unsigned int nodes, prims, overflow; };
 
-// Traversal stack of (node, squared box distance) entries: per-lane private
-// arrays, or a slice of LDS interleaved across the block's lanes.
-template <class T, bool LDS> struct TravStack;
-template <class T> struct TravStack<T, false> {
+// Traversal stack of one lane: (node or leaf reference, squared bound)
+// entries, the first `n` in LDS, the rest (rarely reached) in private memory.
+// LDS is laid out [wavefront][entry][lane], so that the lanes of a wavefront
+// at one depth read consecutive words.
+template <class T> struct StackEntry;
+template <> struct StackEntry<float> { using vec = float __attribute__((ext_vector_type(2))); vec v; };
+template <> struct StackEntry<double> { using vec = double __attribute__((ext_vector_type(2))); vec v; };
+__device__ __forceinline__ float ref_bits(int32_t r, float) { return __int_as_float(r); }
+__device__ __forceinline__ int32_t bits_ref(float b) { return __float_as_int(b); }
+__device__ __forceinline__ double ref_bits(int32_t r, double) { return __hiloint2double(0, r); }
+__device__ __forceinline__ int32_t bits_ref(double b) { return __double2loint(b); }
+
+template <class T>
+struct StackSpill {
     int32_t node[kStackSize];
     T d[kStackSize];
-    __device__ __forceinline__ void put(int i, int32_t n, T v) { node[i] = n; d[i] = v; }
-    __device__ __forceinline__ int32_t get_node(int i) const { return node[i]; }
-    __device__ __forceinline__ T get_d(int i) const { return d[i]; }
 };
-template <class T> struct TravStack<T, true> {
-    int32_t* node;   // node[i * kBlock]
-    T* d;
-    __device__ __forceinline__ void put(int i, int32_t n, T v) { node[i * kBlock] = n; d[i * kBlock] = v; }
-    __device__ __forceinline__ int32_t get_node(int i) const { return node[i * kBlock]; }
-    __device__ __forceinline__ T get_d(int i) const { return d[i * kBlock]; }
+
+template <class T>
+struct LaneStack {
+    StackEntry<T>* lds;
+    int32_t n;               // at least 1
+    StackSpill<T>& rest;     // (an object of its own, so that the others stay in registers)
+    // `entries` per lane from byte `off` of the block's dynamic LDS
+    __device__ __forceinline__ LaneStack(int32_t entries, uint32_t off, StackSpill<T>& r)
+        : lds(reinterpret_cast<StackEntry<T>*>(reinterpret_cast<char*>(g_stage) + off) +
+              (threadIdx.x >> 6) * (unsigned)entries * 64u + (threadIdx.x & 63)),
+          n(entries), rest(r) {}
+    // (an entry beyond the private part is counted and dropped; the builder
+    // bounds the depth, so that there is none)
+    __device__ __forceinline__ void put(int i, int32_t node, T d, unsigned& overflow) {
+        if (__builtin_expect(i >= n, 0)) {
+            if (i - n < kStackSize) { rest.node[i - n] = node; rest.d[i - n] = d; }
+            else ++overflow;
+        } else {
+            lds[i * 64].v = typename StackEntry<T>::vec{d, ref_bits(node, d)};
+        }
+    }
+    // the LDS read is unconditional (of entry n - 1 beyond it), so that the
+    // two memories are not merged into one generic access
+    __device__ __forceinline__ void get(int i, int32_t& node, T& d) const {
+        const typename StackEntry<T>::vec e = lds[(i < n ? i : n - 1) * 64].v;
+        d = e.x;
+        node = bits_ref(e.y);
+        if (__builtin_expect(i >= n, 0)) {
+            const bool kept = i - n < kStackSize;
+            node = kept ? rest.node[i - n] : INT_MIN;   // dropped: go on to the entry below
+            d = kept ? rest.d[i - n] : T(0);
+        }
+    }
+};
+
+// The same in private memory alone.
+template <class T>
+struct PrivateStack {
+    int32_t pnode[kStackSize + 1];
+    T pd[kStackSize + 1];
+    __device__ __forceinline__ void put(int i, int32_t node, T d, unsigned& overflow) {
+        if (i <= kStackSize) { pnode[i] = node; pd[i] = d; }
+        else ++overflow;
+    }
+    __device__ __forceinline__ void get(int i, int32_t& node, T& d) const {
+        const bool kept = i <= kStackSize;
+        node = kept ? pnode[i] : INT_MIN;
+        d = kept ? pd[i] : T(0);
+    }
 };
 
 // DistanceToBoundary: nearest primitive to x through the pair-node BVH, as a
@@ -396,41 +449,36 @@ template <class T> struct TravStack<T, true> {
 // every lane holds a leaf or has finished, then test the held leaves
 // together, so that node and primitive work are not interleaved within one
 // iteration.
-// The traversal stack's R most recent entries are kept in registers (rn,
-// rd; rn[0] the newest); a push moves the oldest of them to the stack
-// memory only when all are in use, and a pop reads memory only when none is
-// left.  Depth-first descent alternates pushes and pops, so most entries
-// never reach memory (the stack's order is unchanged).  R = 8 in 2D: the
-// star's differential launch writes 0.56 GB of stack instead of 6.1 GB at
-// R = 3, for 4% more time; R = 5 in 3D, as fast as 3 on the icosphere (at
-// 8 the 3D kernel spills and slows by 6-8%).
-#ifndef DWOS_STACK_REGS_2D
-#define DWOS_STACK_REGS_2D 8
-#endif
-#ifndef DWOS_STACK_REGS_3D
-#define DWOS_STACK_REGS_3D 5
-#endif
+//
+// A lane's whole traversal state is one word, `cur`: a node to expand, a held
+// leaf, "take the next stack entry" or "answered".  The stack starts with an
+// entry that reads as "answered" and is nearer than any bound, so that
+// running out of entries needs no test of its own, and the next child and
+// the pushed one are selected without branches.  With the newest entries in
+// registers (shifted at every push and pop), the rest in private memory, and
+// the flags and the leaf in variables of their own, the inner loop had some 40
+// register moves and a dozen branches more a node: 3D diffusion step 49.2 ->
+// 39.3 ms, 4096-segment star step 3.84 -> 2.74 ms, 24-instance batch 16.6 ->
+// 13.7 ms, 128-gon probe 0.55 -> 0.46 ms with this form.
 template <class T, int D>
 struct Query {
-    static constexpr int R = D == 2 ? DWOS_STACK_REGS_2D : DWOS_STACK_REGS_3D;
     T best;          // squared distance of the best primitive so far
     int32_t bleaf;   // its leaf position, -1 none
-    int32_t node;    // internal node to expand next, or -1 (pop)
-    int32_t leaf;    // held leaf reference
-    int32_t sp;      // entries in stack memory
-    int32_t rt;      // register-held entries in use
-    int32_t rn[R];   // register-held entries: node reference
-    T rd[R];         // ... and squared bound distance
-    bool has_leaf, done;
+    int32_t cur;     // node >= 0, kDone, kPop, or a held leaf's reference
+    int32_t sp;      // entries on the stack
+    // (values below every leaf reference, ordered so that each test of the
+    // state is one unsigned comparison)
+    static constexpr int32_t kPop = INT_MIN, kDone = INT_MIN + 1;
+    __device__ __forceinline__ bool done() const { return cur == kDone; }
+    __device__ __forceinline__ bool descending() const { return (uint32_t)cur <= (uint32_t)kPop; }
+    __device__ __forceinline__ bool holds_leaf() const { return (uint32_t)cur > (uint32_t)kDone; }
 };
 
-template <class T, int D>
-__device__ __forceinline__ void query_test_prim(const Scene<T>& s, const StageView& sv, const T* x,
-                                                int32_t i, Query<T, D>& q, QueryCount& qc) {
-    T P[9], bb[3];
-    scene_prim<T, D>(s, sv, i, P);
+template <class T, int D, int STAGE>
+__device__ __forceinline__ void query_test_prim(const Scene<T>& s, const T* P, const T* x, int32_t i,
+                                                Query<T, D>& q) {
+    T bb[3];
     const T d2 = prim_closest<T, D>(P, x, bb);
-    qc.prims++;
     if (d2 < q.best * (T(1) - TieBand<T>::v)) { q.best = d2; q.bleaf = i; }
     else if (d2 <= q.best * (T(1) + TieBand<T>::v) && i != q.bleaf && q.bleaf >= 0 &&
              s.orig[i] < s.orig[q.bleaf]) {
@@ -439,9 +487,9 @@ __device__ __forceinline__ void query_test_prim(const Scene<T>& s, const StageVi
     }
 }
 
-template <class T, int D>
-__device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView& sv, int32_t root,
-                                            const T* x, int32_t warm, Query<T, D>& q) {
+template <class T, int D, int STAGE, class Stack>
+__device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView<STAGE>& sv, int32_t root,
+                                            const T* x, int32_t warm, Query<T, D>& q, Stack& st) {
     q.best = T(INFINITY);
     q.bleaf = -1;
     if (warm >= 0) {
@@ -450,116 +498,95 @@ __device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView& 
         q.best = prim_closest<T, D>(P, x, bb);
         q.bleaf = warm;
     }
-    q.node = root;
-    q.leaf = 0;
-    q.sp = 0;
-    q.has_leaf = false;
-    q.done = false;
-    q.rt = 0;
+    q.cur = root;
+    unsigned none = 0;
+    st.put(0, Query<T, D>::kDone, T(-1), none);
+    q.sp = 1;
 }
 
-// One round for the lanes with `active` set (a query in progress).
-// Phase 1 ends when no lane is descending, or (s.tail > 0) when at most
-// s.tail lanes are still descending while some lane holds a leaf for
-// phase 2; the descending lanes keep their position and go on in the next
-// round.  A round in which no lane holds a leaf always expands at least one
-// node per descending lane, so every query progresses.
+// One round for the lanes with a query in progress (the others, done(), pass
+// through).  Phase 1 ends when no lane is descending, or when at most `tail`
+// lanes are still descending while some lane holds a leaf for phase 2; the
+// descending lanes keep their position and go on in the next round.  A round
+// in which no lane holds a leaf always expands at least one node per
+// descending lane, so every query progresses.
 // Measured on the 200,000-triangle icosphere (65536 points x 1024 walks):
 // a tail of 8 lanes cuts the forward launch from 150 to 124 ms and the
 // differential launch from 171 to 141 ms (tails of 4 to 24 lanes give
 // 123-129 / 140-146 ms); on the 4096-gon star the differential launch goes
-// from 60 to 49 ms.  With three register-held stack entries instead of two
-// the icosphere launches take a further 1-2% less.
+// from 60 to 49 ms.
 #ifndef DWOS_DESCEND_TAIL
 #define DWOS_DESCEND_TAIL 8
 #endif
 constexpr int kDescendTail = DWOS_DESCEND_TAIL;
-template <class T, int D, class Stack>
-__device__ __forceinline__ void query_round(const Scene<T>& s, const StageView& sv, const T* x, bool active,
+template <class T, int D, int STAGE, class Stack>
+__device__ __forceinline__ void query_round(const Scene<T>& s, const StageView<STAGE>& sv, const T* x,
                                             Query<T, D>& q, QueryCount& qc, Stack& st, int tail) {
     using Q = Query<T, D>;
-    constexpr T slack = Slack<T>::v;
+    const T lim = q.best * Slack<T>::v;
     // phase 1: expand nodes until this lane holds a leaf or is finished
 #pragma unroll 1
     while (true) {
-        const bool go = active && !q.has_leaf && !q.done;
-        if (tail > 0) {
-            const unsigned long long gm = __ballot(go);
-            if (gm == 0ull) break;
-            if (__popcll(gm) <= tail && __ballot(active && q.has_leaf) != 0ull) break;
-            if (!go) continue;
-        } else if (!go) {
-            break;
-        }
-        int32_t cur = q.node;
-        if (cur < 0) {
+        const int n = __popcll(__ballot(q.descending()));
+        if (n <= (__ballot(q.holds_leaf()) != 0ull ? tail : 0)) break;
+        if (q.cur == Q::kPop) {
             T dd;
-            if (q.rt > 0) {
-                cur = q.rn[0];
-                dd = q.rd[0];
-#pragma unroll
-                for (int i = 0; i + 1 < Q::R; ++i) { q.rn[i] = q.rn[i + 1]; q.rd[i] = q.rd[i + 1]; }
-                --q.rt;
-            } else {
-                if (q.sp == 0) { q.done = true; continue; }
-                --q.sp;
-                cur = st.get_node(q.sp);
-                dd = st.get_d(q.sp);
-            }
-            if (dd > q.best * slack) continue;
-            if (cur < 0) { q.leaf = cur; q.has_leaf = true; continue; }   // a postponed leaf
+            int32_t node;
+            --q.sp;
+            st.get(q.sp, node, dd);
+            q.cur = dd > lim ? Q::kPop : node;
         }
-        NodeData<T, D> nd;
-        scene_node<T, D>(s, sv, cur, nd);
-        qc.nodes++;
-        const T d0 = fmax(box_d2<T, D>(nd.lo0, nd.hi0, x), slab_d2<T, D>(nd.n0, nd.o0, nd.t0, x));
-        const T d1 = fmax(box_d2<T, D>(nd.lo1, nd.hi1, x), slab_d2<T, D>(nd.n1, nd.o1, nd.t1, x));
-        const T lim = q.best * slack;
-        const bool h0 = d0 <= lim, h1 = d1 <= lim;
-        const bool near0 = d0 <= d1;
-        int32_t next = -1;
-        if (h0 && h1) {
-            if (q.sp + q.rt < kStackSize) {
-                if (q.rt == Q::R) {
-                    st.put(q.sp, q.rn[Q::R - 1], q.rd[Q::R - 1]);
-                    ++q.sp;
-                }
-#pragma unroll
-                for (int i = Q::R - 1; i > 0; --i) { q.rn[i] = q.rn[i - 1]; q.rd[i] = q.rd[i - 1]; }
-                q.rn[0] = near0 ? nd.c1 : nd.c0;
-                q.rd[0] = near0 ? d1 : d0;
-                q.rt = q.rt < Q::R ? q.rt + 1 : Q::R;
-            } else {
-                qc.overflow++;
+        if (q.cur >= 0) {
+            NodeData<T, D> nd;
+            scene_node<T, D>(s, sv, q.cur, nd);
+            qc.nodes++;
+            const T d0 = fmax(box_d2<T, D>(nd.lo0, nd.hi0, x), slab_d2<T, D>(nd.n0, nd.o0, nd.t0, x));
+            const T d1 = fmax(box_d2<T, D>(nd.lo1, nd.hi1, x), slab_d2<T, D>(nd.n1, nd.o1, nd.t1, x));
+            const bool h0 = d0 <= lim, h1 = d1 <= lim, near0 = d0 <= d1;
+            const bool both = h0 && h1;
+            const bool first = (both && near0) || (h0 && !h1);   // child 0 is next
+            q.cur = (h0 || h1) ? (first ? nd.c0 : nd.c1) : Q::kPop;
+            if (both) {
+                st.put(q.sp, first ? nd.c1 : nd.c0, first ? d1 : d0, qc.overflow);
+                ++q.sp;
             }
-            next = near0 ? nd.c0 : nd.c1;
-        } else if (h0) {
-            next = nd.c0;
-        } else if (h1) {
-            next = nd.c1;
         }
-        q.node = -1;
-        if (next >= 0) q.node = next;
-        else if (h0 || h1) { q.leaf = next; q.has_leaf = true; }   // -1 is the leaf {0}
     }
     // phase 2: every lane holding a leaf tests it
-    if (active && q.has_leaf) {
-        const int32_t v = -1 - q.leaf;
+    if (q.holds_leaf()) {
+        const int32_t v = -1 - q.cur;
         const int32_t start = v >> 3, n = (v & 7) + 1;
-        for (int32_t i = start; i < start + n; ++i) query_test_prim<T, D>(s, sv, x, i, q, qc);
-        q.has_leaf = false;
+        qc.prims += n;
+        if constexpr (D == 3) {   // the next primitive is loaded while one is tested
+            T P[9];
+            scene_prim<T, D>(s, sv, start, P);
+            for (int32_t i = start; i < start + n; ++i) {
+                T N[9];
+                scene_prim<T, D>(s, sv, i + 1 < start + n ? i + 1 : i, N);
+                query_test_prim<T, D, STAGE>(s, P, x, i, q);
+#pragma unroll
+                for (int k = 0; k < 9; ++k) P[k] = N[k];
+            }
+        } else {
+            for (int32_t i = start; i < start + n; ++i) {
+                T P[4];
+                scene_prim<T, D>(s, sv, i, P);
+                query_test_prim<T, D, STAGE>(s, P, x, i, q);
+            }
+        }
+        q.cur = Q::kPop;
     }
 }
 
 // A whole query (every lane runs its own to completion).
-template <class T, int D, class Stack>
-__device__ __forceinline__ int32_t closest_leaf(const Scene<T>& s, const StageView& sv, int32_t root,
+template <class T, int D, int STAGE, class Stack>
+__device__ __forceinline__ int32_t closest_leaf(const Scene<T>& s, const StageView<STAGE>& sv, int32_t root,
                                                 const T* x, int32_t warm, T& best, QueryCount& qc,
                                                 Stack& st) {
     Query<T, D> q;
-    query_begin<T, D>(s, sv, root, x, warm, q);
+    query_begin<T, D>(s, sv, root, x, warm, q, st);
 #pragma unroll 1
-    while (!q.done) query_round<T, D>(s, sv, x, true, q, qc, st, s.tail);
+    while (!q.done()) query_round<T, D>(s, sv, x, q, qc, st, s.tail);
     best = q.best;
     return q.bleaf;
 }
@@ -568,12 +595,12 @@ __device__ __forceinline__ int32_t closest_leaf(const Scene<T>& s, const StageVi
 // squared distance as closest_leaf when the closest primitive lies within
 // the bound, else -1 (best = bound2).  warm (or -1) with its squared
 // distance warm_d2 seeds the search as in closest_leaf.
-template <class T, int D, class Stack>
-__device__ __forceinline__ int32_t closest_leaf_within(const Scene<T>& s, const StageView& sv, int32_t root,
+template <class T, int D, int STAGE, class Stack>
+__device__ __forceinline__ int32_t closest_leaf_within(const Scene<T>& s, const StageView<STAGE>& sv, int32_t root,
                                                        const T* x, int32_t warm, T warm_d2, T bound2, T& best,
                                                        QueryCount& qc, Stack& st) {
     Query<T, D> q;
-    query_begin<T, D>(s, sv, root, x, -1, q);
+    query_begin<T, D>(s, sv, root, x, -1, q, st);
     if (warm >= 0 && warm_d2 < bound2) {
         q.best = warm_d2;
         q.bleaf = warm;
@@ -581,7 +608,7 @@ __device__ __forceinline__ int32_t closest_leaf_within(const Scene<T>& s, const 
         q.best = bound2;
     }
 #pragma unroll 1
-    while (!q.done) query_round<T, D>(s, sv, x, true, q, qc, st, s.tail);
+    while (!q.done()) query_round<T, D>(s, sv, x, q, qc, st, s.tail);
     best = q.best;
     return q.bleaf;
 }
@@ -718,6 +745,15 @@ __device__ __forceinline__ unsigned long long take_walks(const WalkArgs<T>& a, W
     return id;
 }
 
+// Point of walk n of an instance (W walks per point).  A launch's walks
+// number less than 2^31 in all but the largest batches, and a division by a
+// run-time W in 64 bits costs a new walk some 150 instructions.
+template <class T>
+__device__ __forceinline__ int64_t div_walks(const WalkArgs<T>& a, int64_t n) {
+    if (a.w_magic) return (int64_t)(((unsigned long long)(uint32_t)n * a.w_magic) >> a.w_shift);
+    return n / a.W;
+}
+
 // A lane count given for a full wavefront (park, tail), in proportion to the
 // lanes still live, at least lo: once the queue is empty, or where a launch
 // gives few walks to each wavefront, the count for 64 lanes would make every
@@ -739,37 +775,32 @@ __device__ __forceinline__ int live_share(int full, unsigned long long live, int
 //           ball), and D/R (s.n) (u(y) - g(xbar)) estimates du/dn; rec_uoff
 //           is g - delta times their mean, so that (g - rec_uoff)/delta is
 //           that estimate
-// The unstaged 3D kernel asks for six wavefronts per SIMD (at most 80
-// registers per lane, a few spilled): its closest-point queries wait on L2
-// and Infinity-Cache gathers, and the extra wavefronts hide that latency
-// (200,000-triangle icosphere: forward launch 117 -> 100 ms, differential
-// 162 -> 133 ms, against 106 / 136 ms at five and 107 / 156 ms at seven
-// wavefronts).  Since the registers were trimmed, the differential build
-// (MODE 1) is faster at five (at most 96 registers, fewer spills): 120.0 ->
-// 118.5 ms on the icosphere and 88.2 -> 86.9 ms on the 256-instance batch,
-// while the forward build loses 9-10% at five and stays at six.  The staged
-// kernel's 1024-thread block, the 2D scenes' LDS-resident trees and the FP64
-// reference build keep the compiler's choice.
-template <class T, int D, int MODE, bool STAGED>
+// The unstaged 3D kernel asks for five wavefronts per SIMD (at most 96
+// registers per lane, none spilled): it is bound by the issue of divergent
+// vector instructions (66% of SIMD cycles busy at 28% of lanes) and by the
+// latency of the node gathers, and five leave each lane 15 traversal-stack
+// entries in LDS.  3D diffusion step (200,000 triangles, 65536 points x 128
+// walks, forward and differential launch): 39.3 ms at five wavefronts and 15
+// entries, 40.5 at four and 19, 40.5 at six and 12, 45.4 at six and 6 entries,
+// 45.9 at seven and 10.  The staged kernel's 1024-thread block, the 2D
+// scenes' LDS-resident trees and the FP64 reference build keep the compiler's
+// choice.
+template <class T, int D, int MODE, int STAGE>
 struct WalkWaves {
-    static constexpr int v = (sizeof(T) == 4 && !STAGED && D == 3) ? (MODE == 1 ? 5 : 6) : 1;
+    static constexpr int v = (sizeof(T) == 4 && STAGE == 0 && D == 3) ? 5 : 1;
 };
 
 // CV: the build with the control variate's bookkeeping (MODE >= 1 with
 // a.cv_run set); without it the kernel carries none of that state.
-template <class T, int D, int MODE, bool STAGED, bool CV = false>
-__global__ void __launch_bounds__(STAGED ? kBlockStaged : kBlock) __attribute__((amdgpu_waves_per_eu(WalkWaves<T, D, MODE, STAGED>::v)))
+// STAGE: see StageView.
+template <class T, int D, int MODE, int STAGE, bool CV = false>
+__global__ void __launch_bounds__(STAGE ? kBlockStaged : kBlock) __attribute__((amdgpu_waves_per_eu(WalkWaves<T, D, MODE, STAGE>::v)))
 walk_kernel(WalkArgs<T> a) {
     const int lane = threadIdx.x & 63;
-    TravStack<T, kLdsStack && !STAGED> stack;
-    if constexpr (kLdsStack && !STAGED) {
-        __shared__ int32_t s_node[kStackSize * kBlock];
-        __shared__ T s_d[kStackSize * kBlock];
-        stack.node = s_node + threadIdx.x;
-        stack.d = s_d + threadIdx.x;
-    }
-    StageView sv{0, -1};
-    if constexpr (STAGED) {
+    StackSpill<T> spill;
+    LaneStack<T> stack(a.stack_lds, a.stack_off, spill);
+    StageView<STAGE> sv{0, -1};
+    if constexpr (STAGE > 0) {
         // copy the top BVH levels (and, if they fit, all primitives) into LDS
         // once per persistent block; every later node or primitive fetch
         // below the staged prefix is an LDS read
@@ -807,9 +838,10 @@ walk_kernel(WalkArgs<T> a) {
     T bvc_n[D], bvc_g = T(0), bvc_w = T(0);
 #pragma unroll
     for (int c = 0; c < D; ++c) bvc_n[c] = T(0);
-    // closest-point query in progress (resumable across iterations)
+    // closest-point query in progress (resumable across iterations); done()
+    // at the top of an iteration: the lane's next query is still to start
     Query<T, D> q;
-    bool qpend = false;
+    q.cur = Query<T, D>::kDone;
     // control-variate trace of the current nested walk
     T cv_S = T(0);
     T ysel[D], rho_sel = T(0), d_sel = T(0);
@@ -839,17 +871,22 @@ walk_kernel(WalkArgs<T> a) {
                     wid = (int64_t)myid;
                     const int64_t gid = wid + a.wid_offset;
                     int ii = 0;
-                    if (a.n_inst > 1) {   // instance containing walk gid
-                        int lo = 0, hi = a.n_inst - 1;
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (a.inst[mid].walk_begin <= gid) lo = mid; else hi = mid - 1;
+                    if (a.n_inst > 1) {   // instance containing walk gid: mostly the lane's last one
+                        ii = (int)(inst_tag >> 16);
+                        const bool same = a.inst[ii].walk_begin <= gid &&
+                                          (ii + 1 == a.n_inst || gid < a.inst[ii + 1].walk_begin);
+                        if (!same) {
+                            int lo = 0, hi = a.n_inst - 1;
+                            while (lo < hi) {
+                                const int mid = (lo + hi + 1) >> 1;
+                                if (a.inst[mid].walk_begin <= gid) lo = mid; else hi = mid - 1;
+                            }
+                            ii = lo;
                         }
-                        ii = lo;
                     }
                     const Instance<T> in = a.inst[ii];
                     const int64_t local = gid - in.walk_begin;
-                    int64_t pin = local / a.W;
+                    int64_t pin = div_walks(a, local);
                     m = (uint32_t)(local - pin * a.W);
                     if (a.perm) {   // the slot's point; records stay indexed by point
                         pin = a.perm[pin];
@@ -879,30 +916,24 @@ walk_kernel(WalkArgs<T> a) {
         // answer (or none is still searching); lanes whose query is
         // unfinished skip the rest of this iteration and resume it in the
         // next, so that fast queries do not wait for the slowest one.
-        bool ready = false;
         bool shared = false;   // answered by the point's shared first query
-        T d2 = T(0);
-        int32_t leaf = -1;
-        if (!qpend) {
+        if (q.done()) {
             if (a.first_leaf && phase == 0 && k == 0) {
-                leaf = a.first_leaf[first_row];
-                d2 = a.first_d2[first_row];
-                ready = true;
+                q.bleaf = a.first_leaf[first_row];
+                q.best = a.first_d2[first_row];
                 shared = true;
             } else {
-                query_begin<T, D>(a.s, sv, root, x, warm, q);
-                qpend = true;
+                query_begin<T, D>(a.s, sv, root, x, warm, q, stack);
             }
         }
         {
             QueryCount qc{0, 0, 0};
+            const int present = __popcll(live);
 #pragma unroll 1
             while (true) {
-                const bool searching = qpend && !q.done;
-                const unsigned long long sm = __ballot(searching);
-                const unsigned long long rm = __ballot(ready || (qpend && q.done));
-                if (sm == 0ull || __popcll(rm) >= park) break;
-                query_round<T, D>(a.s, sv, x, searching, q, qc, stack, tail);
+                const unsigned long long sm = __ballot(!q.done());
+                if (sm == 0ull || present - __popcll(sm) >= park) break;
+                query_round<T, D>(a.s, sv, x, q, qc, stack, tail);
             }
             c_nodes += qc.nodes; c_prims += qc.prims;
             if (qc.overflow) count_rare(&Counters::overflow, qc.overflow);
@@ -916,13 +947,9 @@ walk_kernel(WalkArgs<T> a) {
                 c_nodes = 0; c_prims = 0; c_steps = 0;
             }
         }
-        if (qpend && q.done) {
-            leaf = q.bleaf;
-            d2 = q.best;
-            qpend = false;
-            ready = true;
-        }
-        if (!ready) continue;
+        if (!q.done()) continue;
+        const int32_t leaf = q.bleaf;
+        const T d2 = q.best;
         // executed queries: the shared first query of a point (run once for
         // all its walks) counts once, on the point's walk 0
         if (!shared || m == 0) c_steps++;
@@ -955,16 +982,19 @@ walk_kernel(WalkArgs<T> a) {
             scene_prim<T, D>(a.s, sv, leaf, P);
             prim_closest<T, D>(P, x, bary);
             const int32_t orig = a.s.orig[leaf];
-            T V[9];
-            int32_t vid[3];
-            prim_vertices<T, D>(a.s, orig, V, vid);
+            // (a leaf's primitive holds its vertices, in their order)
             T xbar[3] = {T(0), T(0), T(0)};
 #pragma unroll
             for (int c = 0; c < D; ++c) {
                 T v = T(0);
 #pragma unroll
-                for (int kk = 0; kk < D; ++kk) v += bary[kk] * V[kk * D + c];
+                for (int kk = 0; kk < D; ++kk) v += bary[kk] * P[kk * D + c];
                 xbar[c] = v;
+            }
+            int32_t vid[3] = {0, 0, 0};
+            if (a.prm.kind[a.s.label[orig]] == 1) {   // mapped values are read by vertex
+#pragma unroll
+                for (int kk = 0; kk < D; ++kk) vid[kk] = a.s.pverts[(size_t)orig * D + kk];
             }
             const T g = boundary_value<T, D>(a.s, a.prm, orig, bary, xbar, vid);
             if (MODE >= 1 && phase == 0) {
@@ -975,7 +1005,7 @@ walk_kernel(WalkArgs<T> a) {
                 // the side test has no reliable sign.  A walk that starts in
                 // the shell uses its start point.
                 T n[3] = {T(0), T(0), T(0)};
-                geo_normal<T, D>(V, n);
+                geo_normal<T, D>(P, n);
                 T dn = T(0);
 #pragma unroll
                 for (int c = 0; c < D; ++c) dn += n[c] * (xbar[c] - (k > 0 ? xoff[c] : x[c]));

@@ -290,12 +290,8 @@ __device__ __forceinline__ void sil3_round(const RefScene3<T>& r, const T* x, in
         const bool h1 = !(nd.t1 < T(0)) && d1 < q.best && cone3_may_hold<T>(nd.lo1, nd.hi1, cq + kEdgeCone, x);
         if (h0 && h1) {
             const bool n0 = d0 <= d1;
-            if (q.sp < kStackSize) {
-                st.put(q.sp, n0 ? nd.c1 : nd.c0, n0 ? d1 : d0);
-                ++q.sp;
-            } else {
-                qc.overflow++;
-            }
+            st.put(q.sp, n0 ? nd.c1 : nd.c0, n0 ? d1 : d0, qc.overflow);
+            ++q.sp;
             q.cur = n0 ? nd.c0 : nd.c1;
         } else if (h0) {
             q.cur = nd.c0;
@@ -387,12 +383,8 @@ __device__ int32_t ray3_first(const RefScene3<T>& r, const T* x, const T* dir, T
             const bool h0 = e0 <= best, h1 = e1 <= best;
             if (h0 && h1) {
                 const bool n0 = e0 <= e1;
-                if (sp < kStackSize) {
-                    st.put(sp, n0 ? nd.c1 : nd.c0, n0 ? e1 : e0);
-                    ++sp;
-                } else {
-                    qc.overflow++;
-                }
+                st.put(sp, n0 ? nd.c1 : nd.c0, n0 ? e1 : e0, qc.overflow);
+                ++sp;
                 cur = n0 ? nd.c0 : nd.c1;
             } else if (h0) {
                 cur = nd.c0;
@@ -446,8 +438,11 @@ __device__ int32_t ray3_first(const RefScene3<T>& r, const T* x, const T* dir, T
 #pragma unroll 1
             while (sp > 0) {
                 --sp;
-                if (st.get_d(sp) <= best) {
-                    cur = st.get_node(sp);
+                int32_t node;
+                T dd;
+                st.get(sp, node, dd);
+                if (dd <= best) {
+                    cur = node;
                     have = true;
                     break;
                 }
@@ -483,12 +478,8 @@ __device__ int32_t ref3_boundary_sample(const RefScene3<T>& r, const T* x, T R, 
             const bool h1 = !(nd.t1 < T(0)) &&
                             fmax(box_d2<T, 3>(nd.lo1, nd.hi1, x), slab_d2<T, 3>(nd.n1, nd.o1, nd.t1, x)) < R2;
             if (h0 && h1) {
-                if (sp < kStackSize) {
-                    st.put(sp, nd.c1, T(0));
-                    ++sp;
-                } else {
-                    qc.overflow++;
-                }
+                st.put(sp, nd.c1, T(0), qc.overflow);
+                ++sp;
                 cur = nd.c0;
             } else if (h0) {
                 cur = nd.c0;
@@ -524,7 +515,8 @@ __device__ int32_t ref3_boundary_sample(const RefScene3<T>& r, const T* x, T R, 
         }
         if (!have && sp > 0) {
             --sp;
-            cur = st.get_node(sp);
+            T dd;
+            st.get(sp, cur, dd);
             have = true;
         }
     }
@@ -565,8 +557,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Wos
 wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
     constexpr int D = 3;
     const int lane = threadIdx.x & 63;
-    TravStack<T, false> stack;
-    StageView sv{0, -1};
+    PrivateStack<T> stack;
+    StageView<sizeof(T) == 4 ? 1 : 0> sv{0, -1};
     if constexpr (sizeof(T) == 4) {
         // LDS: the Dirichlet BVH's first nodes (and its primitives when they fit)
         const int64_t nn4 = (int64_t)a.s.n_stage_nodes * (node_scalars(D) / 4);
@@ -1005,7 +997,7 @@ __global__ void ref3_query_kernel(RefScene3<T> ref, const double* X, const doubl
     }
     const int32_t on = oo >= 0 ? ref.tleaf_of[oo] : -1;
     QueryCount qc{0, 0, 0};
-    TravStack<T, false> st;
+    PrivateStack<T> st;
     const T c = T(cap[i]);
     out[3 * i] = double(sqrt(silhouette3_d2<T>(ref, x, on, nn, c * c, qc, st)));
     T t;

@@ -140,12 +140,8 @@ __device__ int32_t ref_boundary_sample(const RefScene<T>& r, const T* x, T R, u4
             const bool h1 = !(nd.t1 < T(0)) &&
                             fmax(box_d2<T, 2>(nd.lo1, nd.hi1, x), slab_d2<T, 2>(nd.n1, nd.o1, nd.t1, x)) < R2;
             if (h0 && h1) {
-                if (sp < kStackSize) {
-                    st.put(sp, nd.c1, T(0));
-                    ++sp;
-                } else {
-                    qc.overflow++;
-                }
+                st.put(sp, nd.c1, T(0), qc.overflow);
+                ++sp;
                 cur = nd.c0;
             } else if (h0) {
                 cur = nd.c0;
@@ -178,7 +174,8 @@ __device__ int32_t ref_boundary_sample(const RefScene<T>& r, const T* x, T R, u4
         }
         if (!have && sp > 0) {
             --sp;
-            cur = st.get_node(sp);
+            T dd;
+            st.get(sp, cur, dd);
             have = true;
         }
     }
@@ -318,8 +315,11 @@ __device__ __forceinline__ void sil_pop(SilQuery<T>& q, Stack& st) {
 #pragma unroll 1
     while (q.sp > 0) {
         --q.sp;
-        if (st.get_d(q.sp) < q.best) {
-            q.cur = st.get_node(q.sp);
+        int32_t node;
+        T dd;
+        st.get(q.sp, node, dd);
+        if (dd < q.best) {
+            q.cur = node;
             q.have = true;
             break;
         }
@@ -358,12 +358,8 @@ __device__ __forceinline__ void sil_round(const RefScene<T>& r, const T* x, int3
         const bool h1 = d1 < q.best && cone_may_hold<T>(nd.lo1, nd.hi1, qn + kRefCone, x);
         if (h0 && h1) {
             const bool n0 = d0 <= d1;
-            if (q.sp < kStackSize) {
-                st.put(q.sp, n0 ? nd.c1 : nd.c0, n0 ? d1 : d0);
-                ++q.sp;
-            } else {
-                qc.overflow++;
-            }
+            st.put(q.sp, n0 ? nd.c1 : nd.c0, n0 ? d1 : d0, qc.overflow);
+            ++q.sp;
             q.cur = n0 ? nd.c0 : nd.c1;
         } else if (h0) {
             q.cur = nd.c0;
@@ -468,12 +464,8 @@ __device__ int32_t ray_first(const RefScene<T>& r, const T* x, const T* dir, T t
             const bool h0 = e0 <= best, h1 = e1 <= best;
             if (h0 && h1) {
                 const bool n0 = e0 <= e1;
-                if (sp < kStackSize) {
-                    st.put(sp, n0 ? nd.c1 : nd.c0, n0 ? e1 : e0);
-                    ++sp;
-                } else {
-                    qc.overflow++;
-                }
+                st.put(sp, n0 ? nd.c1 : nd.c0, n0 ? e1 : e0, qc.overflow);
+                ++sp;
                 cur = n0 ? nd.c0 : nd.c1;
             } else if (h0) {
                 cur = nd.c0;
@@ -523,8 +515,11 @@ __device__ int32_t ray_first(const RefScene<T>& r, const T* x, const T* dir, T t
 #pragma unroll 1
             while (sp > 0) {
                 --sp;
-                if (st.get_d(sp) <= best) {
-                    cur = st.get_node(sp);
+                int32_t node;
+                T dd;
+                st.get(sp, node, dd);
+                if (dd <= best) {
+                    cur = node;
                     have = true;
                     break;
                 }
@@ -584,8 +579,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Wos
 wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
     constexpr int D = 2;
     const int lane = threadIdx.x & 63;
-    TravStack<T, false> stack;
-    StageView sv{0, -1};
+    PrivateStack<T> stack;
+    StageView<sizeof(T) == 4 ? 1 : 0> sv{0, -1};
     if constexpr (sizeof(T) == 4) {
         // LDS: the Dirichlet BVH's first nodes (and its primitives when they
         // fit), then the reflecting BVH's top nodes and their cones
@@ -976,7 +971,7 @@ __global__ void ref_query_kernel(RefScene<T> ref, const double* X, const double*
     }
     const int32_t on = oo >= 0 ? ref.leaf_of[oo] : -1;
     QueryCount qc{0, 0, 0};
-    TravStack<T, false> st;
+    PrivateStack<T> st;
     const T c = T(cap[i]);
     out[3 * i] = double(sqrt(silhouette_d2<T>(ref, x, on, nn, c * c, qc, st)));
     T t;
