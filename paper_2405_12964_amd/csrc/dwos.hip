@@ -291,6 +291,10 @@ std::vector<T> pack_nodes(int D, const std::vector<dwos::HostNode>& hn) {
     return nodes;
 }
 
+// 2 sin(s0/2) + kappa of a silhouette cone from its stored cos s0
+template <class T>
+T spread_of(T cos_s0, double kappa) { return std::sqrt(std::max(T(0), T(2) - T(2) * cos_s0)) + T(kappa); }
+
 // Reflecting segments: BVH nodes, per-segment geometry and adjacency in
 // leaf order (the layout of wost_kernels.hpp's RefScene).  inc[v]: the
 // segments at vertex v.
@@ -327,7 +331,11 @@ dwos_status upload_reflecting(dwos_ctx* c, const double* V, const int32_t* segs,
         for (int ch = 0; ch < 2; ++ch) {
             T* q = &cones[(ni * 2 + ch) * dwos::kRefCone];
             q[0] = T(0); q[1] = T(0); q[2] = T(2); q[3] = T(-1);   // never pruned
-            q[4] = T(0); q[5] = T(0); q[6] = T(0); q[7] = T(0);
+            q[4] = T(0); q[5] = T(0); q[6] = T(2);
+            // radius of the child box's bounding circle, as the kernel sees the box
+            const T* box = &nodes[ni * dwos::node_scalars(2) + 4 * ch];
+            const double ex = 0.5 * (double(box[2]) - double(box[0])), ey = 0.5 * (double(box[3]) - double(box[1]));
+            q[7] = ex >= 0 && ey >= 0 ? T(std::sqrt(ex * ex + ey * ey)) : T(0);
             const int32_t b0 = bvh.nodes[ni].range[ch][0], b1 = bvh.nodes[ni].range[ch][1];
             std::vector<double> nrm;
             bool forced = b1 <= b0;
@@ -374,7 +382,7 @@ dwos_status upload_reflecting(dwos_ctx* c, const double* V, const int32_t* segs,
             }
             const double tol = sizeof(T) == 4 ? 1e-4 : 1e-10;
             q[0] = T(ax); q[1] = T(ay); q[2] = T(std::sin(s0)); q[3] = T(std::cos(s0));
-            q[4] = T(omin); q[5] = T(omax); q[6] = T(4.0 * tol); q[7] = T(0);
+            q[4] = T(omin); q[5] = T(omax); q[6] = spread_of(q[3], 4.0 * tol);
         }
     hipStream_t s = c->stream;
     HIP_OK(upload(c->ref_cones, cones.data(), cones.size(), s));
@@ -502,7 +510,7 @@ dwos_status upload_reflecting3(dwos_ctx* c, const double* V, const int32_t* tris
     for (size_t ni = 0; ni < eb.nodes.size(); ++ni)
         for (int ch = 0; ch < 2; ++ch) {
             T* q = &cones[(ni * 2 + ch) * dwos::kEdgeCone];
-            q[3] = T(2); q[4] = T(-1);   // never pruned
+            q[3] = T(2); q[4] = T(-1); q[7] = T(2);   // never pruned
             const int32_t b0 = eb.nodes[ni].range[ch][0], b1 = eb.nodes[ni].range[ch][1];
             if (b1 <= b0) continue;
             nrm.clear();
@@ -557,7 +565,8 @@ dwos_status upload_reflecting3(dwos_ctx* c, const double* V, const int32_t* tris
             const double tol = sizeof(T) == 4 ? 1e-4 : 1e-10;
             const double kappa = min_sin > 0.0 ? 4.0 * tol / min_sin : HUGE_VAL;
             q[0] = T(ax); q[1] = T(ay); q[2] = T(az); q[3] = T(std::sin(s0)); q[4] = T(std::cos(s0));
-            q[5] = T(omin); q[6] = T(omax); q[7] = T(kappa);
+            q[5] = T(omin); q[6] = T(omax);
+            q[7] = spread_of(q[4], kappa);
         }
     hipStream_t s = c->stream;
     HIP_OK(upload(c->ref_econes, cones.data(), cones.size(), s));
@@ -822,6 +831,13 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     return DWOS_OK;
 }
 
+// Walk on stars: traversal-stack entries of a lane in LDS (8 bytes each, 2 KB
+// per entry and block), within the 40 KB of a block that leave four blocks per
+// CU.  2D: 10 entries and 32 staged reflecting nodes 144.8 ms per thermal step,
+// 8 and 64 149 ms, 6 and 128 (three blocks per CU) 166 ms; 3D: 8 entries
+// 420-440 ms, 6 447 ms.
+constexpr int kStarStack2 = 10, kStarStack3 = 8, kStarRefNodes = 32;
+
 // Launch the persistent walk-on-stars kernel (2D, reflecting boundary).
 template <class T, int MODE>
 dwos_status launch_wost(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
@@ -835,19 +851,23 @@ dwos_status launch_wost(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
     size_t lds = 0;
     if constexpr (sizeof(T) == 4) {
         // LDS per block (a few blocks per CU): up to 256 Dirichlet nodes, its
-        // primitives up to 16 KB, the reflecting BVH's first 128 nodes
+        // primitives up to 16 KB, the reflecting BVH's first nodes, the stacks
         a.s.n_stage_nodes = (int32_t)std::min<int64_t>(c->n_nodes, 256);
         a.s.stage_prims = c->np * (int64_t)(dwos::prim_scalars(2) * sizeof(T)) <= 16384 ? 1 : 0;
-        ref.n_stage = (int32_t)std::min<int64_t>(c->ref_nn, 128);
+        ref.n_stage = (int32_t)std::min<int64_t>(c->ref_nn, kStarRefNodes);
         const int64_t w_nodes = dwos::node_scalars(2) / 4;
         ref.stage_off4 = (int64_t)a.s.n_stage_nodes * w_nodes + (a.s.stage_prims ? c->np : 0);
         lds = (size_t)(ref.stage_off4 + (int64_t)ref.n_stage * (w_nodes + 2 * dwos::kRefCone / 4)) * 16;
+        a.stack_lds = kStarStack2;
     } else {
+        a.stack_lds = kStarStack2 / 2;
         a.s.n_stage_nodes = 0;
         a.s.stage_prims = 0;
         ref.n_stage = 0;
         ref.stage_off4 = 0;
     }
+    a.stack_off = (uint32_t)lds;
+    lds += (size_t)a.stack_lds * block * sizeof(dwos::StackEntry<T>);
     static size_t occ_lds = ~size_t(0);
     static int occ_per_cu = 1;
     if (occ_lds != lds) {
@@ -896,7 +916,7 @@ dwos_status launch_wost3(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
     size_t lds = 0;
     dwos::RefScene3<T> ref = make_ref3<T>(c);
     if constexpr (sizeof(T) == 4) {
-        // LDS per block (40 KB: four 256-thread blocks per CU): up to 64
+        // LDS per block (40 KB with the stacks: four 256-thread blocks per CU): up to 64
         // Dirichlet nodes and its primitives up to 16 KB (the Dirichlet query
         // mostly runs bounded by the star radius), then as many of the edge
         // BVH's first nodes with their cones as fit (every silhouette query
@@ -906,16 +926,20 @@ dwos_status launch_wost3(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         lds = (size_t)a.s.n_stage_nodes * dwos::node_scalars(3) * sizeof(T) +
               (a.s.stage_prims ? (size_t)c->np * dwos::prim_scalars(3) * sizeof(T) : 0);
         const size_t per_edge = (size_t)(dwos::node_scalars(3) + 2 * dwos::kEdgeCone) * sizeof(T);
-        const size_t budget = 40 * 1024;
+        const size_t budget = 40 * 1024 - (size_t)kStarStack3 * block * sizeof(dwos::StackEntry<float>);
         lds = (lds + 15) & ~size_t(15);
         ref.n_estage = lds < budget ? (int32_t)std::min<int64_t>(c->ref_enn, (int64_t)((budget - lds) / per_edge)) : 0;
         if (c->stage_cap >= 0) ref.n_estage = std::min<int32_t>(ref.n_estage, c->stage_cap);
         ref.estage_off4 = (int64_t)(lds / 16);
         lds += (size_t)ref.n_estage * per_edge;
+        a.stack_lds = kStarStack3;
     } else {
         a.s.n_stage_nodes = 0;
         a.s.stage_prims = 0;
+        a.stack_lds = kStarStack3 / 2;
     }
+    a.stack_off = (uint32_t)lds;
+    lds += (size_t)a.stack_lds * block * sizeof(dwos::StackEntry<T>);
     static size_t occ_lds = ~size_t(0);
     static int occ_per_cu = 1;
     if (occ_lds != lds) {

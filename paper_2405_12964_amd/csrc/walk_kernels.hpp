@@ -763,6 +763,26 @@ __device__ __forceinline__ int live_share(int full, unsigned long long live, int
     return n > lo ? n : lo;
 }
 
+// Statistics of a wavefront: wave sums, then one atomic per counter.
+template <class T>
+__device__ __forceinline__ void add_counts(const WalkArgs<T>& a, int lane, uint32_t walks, uint32_t nested,
+                                           uint32_t steps, uint32_t term, uint32_t nodes, uint32_t prims) {
+    const unsigned long long s_walks = wave_sum_u64(walks), s_nested = wave_sum_u64(nested);
+    const unsigned long long s_steps = wave_sum_u64(steps), s_term = wave_sum_u64(term);
+    const unsigned long long s_nodes = wave_sum_u64(nodes), s_prims = wave_sum_u64(prims);
+    if (lane != 0) return;
+    Counters* dst[2] = {a.cnt, a.tot};
+    for (int q = 0; q < 2; ++q) {
+        Counters* c = dst[q];
+        atomicAdd(&c->walks, s_walks);
+        atomicAdd(&c->nested, s_nested);
+        atomicAdd(&c->steps, s_steps);
+        atomicAdd(&c->terminal, s_term);
+        atomicAdd(&c->nodes, s_nodes);
+        atomicAdd(&c->prims, s_prims);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // the walk kernel
 //   MODE 0: Algorithm 1 (forward walks): rec_u = walk estimate
@@ -1194,25 +1214,7 @@ walk_kernel(WalkArgs<T> a) {
             }
         }
     }
-    // ---- statistics: wave sums, then one atomic per counter per wave -------
-    const unsigned long long s_walks = wave_sum_u64(c_walks);
-    const unsigned long long s_nested = wave_sum_u64(c_nested);
-    const unsigned long long s_steps = wave_sum_u64(c_steps);
-    const unsigned long long s_term = wave_sum_u64(c_term);
-    const unsigned long long s_nodes = wave_sum_u64(c_nodes);
-    const unsigned long long s_prims = wave_sum_u64(c_prims);
-    if (lane == 0) {
-        Counters* dst[2] = {a.cnt, a.tot};
-        for (int q = 0; q < 2; ++q) {
-            Counters* c = dst[q];
-            atomicAdd(&c->walks, s_walks);
-            atomicAdd(&c->nested, s_nested);
-            atomicAdd(&c->steps, s_steps);
-            atomicAdd(&c->terminal, s_term);
-            atomicAdd(&c->nodes, s_nodes);
-            atomicAdd(&c->prims, s_prims);
-        }
-    }
+    add_counts(a, lane, c_walks, c_nested, c_steps, c_term, c_nodes, c_prims);
 }
 
 }  // namespace dwos

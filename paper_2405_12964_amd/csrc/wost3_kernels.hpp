@@ -50,7 +50,8 @@ constexpr int kEdgeGeo = 12;
 
 // Normal cones of the silhouette query, per edge-BVH node and child (8
 // scalars: a unit axis a[3], sin and cos of s0 = theta + margin, the range
-// [omin, omax] of a.p over the child's edge vertices p, and kappa), theta
+// [omin, omax] of a.p over the child's edge vertices p, and 2 sin(s0/2) +
+// kappa), theta
 // the largest angle between a and the left normals of the triangles at the
 // child's edges.  Seen from x, an edge of two consistently wound triangles
 // is a silhouette only if x is in front of one triangle's plane and behind
@@ -208,31 +209,17 @@ __device__ __forceinline__ bool sil3_edge_nearer(const RefScene3<T>& r, int32_t 
 
 // Can the child with box lo..hi and cone q hold a silhouette edge seen from x?
 template <class T>
-__device__ __forceinline__ bool cone3_may_hold(const T* lo, const T* hi, const T* q, const T* x) {
-    if (!(q[3] <= T(1))) return true;      // never pruned
-    T c[3], r2 = T(0), d2 = T(0), mag = T(0);
+__device__ __forceinline__ bool cone3_keeps(const T* lo, const T* hi, const T* q, const T* x, T xmag) {
+    T c[3], r2 = T(0), d2 = T(0), mag = xmag;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         c[k] = T(0.5) * (lo[k] + hi[k]) - x[k];
         const T e = T(0.5) * (hi[k] - lo[k]);
         r2 += e * e;
         d2 += c[k] * c[k];
-        mag += fabs(x[k]) + fabs(lo[k]) + fabs(hi[k]);
+        mag += fabs(lo[k]) + fabs(hi[k]);
     }
-    {   // planes: x in front of (or behind) every triangle plane of the child
-        const T ulp = sizeof(T) == 4 ? T(1.1920929e-07) : T(2.220446049250313e-16);
-        const T ax = q[0] * x[0] + q[1] * x[1] + q[2] * x[2];
-        const T dmax = sqrt(d2) + sqrt(r2);
-        const T marg = (sqrt(fmax(T(0), T(2) - T(2) * q[4])) + q[7]) * dmax + T(32) * ulp * (mag + dmax);
-        if (ax - q[6] > marg || q[5] - ax > marg) return false;
-    }
-    if (!(d2 > r2)) return true;           // x inside the bounding sphere
-    const T inv = T(1) / sqrt(d2);
-    const T sb = sqrt(r2) * inv, cb = sqrt(T(1) - sb * sb);
-    const T cs = q[4] * cb - q[3] * sb;   // cos(s0 + beta)
-    if (!(cs > T(0))) return true;
-    const T ss = q[3] * cb + q[4] * sb;   // sin(s0 + beta)
-    return !(fabs((q[0] * c[0] + q[1] * c[1] + q[2] * c[2]) * inv) > ss);
+    return cone_keeps<T>(d2, bound_sqrt(r2), dot3d<T>(q, c), dot3d<T>(q, x), q[3], q[4], q[5], q[6], q[7], mag);
 }
 
 // An edge-BVH node and its children's cones, from LDS for the staged prefix.
@@ -257,6 +244,23 @@ __device__ __forceinline__ void edge_node3(const RefScene3<T>& r, int32_t i, Nod
     for (int k = 0; k < 2 * kEdgeCone; ++k) cq[k] = g[k];
 }
 
+// box_d2 in 3D with the order of its sum spelled out (FP32, fused): component
+// FIRST's square is the rounded one.  Where the closest silhouette point is a
+// vertex of the box, this bound and the distances of the edges that share the
+// vertex differ by rounding alone, so the order decides which of them is
+// tested, and the walk's next position by one unit of rounding.
+template <int FIRST>
+__device__ __forceinline__ float box3_d2(const float* lo, const float* hi, const float* x) {
+    float e[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) e[i] = fmaxf(fmaxf(lo[i] - x[i], x[i] - hi[i]), 0.0f);
+    return __builtin_fmaf(e[2], e[2], __builtin_fmaf(e[1 - FIRST], e[1 - FIRST], e[FIRST] * e[FIRST]));
+}
+template <int FIRST>
+__device__ __forceinline__ double box3_d2(const double* lo, const double* hi, const double* x) {
+    return box_d2<double, 3>(lo, hi, x);
+}
+
 // Closest silhouette edge as a resumable query, as sil_round in 2D; x lies
 // on leaf triangle `on` (domain side nin) or inside (-1).  A round expands
 // nodes until the lane holds a leaf or is answered, then the lanes holding
@@ -265,51 +269,50 @@ __device__ __forceinline__ void edge_node3(const RefScene3<T>& r, int32_t i, Nod
 // the next round), as in the closest-point query.  Each lane visits the same
 // nodes and edges in the same order whatever the tail, so the answer and
 // the edge found do not depend on it.
-template <class T, class Stack>
+template <int FIRST, class T, class Stack>
 __device__ __forceinline__ void sil3_round(const RefScene3<T>& r, const T* x, int32_t on, const T* nin,
                                            SilQuery<T>& q, QueryCount& qc, Stack& st, int tail = 0) {
+    using Q = SilQuery<T>;
+    const T xmag = fabs(x[0]) + fabs(x[1]) + fabs(x[2]);
     // phase 1: expand nodes
 #pragma unroll 1
     while (true) {
-        const bool go = q.have && q.cur >= 0;
-        if (tail > 0) {
-            const unsigned long long gm = __ballot(go);
-            if (gm == 0ull) break;
-            if (__popcll(gm) <= tail && __ballot(q.have && q.cur < 0) != 0ull) break;
-            if (!go) continue;
-        } else if (!go) {
-            break;
+        const int n = __popcll(__ballot(q.descending()));
+        if (n <= (__ballot(q.holds_leaf()) != 0ull ? tail : 0)) break;
+        if (q.cur == Q::kPop) {
+            T dd;
+            int32_t node;
+            --q.sp;
+            st.get(q.sp, node, dd);
+            q.cur = dd < q.best ? node : Q::kPop;
         }
-        NodeData<T, 3> nd;
-        T cq[2 * kEdgeCone];
-        edge_node3<T>(r, q.cur, nd, cq);
-        qc.nodes++;
-        const T d0 = fmax(box_d2<T, 3>(nd.lo0, nd.hi0, x), slab_d2<T, 3>(nd.n0, nd.o0, nd.t0, x));
-        const T d1 = fmax(box_d2<T, 3>(nd.lo1, nd.hi1, x), slab_d2<T, 3>(nd.n1, nd.o1, nd.t1, x));
-        const bool h0 = !(nd.t0 < T(0)) && d0 < q.best && cone3_may_hold<T>(nd.lo0, nd.hi0, cq, x);
-        const bool h1 = !(nd.t1 < T(0)) && d1 < q.best && cone3_may_hold<T>(nd.lo1, nd.hi1, cq + kEdgeCone, x);
-        if (h0 && h1) {
-            const bool n0 = d0 <= d1;
-            st.put(q.sp, n0 ? nd.c1 : nd.c0, n0 ? d1 : d0, qc.overflow);
-            ++q.sp;
-            q.cur = n0 ? nd.c0 : nd.c1;
-        } else if (h0) {
-            q.cur = nd.c0;
-        } else if (h1) {
-            q.cur = nd.c1;
-        } else {
-            sil_pop<T>(q, st);
+        if (q.cur >= 0) {
+            NodeData<T, 3> nd;
+            T cq[2 * kEdgeCone];
+            edge_node3<T>(r, q.cur, nd, cq);
+            qc.nodes++;
+            const T d0 = fmax(box3_d2<FIRST>(nd.lo0, nd.hi0, x), slab_d2<T, 3>(nd.n0, nd.o0, nd.t0, x));
+            const T d1 = fmax(box3_d2<FIRST>(nd.lo1, nd.hi1, x), slab_d2<T, 3>(nd.n1, nd.o1, nd.t1, x));
+            const bool k0 = cone3_keeps<T>(nd.lo0, nd.hi0, cq, x, xmag);
+            const bool k1 = cone3_keeps<T>(nd.lo1, nd.hi1, cq + kEdgeCone, x, xmag);
+            const bool h0 = !(nd.t0 < T(0)) && d0 < q.best && k0, h1 = !(nd.t1 < T(0)) && d1 < q.best && k1;
+            const bool near0 = d0 <= d1, both = h0 && h1;
+            const bool first = (both && near0) || (h0 && !h1);
+            q.cur = (h0 || h1) ? (first ? nd.c0 : nd.c1) : Q::kPop;
+            if (both) {
+                st.put(q.sp, first ? nd.c1 : nd.c0, first ? d1 : d0, qc.overflow);
+                ++q.sp;
+            }
         }
     }
     // phase 2: the lanes holding a leaf test its edges
-    if (q.have && q.cur < 0) {
+    if (q.holds_leaf()) {
         const int32_t v = -1 - q.cur;
         const int32_t start = v >> 3, n = (v & 7) + 1;
-        for (int32_t i = start; i < start + n; ++i) {
-            qc.prims++;
+        qc.prims += n;
+        for (int32_t i = start; i < start + n; ++i)
             if (sil3_edge_nearer<T>(r, i, x, on, nin, q.best)) q.bsil = i;
-        }
-        sil_pop<T>(q, st);
+        q.cur = Q::kPop;
     }
 }
 
@@ -317,9 +320,9 @@ template <class T, class Stack>
 __device__ T silhouette3_d2(const RefScene3<T>& r, const T* x, int32_t on, const T* nin, T best, QueryCount& qc,
                             Stack& st) {
     SilQuery<T> q;
-    sil_begin<T>(q, best);
+    sil_begin<T>(q, best, -1, st);
 #pragma unroll 1
-    while (q.have) sil3_round<T>(r, x, on, nin, q, qc, st);
+    while (!q.done()) sil3_round<0>(r, x, on, nin, q, qc, st);
     return q.best;
 }
 
@@ -343,13 +346,13 @@ __device__ __forceinline__ T ray_child3(const T* lo, const T* hi, const T* n, T 
     const T pn = n[0] * dir[0] + n[1] * dir[1] + n[2] * dir[2];
     const T q = n[0] * x[0] + n[1] * x[1] + n[2] * x[2] - o;
     if (pn != T(0)) {
-        const T s1 = (-th - q) / pn, s2 = (th - q) / pn;
+        const T s1 = quot<T>(-th - q, pn), s2 = quot<T>(th - q, pn);
         tn = fmax(tn, fmin(s1, s2));
         tf = fmin(tf, fmax(s1, s2));
     } else if (fabs(q) > th) {
         return T(INFINITY);
     }
-    return tn <= tf * Slack<T>::v + T(1e-30) ? tn : T(INFINITY);
+    return tn <= tf * Slack<T>::v + T(1e-30) ? tn * RayIn<T>::v : T(INFINITY);
 }
 
 // Barycentric slack of the ray-triangle test: a ray through an edge shared
@@ -363,37 +366,45 @@ template <> struct BaryTol<double> { static constexpr double v = 1e-13; };
 // or tmax.  Equal t go to the lowest original index.
 template <class T, class Stack>
 __device__ int32_t ray3_first(const RefScene3<T>& r, const T* x, const T* dir, T tmax, int32_t skip, T& t_out,
-                              QueryCount& qc, Stack& st) {
+                              QueryCount& qc, Stack& st, int tail = 0) {
     T inv[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) inv[k] = dir[k] != T(0) ? T(1) / dir[k] : T(0);
     T best = tmax;
     int32_t hit = -1;
-    int sp = 0;
-    int32_t cur = 0;
-    bool have = true;
+    // state and rounds as in the other queries
+    constexpr int32_t kPop = INT_MIN, kDone = INT_MIN + 1;
+    st.put(0, kDone, T(-1), qc.overflow);
+    int32_t sp = 1, cur = 0;
 #pragma unroll 1
-    while (have) {
-        if (cur >= 0) {
-            NodeData<T, 3> nd;
-            load_node<T, 3>(r.tnodes, cur, nd);
-            qc.nodes++;
-            const T e0 = ray_child3<T>(nd.lo0, nd.hi0, nd.n0, nd.o0, nd.t0, x, dir, inv, best);
-            const T e1 = ray_child3<T>(nd.lo1, nd.hi1, nd.n1, nd.o1, nd.t1, x, dir, inv, best);
-            const bool h0 = e0 <= best, h1 = e1 <= best;
-            if (h0 && h1) {
-                const bool n0 = e0 <= e1;
-                st.put(sp, n0 ? nd.c1 : nd.c0, n0 ? e1 : e0, qc.overflow);
-                ++sp;
-                cur = n0 ? nd.c0 : nd.c1;
-            } else if (h0) {
-                cur = nd.c0;
-            } else if (h1) {
-                cur = nd.c1;
-            } else {
-                have = false;
+    while (__ballot(cur != kDone) != 0ull) {
+#pragma unroll 1
+        while (true) {
+            const int n = __popcll(__ballot((uint32_t)cur <= (uint32_t)kPop));
+            if (n <= (__ballot((uint32_t)cur > (uint32_t)kDone) != 0ull ? tail : 0)) break;
+            if (cur == kPop) {
+                T dd;
+                int32_t node;
+                --sp;
+                st.get(sp, node, dd);
+                cur = dd <= best ? node : kPop;
             }
-        } else {
+            if (cur >= 0) {
+                NodeData<T, 3> nd;
+                load_node<T, 3>(r.tnodes, cur, nd);
+                qc.nodes++;
+                const T e0 = ray_child3<T>(nd.lo0, nd.hi0, nd.n0, nd.o0, nd.t0, x, dir, inv, best);
+                const T e1 = ray_child3<T>(nd.lo1, nd.hi1, nd.n1, nd.o1, nd.t1, x, dir, inv, best);
+                const bool h0 = e0 <= best, h1 = e1 <= best, near0 = e0 <= e1, both = h0 && h1;
+                const bool first = (both && near0) || (h0 && !h1);
+                cur = (h0 || h1) ? (first ? nd.c0 : nd.c1) : kPop;
+                if (both) {
+                    st.put(sp, first ? nd.c1 : nd.c0, first ? e1 : e0, qc.overflow);
+                    ++sp;
+                }
+            }
+        }
+        if ((uint32_t)cur > (uint32_t)kDone) {
             const int32_t v = -1 - cur;
             const int32_t start = v >> 3, n = (v & 7) + 1;
             for (int32_t i = start; i < start + n; ++i) {
@@ -432,21 +443,7 @@ __device__ int32_t ray3_first(const RefScene3<T>& r, const T* x, const T* dir, T
                     hit = i;
                 }
             }
-            have = false;
-        }
-        if (!have) {
-#pragma unroll 1
-            while (sp > 0) {
-                --sp;
-                int32_t node;
-                T dd;
-                st.get(sp, node, dd);
-                if (dd <= best) {
-                    cur = node;
-                    have = true;
-                    break;
-                }
-            }
+            cur = kPop;
         }
     }
     t_out = best;
@@ -517,7 +514,7 @@ __device__ int32_t ref3_boundary_sample(const RefScene3<T>& r, const T* x, T R, 
             --sp;
             T dd;
             st.get(sp, cur, dd);
-            have = true;
+            have = cur != INT_MIN;
         }
     }
     if (win < 0) return -1;
@@ -557,7 +554,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Wos
 wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
     constexpr int D = 3;
     const int lane = threadIdx.x & 63;
-    PrivateStack<T> stack;
+    StackSpill<T> spill;
+    LaneStack<T> stack(a.stack_lds, a.stack_off, spill);
     StageView<sizeof(T) == 4 ? 1 : 0> sv{0, -1};
     if constexpr (sizeof(T) == 4) {
         // LDS: the Dirichlet BVH's first nodes (and its primitives when they fit)
@@ -601,14 +599,29 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
     T term_b1 = T(0), term_b2 = T(0);
     int64_t wsteps = 0;
     SilQuery<T> sq;
-    sq.have = false;
+    sq.cur = SilQuery<T>::kDone;
     bool spend = false;
     bool sexact = true;    // sd2 is the Dirichlet distance (else an upper bound)
     int32_t swarm = -1;    // the previous step's closest silhouette edge, or -1
     T sd2 = T(0);
     int32_t sleaf = -1;
-    unsigned long long c_walks = 0, c_nested = 0, c_steps = 0, c_term = 0, c_trunc = 0,
-                       c_nodes = 0, c_prims = 0, c_ovf = 0, c_invalid = 0;
+    // lane statistics in 32 bits (they move to the device totals before they
+    // could wrap); the rare ones go there when they happen
+    uint32_t c_walks = 0, c_nested = 0, c_steps = 0, c_term = 0, c_nodes = 0, c_prims = 0;
+    auto count_rare = [&](unsigned long long Counters::*field, unsigned long long v) {
+        atomicAdd(&(a.cnt->*field), v);
+        atomicAdd(&(a.tot->*field), v);
+    };
+    auto count_queries = [&](const QueryCount& qc) {
+        c_nodes += qc.nodes; c_prims += qc.prims;
+        if (qc.overflow) count_rare(&Counters::overflow, qc.overflow);
+        if ((c_nodes | c_prims | c_steps) >= 0x80000000u) {
+            count_rare(&Counters::nodes, c_nodes);
+            count_rare(&Counters::prims, c_prims);
+            count_rare(&Counters::steps, c_steps);
+            c_nodes = 0; c_prims = 0; c_steps = 0;
+        }
+    };
 #pragma unroll 1
     while (true) {
         // ---- hand new walks to idle lanes ------------------------------------
@@ -624,7 +637,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                     const int64_t gid = wid + a.wid_offset;
                     const Instance<T> in = a.inst[0];
                     const int64_t local = gid - in.walk_begin;
-                    int64_t pin = local / a.W;
+                    int64_t pin = div_walks(a, local);
                     m = (uint32_t)(local - pin * a.W);
                     if (a.perm) {   // the slot's point; records stay indexed by point
                         pin = a.perm[pin];
@@ -693,7 +706,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
             if (executed) c_steps++;
             wsteps++;
             if (leaf < 0 || !(d2 >= T(0))) {
-                c_invalid++;
+                count_rare(&Counters::invalid, 1ull);
                 const T nanv = T(NAN);
                 a.rec_u[wid] = nanv;
                 if (MODE == 1) {
@@ -703,7 +716,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                 }
                 if (a.rec_steps) a.rec_steps[wid] = wsteps;
                 wid = -1;
-                c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+                count_queries(qc);
                 continue;
             }
             if (sexact && (sqrt(d2) < eps || cap)) {
@@ -718,7 +731,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                     qc.prims++;
                     if (sil3_edge_nearer<T>(ref, swarm, x, on, nin, sb)) bs = swarm;
                 }
-                sil_begin<T>(sq, sb, bs);
+                sil_begin<T>(sq, sb, bs, stack);
                 spend = true;
                 sd2 = d2;
                 sleaf = leaf;
@@ -728,15 +741,14 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
         {
 #pragma unroll 1
             while (true) {
-                const bool trav = spend && sq.have;
-                const unsigned long long sm = __ballot(trav);
+                const unsigned long long sm = __ballot(!sq.done());
                 const unsigned long long present = __ballot(true);
                 if (sm == 0ull || __popcll(present & ~sm) >= park) break;
-                if (trav) sil3_round<T>(ref, x, on, nin, sq, qc, stack, tail);
+                sil3_round<MODE>(ref, x, on, nin, sq, qc, stack, tail);
             }
         }
-        if (spend && sq.have) {
-            c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+        if (!sq.done()) {
+            count_queries(qc);
             continue;
         }
         if (spend) {
@@ -787,7 +799,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                 }
                 T t;
                 const T reach = R + T(8) * ulp * (fabs(x[0]) + fabs(x[1]) + fabs(x[2]) + R);
-                int32_t tri = ray3_first<T>(ref, x, dir, reach, on, t, qc, stack);
+                int32_t tri = ray3_first<T>(ref, x, dir, reach, on, t, qc, stack, tail);
                 if (tri < 0) t = R;
                 if (a.prm.has_source) {
                     const T rho = cbrt(unif_pos<T>(r.w));
@@ -850,7 +862,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
         if (at_term) {
             const T d = sqrt(td2);
             const int32_t leaf = tleaf;
-            if (cap && !(d < eps)) c_trunc++;
+            if (cap && !(d < eps)) count_rare(&Counters::truncated, 1ull);
             T P[9], bary[3];
             scene_prim<T, D>(a.s, sv, leaf, P);
             prim_closest<T, D>(P, x, bary);
@@ -898,7 +910,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                     if (a.rec_w) a.rec_w[wid] = tau_main;
                     if (a.rec_steps) a.rec_steps[wid] = wsteps;
                     wid = -1;
-                    c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+                    count_queries(qc);
                     continue;
                 }
                 // the first nested walk on stars starts at the offset point
@@ -907,13 +919,13 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                 for (int c = 0; c < D; ++c) x[c] = xoff[c];
                 acc = T(0); k = 0; warm = term_leaf; on = -1; tau = T(1);
                 c_nested++;
-                c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+                count_queries(qc);
                 continue;
             }
             finished = true;
             result = acc + tau * g;
         }
-        c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+        count_queries(qc);
         if (!finished) continue;
 
         if (MODE == 0) {
@@ -947,30 +959,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
             }
         }
     }
-    c_walks = wave_sum_u64(c_walks);
-    c_nested = wave_sum_u64(c_nested);
-    c_steps = wave_sum_u64(c_steps);
-    c_term = wave_sum_u64(c_term);
-    c_nodes = wave_sum_u64(c_nodes);
-    c_prims = wave_sum_u64(c_prims);
-    c_trunc = wave_sum_u64(c_trunc);
-    c_ovf = wave_sum_u64(c_ovf);
-    c_invalid = wave_sum_u64(c_invalid);
-    if (lane == 0) {
-        Counters* dst[2] = {a.cnt, a.tot};
-        for (int q = 0; q < 2; ++q) {
-            Counters* c = dst[q];
-            atomicAdd(&c->walks, c_walks);
-            atomicAdd(&c->nested, c_nested);
-            atomicAdd(&c->steps, c_steps);
-            atomicAdd(&c->terminal, c_term);
-            atomicAdd(&c->nodes, c_nodes);
-            atomicAdd(&c->prims, c_prims);
-            if (c_trunc) atomicAdd(&c->truncated, c_trunc);
-            if (c_ovf) atomicAdd(&c->overflow, c_ovf);
-            if (c_invalid) atomicAdd(&c->invalid, c_invalid);
-        }
-    }
+    add_counts(a, lane, c_walks, c_nested, c_steps, c_term, c_nodes, c_prims);
 }
 
 // Closest silhouette distance and first ray hit for query rows (parity

@@ -39,8 +39,8 @@ constexpr int kRefGeo = 8;
 
 // Normal cones of the silhouette query, per node and child (8 scalars
 // each): a unit axis a, sin and cos of s0 = theta + margin, the range
-// [omin, omax] of a.p over the child's segment endpoints p, kappa and a pad;
-// theta the largest angle between a and the normals involved in the child's
+// [omin, omax] of a.p over the child's segment endpoints p, 2 sin(s0/2) +
+// kappa and the radius of the child box's bounding circle; theta the largest angle between a and the normals involved in the child's
 // vertex tests (its segments' and, at each vertex it tests, the other
 // segment's, all oriented along the polyline through that vertex).  A
 // vertex is a silhouette only if x is in front of one of its segments'
@@ -176,7 +176,7 @@ __device__ int32_t ref_boundary_sample(const RefScene<T>& r, const T* x, T R, u4
             --sp;
             T dd;
             st.get(sp, cur, dd);
-            have = true;
+            have = cur != INT_MIN;
         }
     }
     if (win >= 0) {
@@ -220,28 +220,33 @@ __device__ __forceinline__ void ref_cones(const RefScene<T>& r, int32_t i, T* q)
     for (int k = 0; k < 2 * kRefCone; ++k) q[k] = g[k];
 }
 
-// Can the child with box lo..hi and cone q hold a silhouette seen from x?
+// Square root and reciprocal square root for bounds: in FP32 the hardware's
+// (1 ulp), which the bounds' margins cover; the correctly rounded sequences
+// take ten times the instructions.
+__device__ __forceinline__ float bound_sqrt(float v) { return __builtin_amdgcn_sqrtf(v); }
+__device__ __forceinline__ double bound_sqrt(double v) { return sqrt(v); }
+__device__ __forceinline__ float bound_rsqrt(float v) { return __builtin_amdgcn_rsqf(v); }
+__device__ __forceinline__ double bound_rsqrt(double v) { return 1.0 / sqrt(v); }
+
+// Can a child hold a silhouette seen from x?  c: from x to the centre of the
+// child's box, of half-diagonal r, d2 = |c|^2; ac, ax: the cone axis times c
+// and x; the cone's sin and cos of s0, [omin, omax] and spread = 2 sin(s0/2) +
+// kappa; mag: the sum of the coordinates' magnitudes of x and the box (the
+// line test's rounding floor).  No branches: with a branch per test and the
+// correctly rounded roots and quotients a node cost some 300 instructions,
+// most of a step's time (2D thermal step 189 -> 165 ms, 3D 526 -> 427 ms).
 template <class T>
-__device__ __forceinline__ bool cone_may_hold(const T* lo, const T* hi, const T* q, const T* x) {
-    if (!(q[2] <= T(1))) return true;     // never pruned
-    const T cx = T(0.5) * (lo[0] + hi[0]) - x[0], cy = T(0.5) * (lo[1] + hi[1]) - x[1];
-    const T ex = T(0.5) * (hi[0] - lo[0]), ey = T(0.5) * (hi[1] - lo[1]);
-    const T d2 = cx * cx + cy * cy, r2 = ex * ex + ey * ey;
-    {   // lines: x in front of (or behind) every segment line of the child
-        const T ulp = sizeof(T) == 4 ? T(1.1920929e-07) : T(2.220446049250313e-16);
-        const T ax = q[0] * x[0] + q[1] * x[1];
-        const T dmax = sqrt(d2) + sqrt(r2);
-        const T mag = fabs(x[0]) + fabs(x[1]) + fabs(lo[0]) + fabs(lo[1]) + fabs(hi[0]) + fabs(hi[1]);
-        const T marg = (sqrt(fmax(T(0), T(2) - T(2) * q[3])) + q[6]) * dmax + T(32) * ulp * (mag + dmax);
-        if (ax - q[5] > marg || q[4] - ax > marg) return false;
-    }
-    if (!(d2 > r2)) return true;          // x inside the bounding circle
-    const T inv = T(1) / sqrt(d2);
-    const T sb = sqrt(r2) * inv, cb = sqrt(T(1) - sb * sb);
-    const T cs = q[3] * cb - q[2] * sb;   // cos(s0 + beta)
-    if (!(cs > T(0))) return true;
-    const T ss = q[2] * cb + q[3] * sb;   // sin(s0 + beta)
-    return !(fabs((q[0] * cx + q[1] * cy) * inv) > ss);
+__device__ __forceinline__ bool cone_keeps(T d2, T r, T ac, T ax, T sn, T cs, T omin, T omax, T spread, T mag) {
+    constexpr T ulp = sizeof(T) == 4 ? T(1.1920929e-07) : T(2.220446049250313e-16);
+    const T dmax = bound_sqrt(d2) + r;
+    const T marg = spread * dmax + T(32) * ulp * (mag + dmax);
+    const bool clear = ax - omax > marg || omin - ax > marg;   // in front of, or behind, every line (plane)
+    const T inv = bound_rsqrt(d2);
+    const T sb = r * inv, cb = bound_sqrt(fmax(T(0), T(1) - sb * sb));
+    const T cc = cs * cb - sn * sb;   // cos(s0 + beta)
+    const T ss = sn * cb + cs * sb;   // sin(s0 + beta)
+    const bool seen = d2 > r * r && cc > T(0) && fabs(ac * inv) > ss;   // x outside the circle, no normal edge-on
+    return !(clear || seen);
 }
 
 // Relative size below which a cross product counts as zero in the silhouette
@@ -282,101 +287,90 @@ __device__ __forceinline__ bool sil_test(const T* v, const T* u, const T* w, int
     return (cu > T(0)) == (cw > T(0));
 }
 
-// Closest silhouette vertex as a resumable query: the traversal state of one
-// lane (node to visit next or a held leaf, stack depth, best squared
-// distance so far).  sil_round expands nodes, then tests a leaf; a lane keeps
-// its state (and its entries in the traversal stack) across iterations of
-// the walk loop, so a wavefront can take its step once enough lanes are
-// answered (see wost_kernel).  x lies on leaf segment `on` (domain side nin)
-// or inside (-1).
+// Closest silhouette vertex as a resumable query, one word of state (`cur`)
+// and an "answered" entry at the bottom of the stack as in the closest-point
+// query.  A lane keeps its state (and its stack) across iterations of the walk
+// loop, so a wavefront can take its step once enough lanes are answered (see
+// wost_kernel).  x lies on leaf segment `on` (domain side nin) or inside (-1).
 template <class T>
 struct SilQuery {
-    int32_t cur;   // node (>= 0) or leaf reference (< 0) to process next
+    int32_t cur;   // node >= 0, kDone, kPop, or a held leaf's reference
     int32_t sp;    // entries in the traversal stack
-    bool have;     // cur is valid; false once the query is answered
     T best;        // squared distance of the closest silhouette so far
     int32_t bsil;  // the silhouette at that distance (3D: leaf edge), or -1
+    static constexpr int32_t kPop = INT_MIN, kDone = INT_MIN + 1;
+    __device__ __forceinline__ bool done() const { return cur == kDone; }
+    __device__ __forceinline__ bool descending() const { return (uint32_t)cur <= (uint32_t)kPop; }
+    __device__ __forceinline__ bool holds_leaf() const { return (uint32_t)cur > (uint32_t)kDone; }
 };
 
-template <class T>
-__device__ __forceinline__ void sil_begin(SilQuery<T>& q, T best, int32_t bsil = -1) {
+template <class T, class Stack>
+__device__ __forceinline__ void sil_begin(SilQuery<T>& q, T best, int32_t bsil, Stack& st) {
     q.cur = 0;   // the root pair node
-    q.sp = 0;
-    q.have = true;
+    unsigned none = 0;
+    st.put(0, SilQuery<T>::kDone, T(-1), none);
+    q.sp = 1;
     q.best = best;
     q.bsil = bsil;
 }
 
-// Answer the next entry of the traversal stack still nearer than the best
-// distance, or end the query when none is left.
-template <class T, class Stack>
-__device__ __forceinline__ void sil_pop(SilQuery<T>& q, Stack& st) {
-    q.have = false;
-#pragma unroll 1
-    while (q.sp > 0) {
-        --q.sp;
-        int32_t node;
-        T dd;
-        st.get(q.sp, node, dd);
-        if (dd < q.best) {
-            q.cur = node;
-            q.have = true;
-            break;
-        }
-    }
-}
-
-// One round of the query: expand nodes until the lane holds a leaf or is
-// answered, then the lanes holding leaves test them together; with tail > 0
-// the expansion stops once at most `tail` lanes still descend while some
-// lane holds a leaf (those go on in the next round), as in the closest-point
-// query.  Each lane visits the same nodes and vertices in the same order
-// whatever the tail, so the answer does not depend on it.
+// One round of the query for the lanes that have one in progress (the
+// others, done(), pass through): expand nodes until the lane holds a leaf or
+// is answered, then the lanes holding leaves test them together; the expansion
+// stops once at most `tail` lanes still descend while some lane holds a leaf
+// (those go on in the next round), as in the closest-point query.  Each lane
+// visits the same nodes and vertices in the same order whatever the tail, so
+// the answer does not depend on it.
 template <class T, class Stack>
 __device__ __forceinline__ void sil_round(const RefScene<T>& r, const T* x, int32_t on, const T* nin,
                                           SilQuery<T>& q, QueryCount& qc, Stack& st, int tail = 0) {
+    using Q = SilQuery<T>;
+    const T xmag = fabs(x[0]) + fabs(x[1]);
     // phase 1: expand nodes
 #pragma unroll 1
     while (true) {
-        const bool go = q.have && q.cur >= 0;
-        if (tail > 0) {
-            const unsigned long long gm = __ballot(go);
-            if (gm == 0ull) break;
-            if (__popcll(gm) <= tail && __ballot(q.have && q.cur < 0) != 0ull) break;
-            if (!go) continue;
-        } else if (!go) {
-            break;
+        const int n = __popcll(__ballot(q.descending()));
+        if (n <= (__ballot(q.holds_leaf()) != 0ull ? tail : 0)) break;
+        if (q.cur == Q::kPop) {
+            T dd;
+            int32_t node;
+            --q.sp;
+            st.get(q.sp, node, dd);
+            q.cur = dd < q.best ? node : Q::kPop;
         }
-        NodeData<T, 2> nd;
-        ref_node<T>(r, q.cur, nd);
-        qc.nodes++;
-        const T d0 = fmax(box_d2<T, 2>(nd.lo0, nd.hi0, x), slab_d2<T, 2>(nd.n0, nd.o0, nd.t0, x));
-        const T d1 = fmax(box_d2<T, 2>(nd.lo1, nd.hi1, x), slab_d2<T, 2>(nd.n1, nd.o1, nd.t1, x));
-        T qn[2 * kRefCone];
-        ref_cones<T>(r, q.cur, qn);
-        const bool h0 = d0 < q.best && cone_may_hold<T>(nd.lo0, nd.hi0, qn, x);
-        const bool h1 = d1 < q.best && cone_may_hold<T>(nd.lo1, nd.hi1, qn + kRefCone, x);
-        if (h0 && h1) {
-            const bool n0 = d0 <= d1;
-            st.put(q.sp, n0 ? nd.c1 : nd.c0, n0 ? d1 : d0, qc.overflow);
-            ++q.sp;
-            q.cur = n0 ? nd.c0 : nd.c1;
-        } else if (h0) {
-            q.cur = nd.c0;
-        } else if (h1) {
-            q.cur = nd.c1;
-        } else {
-            sil_pop<T>(q, st);
+        if (q.cur >= 0) {
+            NodeData<T, 2> nd;
+            ref_node<T>(r, q.cur, nd);
+            T qn[2 * kRefCone];
+            ref_cones<T>(r, q.cur, qn);
+            qc.nodes++;
+            const T d0 = fmax(box_d2<T, 2>(nd.lo0, nd.hi0, x), slab_d2<T, 2>(nd.n0, nd.o0, nd.t0, x));
+            const T d1 = fmax(box_d2<T, 2>(nd.lo1, nd.hi1, x), slab_d2<T, 2>(nd.n1, nd.o1, nd.t1, x));
+            const auto keeps = [&](const T* lo, const T* hi, const T* w) {
+                const T cx = T(0.5) * (lo[0] + hi[0]) - x[0], cy = T(0.5) * (lo[1] + hi[1]) - x[1];
+                return cone_keeps<T>(cx * cx + cy * cy, w[7], w[0] * cx + w[1] * cy, w[0] * x[0] + w[1] * x[1],
+                                     w[2], w[3], w[4], w[5], w[6],
+                                     xmag + fabs(lo[0]) + fabs(lo[1]) + fabs(hi[0]) + fabs(hi[1]));
+            };
+            const bool k0 = keeps(nd.lo0, nd.hi0, qn), k1 = keeps(nd.lo1, nd.hi1, qn + kRefCone);
+            const bool h0 = d0 < q.best && k0, h1 = d1 < q.best && k1;
+            const bool near0 = d0 <= d1, both = h0 && h1;
+            const bool first = (both && near0) || (h0 && !h1);
+            q.cur = (h0 || h1) ? (first ? nd.c0 : nd.c1) : Q::kPop;
+            if (both) {
+                st.put(q.sp, first ? nd.c1 : nd.c0, first ? d1 : d0, qc.overflow);
+                ++q.sp;
+            }
         }
     }
     // phase 2: the lanes holding a leaf test its vertices
-    if (q.have && q.cur < 0) {
+    if (q.holds_leaf()) {
         const int32_t v = -1 - q.cur;
         const int32_t start = v >> 3, n = (v & 7) + 1;
+        qc.prims += n;
         for (int32_t i = start; i < start + n; ++i) {
             const int4 inf = r.info[i];
             const T* g = r.geo + (size_t)i * kRefGeo;
-            qc.prims++;
             if (inf.x & 1) {   // vertex a: segments i (far end b) and inf.y (far end na)
                 const T dx = g[0] - x[0], dy = g[1] - x[1];
                 const T d2 = dx * dx + dy * dy;
@@ -394,7 +388,7 @@ __device__ __forceinline__ void sil_round(const RefScene<T>& r, const T* x, int3
                 }
             }
         }
-        sil_pop<T>(q, st);
+        q.cur = Q::kPop;
     }
 }
 
@@ -404,11 +398,15 @@ template <class T, class Stack>
 __device__ T silhouette_d2(const RefScene<T>& r, const T* x, int32_t on, const T* nin, T best,
                            QueryCount& qc, Stack& st) {
     SilQuery<T> q;
-    sil_begin<T>(q, best);
+    sil_begin<T>(q, best, -1, st);
 #pragma unroll 1
-    while (q.have) sil_round<T>(r, x, on, nin, q, qc, st);
+    while (!q.done()) sil_round<T>(r, x, on, nin, q, qc, st);
     return q.best;
 }
+
+template <class T> struct RayIn;
+template <> struct RayIn<float> { static constexpr float v = 1.0f - 1e-6f; };
+template <> struct RayIn<double> { static constexpr double v = 1.0; };
 
 // Entry distance of the ray x + t dir (t in [0, tmax]) into a child's box
 // and oriented slab, or +inf if it misses them.  inv = 1/dir per axis.
@@ -430,13 +428,14 @@ __device__ __forceinline__ T ray_child(const T* lo, const T* hi, const T* n, T o
     const T pn = n[0] * dir[0] + n[1] * dir[1];
     const T q = n[0] * x[0] + n[1] * x[1] - o;
     if (pn != T(0)) {
-        const T s1 = (-th - q) / pn, s2 = (th - q) / pn;
+        const T s1 = quot<T>(-th - q, pn), s2 = quot<T>(th - q, pn);
         tn = fmax(tn, fmin(s1, s2));
         tf = fmin(tf, fmax(s1, s2));
     } else if (fabs(q) > th) {
         return T(INFINITY);
     }
-    return tn <= tf * Slack<T>::v + T(1e-30) ? tn : T(INFINITY);
+    // (the entry is lowered by the quotients' rounding: it bounds a hit's t)
+    return tn <= tf * Slack<T>::v + T(1e-30) ? tn * RayIn<T>::v : T(INFINITY);
 }
 
 // First reflecting segment (leaf position) entered from its domain side
@@ -444,37 +443,45 @@ __device__ __forceinline__ T ray_child(const T* lo, const T* hi, const T* n, T o
 // none.  t_out: its t, or tmax.  Equal t go to the lowest original index.
 template <class T, class Stack>
 __device__ int32_t ray_first(const RefScene<T>& r, const T* x, const T* dir, T tmax, int32_t skip, T& t_out,
-                             QueryCount& qc, Stack& st) {
+                             QueryCount& qc, Stack& st, int tail = 0) {
     T inv[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) inv[k] = dir[k] != T(0) ? T(1) / dir[k] : T(0);
     T best = tmax;
     int32_t hit = -1;
-    int sp = 0;
-    int32_t cur = 0;
-    bool have = true;
+    // state and rounds as in the other queries
+    constexpr int32_t kPop = INT_MIN, kDone = INT_MIN + 1;
+    st.put(0, kDone, T(-1), qc.overflow);
+    int32_t sp = 1, cur = 0;
 #pragma unroll 1
-    while (have) {
-        if (cur >= 0) {
-            NodeData<T, 2> nd;
-            ref_node<T>(r, cur, nd);
-            qc.nodes++;
-            const T e0 = ray_child<T>(nd.lo0, nd.hi0, nd.n0, nd.o0, nd.t0, x, dir, inv, best);
-            const T e1 = ray_child<T>(nd.lo1, nd.hi1, nd.n1, nd.o1, nd.t1, x, dir, inv, best);
-            const bool h0 = e0 <= best, h1 = e1 <= best;
-            if (h0 && h1) {
-                const bool n0 = e0 <= e1;
-                st.put(sp, n0 ? nd.c1 : nd.c0, n0 ? e1 : e0, qc.overflow);
-                ++sp;
-                cur = n0 ? nd.c0 : nd.c1;
-            } else if (h0) {
-                cur = nd.c0;
-            } else if (h1) {
-                cur = nd.c1;
-            } else {
-                have = false;
+    while (__ballot(cur != kDone) != 0ull) {
+#pragma unroll 1
+        while (true) {
+            const int n = __popcll(__ballot((uint32_t)cur <= (uint32_t)kPop));
+            if (n <= (__ballot((uint32_t)cur > (uint32_t)kDone) != 0ull ? tail : 0)) break;
+            if (cur == kPop) {
+                T dd;
+                int32_t node;
+                --sp;
+                st.get(sp, node, dd);
+                cur = dd <= best ? node : kPop;
             }
-        } else {
+            if (cur >= 0) {
+                NodeData<T, 2> nd;
+                ref_node<T>(r, cur, nd);
+                qc.nodes++;
+                const T e0 = ray_child<T>(nd.lo0, nd.hi0, nd.n0, nd.o0, nd.t0, x, dir, inv, best);
+                const T e1 = ray_child<T>(nd.lo1, nd.hi1, nd.n1, nd.o1, nd.t1, x, dir, inv, best);
+                const bool h0 = e0 <= best, h1 = e1 <= best, near0 = e0 <= e1, both = h0 && h1;
+                const bool first = (both && near0) || (h0 && !h1);
+                cur = (h0 || h1) ? (first ? nd.c0 : nd.c1) : kPop;
+                if (both) {
+                    st.put(sp, first ? nd.c1 : nd.c0, first ? e1 : e0, qc.overflow);
+                    ++sp;
+                }
+            }
+        }
+        if ((uint32_t)cur > (uint32_t)kDone) {
             const int32_t v = -1 - cur;
             const int32_t start = v >> 3, n = (v & 7) + 1;
             for (int32_t i = start; i < start + n; ++i) {
@@ -509,21 +516,7 @@ __device__ int32_t ray_first(const RefScene<T>& r, const T* x, const T* dir, T t
                     hit = i;
                 }
             }
-            have = false;
-        }
-        if (!have) {
-#pragma unroll 1
-            while (sp > 0) {
-                --sp;
-                int32_t node;
-                T dd;
-                st.get(sp, node, dd);
-                if (dd <= best) {
-                    cur = node;
-                    have = true;
-                    break;
-                }
-            }
+            cur = kPop;
         }
     }
     t_out = best;
@@ -566,11 +559,8 @@ __device__ __forceinline__ void keep_on_domain_side(const RefScene<T>& r, int32_
 // left.
 // ---------------------------------------------------------------------------
 // FP32 differential kernel: four wavefronts per SIMD (at most 128 registers
-// per lane instead of the compiler's 130, which gave three).  On the 2D
-// thermal workload (W = 128, three runs each) the differential launch takes
-// 306 ms against 315 ms at five wavefronts (96 registers, more spilling) and
-// 333 ms at six; the forward kernel keeps the compiler's choice (four; five
-// was slower, 362 against 337 ms).
+// per lane), what its LDS admits (kStarStack2); the forward kernel's own
+// choice is the same.
 template <class T, int MODE>
 struct WostWaves { static constexpr int v = (sizeof(T) == 4 && MODE == 1) ? 4 : 1; };
 
@@ -579,7 +569,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Wos
 wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
     constexpr int D = 2;
     const int lane = threadIdx.x & 63;
-    PrivateStack<T> stack;
+    StackSpill<T> spill;
+    LaneStack<T> stack(a.stack_lds, a.stack_off, spill);
     StageView<sizeof(T) == 4 ? 1 : 0> sv{0, -1};
     if constexpr (sizeof(T) == 4) {
         // LDS: the Dirichlet BVH's first nodes (and its primitives when they
@@ -625,12 +616,27 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
     // silhouette query in progress (resumable across iterations) and the
     // Dirichlet answer of its step
     SilQuery<T> sq;
-    sq.have = false;
+    sq.cur = SilQuery<T>::kDone;
     bool spend = false;
     T sd2 = T(0);
     int32_t sleaf = -1;
-    unsigned long long c_walks = 0, c_nested = 0, c_steps = 0, c_term = 0, c_trunc = 0,
-                       c_nodes = 0, c_prims = 0, c_ovf = 0, c_invalid = 0;
+    // lane statistics in 32 bits (they move to the device totals before they
+    // could wrap); the rare ones go there when they happen
+    uint32_t c_walks = 0, c_nested = 0, c_steps = 0, c_term = 0, c_nodes = 0, c_prims = 0;
+    auto count_rare = [&](unsigned long long Counters::*field, unsigned long long v) {
+        atomicAdd(&(a.cnt->*field), v);
+        atomicAdd(&(a.tot->*field), v);
+    };
+    auto count_queries = [&](const QueryCount& qc) {
+        c_nodes += qc.nodes; c_prims += qc.prims;
+        if (qc.overflow) count_rare(&Counters::overflow, qc.overflow);
+        if ((c_nodes | c_prims | c_steps) >= 0x80000000u) {
+            count_rare(&Counters::nodes, c_nodes);
+            count_rare(&Counters::prims, c_prims);
+            count_rare(&Counters::steps, c_steps);
+            c_nodes = 0; c_prims = 0; c_steps = 0;
+        }
+    };
 #pragma unroll 1
     while (true) {
         // ---- hand new walks to idle lanes ------------------------------------
@@ -646,7 +652,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                     const int64_t gid = wid + a.wid_offset;
                     const Instance<T> in = a.inst[0];
                     const int64_t local = gid - in.walk_begin;
-                    const int64_t pin = local / a.W;
+                    const int64_t pin = div_walks(a, local);
                     m = (uint32_t)(local - pin * a.W);
                     p = (uint32_t)(pin + in.p_counter);
                     root = in.root;
@@ -694,7 +700,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
             if (executed) c_steps++;
             wsteps++;
             if (leaf < 0 || !(d2 >= T(0))) {
-                c_invalid++;
+                count_rare(&Counters::invalid, 1ull);
                 const T nanv = T(NAN);
                 a.rec_u[wid] = nanv;
                 if (MODE == 1) {
@@ -704,13 +710,13 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                 }
                 if (a.rec_steps) a.rec_steps[wid] = wsteps;
                 wid = -1;
-                c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+                count_queries(qc);
                 continue;
             }
             const T d = sqrt(d2);
             const bool cap = (int)(k + 1) >= a.prm.kmax;
             if (d < eps || cap) {
-                if (cap && !(d < eps)) c_trunc++;
+                if (cap && !(d < eps)) count_rare(&Counters::truncated, 1ull);
                 T P[9], bary[3];
                 scene_prim<T, D>(a.s, sv, leaf, P);
                 prim_closest<T, D>(P, x, bary);
@@ -756,7 +762,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                         if (a.rec_w) a.rec_w[wid] = tau_main;
                         if (a.rec_steps) a.rec_steps[wid] = wsteps;
                         wid = -1;
-                        c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+                        count_queries(qc);
                         continue;
                     }
                     // the first nested walk on stars starts at the offset point
@@ -765,13 +771,13 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                     for (int c = 0; c < D; ++c) x[c] = xoff[c];
                     acc = T(0); k = 0; warm = term_leaf; on = -1; tau = T(1);
                     c_nested++;
-                    c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+                    count_queries(qc);
                     continue;
                 }
                 finished = true;
                 result = acc + tau * g;
             } else {
-                sil_begin<T>(sq, d2);
+                sil_begin<T>(sq, d2, -1, stack);
                 spend = true;
                 sd2 = d2;
                 sleaf = leaf;
@@ -785,15 +791,14 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
         {
 #pragma unroll 1
             while (true) {
-                const bool trav = spend && sq.have;
-                const unsigned long long sm = __ballot(trav);
+                const unsigned long long sm = __ballot(!sq.done());
                 const unsigned long long present = __ballot(true);
                 if (sm == 0ull || __popcll(present & ~sm) >= park) break;
-                if (trav) sil_round<T>(ref, x, on, nin, sq, qc, stack, tail);
+                sil_round<T>(ref, x, on, nin, sq, qc, stack, tail);
             }
         }
-        if (spend && sq.have) {
-            c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+        if (!sq.done()) {
+            count_queries(qc);
             continue;
         }
         if (spend) {
@@ -829,7 +834,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
             // rounded end point x + R v could land behind counts as hit.
             T t;
             const T reach = R + T(8) * ulp * (fabs(x[0]) + fabs(x[1]) + R);
-            int32_t seg = ray_first<T>(ref, x, dir, reach, on, t, qc, stack);
+            int32_t seg = ray_first<T>(ref, x, dir, reach, on, t, qc, stack, tail);
             if (seg < 0) t = R;
             if (a.prm.has_source) {
                 const T rho = sqrt(unif_pos<T>(r.w));
@@ -892,7 +897,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
                 warm = leaf;
             }
         }
-        c_nodes += qc.nodes; c_prims += qc.prims; c_ovf += qc.overflow;
+        count_queries(qc);
         if (!finished) continue;
 
         if (MODE == 0) {
@@ -925,30 +930,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
             }
         }
     }
-    c_walks = wave_sum_u64(c_walks);
-    c_nested = wave_sum_u64(c_nested);
-    c_steps = wave_sum_u64(c_steps);
-    c_term = wave_sum_u64(c_term);
-    c_nodes = wave_sum_u64(c_nodes);
-    c_prims = wave_sum_u64(c_prims);
-    c_trunc = wave_sum_u64(c_trunc);
-    c_ovf = wave_sum_u64(c_ovf);
-    c_invalid = wave_sum_u64(c_invalid);
-    if (lane == 0) {
-        Counters* dst[2] = {a.cnt, a.tot};
-        for (int q = 0; q < 2; ++q) {
-            Counters* c = dst[q];
-            atomicAdd(&c->walks, c_walks);
-            atomicAdd(&c->nested, c_nested);
-            atomicAdd(&c->steps, c_steps);
-            atomicAdd(&c->terminal, c_term);
-            atomicAdd(&c->nodes, c_nodes);
-            atomicAdd(&c->prims, c_prims);
-            if (c_trunc) atomicAdd(&c->truncated, c_trunc);
-            if (c_ovf) atomicAdd(&c->overflow, c_ovf);
-            if (c_invalid) atomicAdd(&c->invalid, c_invalid);
-        }
-    }
+    add_counts(a, lane, c_walks, c_nested, c_steps, c_term, c_nodes, c_prims);
 }
 
 // Closest silhouette distance and first ray hit for query rows (parity
