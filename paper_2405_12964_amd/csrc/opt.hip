@@ -13,11 +13,14 @@
 //   x = M^-1 u
 // The solves are Jacobi-preconditioned conjugate gradients on the D
 // coordinate systems at once (block-diagonal M (x) I_D), warm-started from
-// the previous solution, with every scalar kept on the device; the host
-// reads a convergence flag every kCheckEvery iterations.  An iteration is
-// three launches (M p with p . q, the update with r . z, the new direction),
-// each block adding the previous launch's per-block partials itself in one
-// fixed order, so no launch waits on a separate reduction.
+// the previous solution, with every scalar kept on the device.  A mesh whose
+// rows all fit on the chip at once is solved by one launch (cg_resident): each
+// thread keeps its row -- columns, x, r, p, q and its neighbours' p -- in
+// registers through all iterations, and the blocks meet at two grid barriers
+// per iteration.  A larger one takes three launches per iteration (M p with
+// p . q, the update with r . z, the new direction), the host reading a
+// convergence flag every kCheckEvery iterations.  Both add per-block partials
+// of the dot products in one fixed order and give the same iterates bit for bit.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,16 +44,19 @@ constexpr int kCheckEvery = 16;      // CG iterations between convergence reads
 // device scalars
 // S_RZ, S_RZ1: r . z of the current iteration in alternating slots (iteration
 // k reads slot k & 1 and leaves the next one in the other)
-enum { S_RZ = 0, S_RZ1, S_RZ0, S_PQ, S_VMAX, S_DONE, S_COUNT };
+// S_IT, S_FAIL: iterations of a resident solve, and whether its blocks missed
+// each other
+enum { S_RZ = 0, S_RZ1, S_RZ0, S_PQ, S_VMAX, S_DONE, S_IT, S_FAIL, S_COUNT };
 }  // namespace
 
 struct dwos_opt {
     int D = 0;
     int64_t nv = 0, nnz = 0;
+    bool resident = false;    // solves run as one launch of cg_resident
     int device = 0;
     hipStream_t stream = nullptr;
     DevBuf rowptr, col, val, diag, movable;
-    DevBuf u, m, v, gu, r, z, p, q, red, scal;
+    DevBuf u, m, v, gu, r, z, p, q, red, scal, pex;
     int64_t t = 0;
     bool ready = false;
 };
@@ -230,6 +236,216 @@ __global__ void cg_direction_beta(double* p, const double* z, int64_t nv, int D,
     for (int c = 0; c < D; ++c) p[i * D + c] = z[i * D + c] + beta * p[i * D + c];
 }
 
+// ---------------------------------------------------------------------------
+// The whole solve in one launch.  A CG iteration on a mesh of 100,000 vertices
+// moves some 20 MB through the caches; as three launches of 391 blocks it took
+// 23 us, all latency: each row's pointers, columns and neighbours are loaded
+// one after the other by few wavefronts, and every vector goes through memory
+// between the launches.  Here a thread owns a row: its columns are read once,
+// x, r, p, q, its own z and its neighbours' p stay in registers, and one
+// iteration is one gather of the neighbours' z and two exchanges of partial
+// sums (p . q before the update, r . z before the gather); a neighbour's new
+// direction z_j + beta p_j is formed by every thread that needs it, with the
+// same rounding as by its owner.  Registers hold the first NB neighbours (a
+// closed triangle mesh has 6 on average); the rest of a row's directions are
+// kept in pex.  8.4 us an iteration (a counter as grid barrier, with every
+// wavefront writing the L2 back and invalidating it: 61 us; gathering past the
+// L2 instead of invalidating it once a block: 8.9 us).  Launched cooperatively,
+// so that all blocks are resident; a wait gives up after kWaitTicks all the same.
+// ---------------------------------------------------------------------------
+constexpr int kResThreads = 512;                  // threads per block: two groups of kThreads rows
+constexpr int kGroups = kResThreads / kThreads;
+constexpr uint64_t kWaitTicks = 1000000000ull;    // 10 s of the 100 MHz clock
+constexpr int held_neighbours(int D) { return D == 2 ? 2 : 8; }
+
+__device__ __forceinline__ void store_agent(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ uint64_t load_agent(const uint64_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Publishes the partial sums of the block's groups of kThreads rows (block_sum's
+// order): each as two words of half a double and the epoch, so that a word seen
+// with its epoch is the value itself.  The stores the block made before (all
+// at agent scope) have arrived when its words do.
+__device__ __forceinline__ void publish(double s, int64_t nblk, uint32_t epoch, uint64_t* slots, double* sh) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const int64_t blk = (int64_t)blockIdx.x * kGroups + threadIdx.x;
+    if (threadIdx.x < kGroups && blk < nblk) {
+        double t = 0.0;
+        for (int w = 0; w < kThreads / 64; ++w) t += sh[threadIdx.x * (kThreads / 64) + w];
+        const uint64_t v = (uint64_t)__double_as_longlong(t);
+        store_agent(&slots[2 * blk], (uint64_t)epoch << 32 | (v & 0xffffffffu));
+        store_agent(&slots[2 * blk + 1], (uint64_t)epoch << 32 | v >> 32);
+    }
+}
+
+// Waits for all nblk partials of an epoch and adds them, in block_total's
+// order: a grid barrier and its reduction in one round trip.  False for every
+// thread of the block if a partial did not come.
+__device__ __forceinline__ bool collect(const uint64_t* slots, int64_t nblk, uint32_t epoch, double* sh, double* tot,
+                                        int* late, double& sum) {
+    double s = 0.0;
+    if (threadIdx.x < kThreads) {
+        const uint64_t t0 = wall_clock64();
+        for (int64_t i = threadIdx.x; i < nblk; i += kThreads) {
+            uint64_t lo = load_agent(&slots[2 * i]), hi = load_agent(&slots[2 * i + 1]);
+            while ((uint32_t)(lo >> 32) != epoch || (uint32_t)(hi >> 32) != epoch) {
+                if (wall_clock64() - t0 > kWaitTicks) {
+                    *late = 1;
+                    break;
+                }
+                lo = load_agent(&slots[2 * i]);
+                hi = load_agent(&slots[2 * i + 1]);
+            }
+            s += __longlong_as_double((long long)(hi << 32 | (lo & 0xffffffffu)));
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < kThreads / 64; ++w) t += sh[w];
+        *tot = t;
+    }
+    __syncthreads();
+    sum = *tot;
+    return *late == 0;
+}
+
+// From x, r, p = z and scal[S_RZ] = r . z of the start.  pex: nnz x D.
+template <int D>
+__global__ void __launch_bounds__(kResThreads) cg_resident(const int64_t* rowptr, const int32_t* col, const double* val,
+                                                           const double* diag, double* x, const double* r0, double* z,
+                                                           double* pex, int64_t nv, int64_t nblk, uint64_t* slots_pq,
+                                                           uint64_t* slots_rz, double* scal, int max_iters,
+                                                           double tol2) {
+    constexpr int NB = held_neighbours(D);
+    __shared__ double sh_out[kResThreads / 64], sh_in[kResThreads / 64];
+    __shared__ double tot;
+    __shared__ int late;
+    if (threadIdx.x == 0) late = 0;
+    const int64_t i = (int64_t)blockIdx.x * kResThreads + threadIdx.x;
+    const bool live = i < nv;
+    double rz = scal[S_RZ];
+    const double rz0 = scal[S_RZ0];
+    bool done = scal[S_DONE] != 0.0;
+    int32_t cj[NB];
+    double xi[D], ri[D], pi[D], pj[NB][D], di = 1.0, dg = 0.0, off = 0.0;
+    int nb = 0;
+    int64_t first = 0;                    // the row's first neighbour
+#pragma unroll
+    for (int c = 0; c < D; ++c) { xi[c] = 0.0; ri[c] = 0.0; pi[c] = 0.0; }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        cj[k] = 0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) pj[k][c] = 0.0;
+    }
+    if (live) {
+        first = rowptr[i] + 1;
+        nb = (int)(rowptr[i + 1] - first);
+        dg = val[first - 1];
+        if (nb > 0) off = val[first];     // every off-diagonal entry is -lambda
+        di = 1.0 / diag[i];
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            xi[c] = x[i * D + c];
+            ri[c] = r0[i * D + c];
+            pi[c] = z[i * D + c];
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (k < nb) {
+                cj[k] = col[first + k];
+#pragma unroll
+                for (int c = 0; c < D; ++c) pj[k][c] = z[(int64_t)cj[k] * D + c];
+            }
+        for (int k = NB; k < nb; ++k)
+            for (int c = 0; c < D; ++c) pex[(first + k) * D + c] = z[(int64_t)col[first + k] * D + c];
+    }
+    int it = 0;
+    while (!done && it < max_iters) {
+        // q = M p, p . q
+        double qi[D], s = 0.0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            qi[c] = dg * pi[c];
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (k < nb) qi[c] += off * pj[k][c];
+        }
+        for (int k = NB; k < nb; ++k)
+#pragma unroll
+            for (int c = 0; c < D; ++c) qi[c] += off * pex[(first + k) * D + c];
+#pragma unroll
+        for (int c = 0; c < D; ++c) s += pi[c] * qi[c];
+        double pq, rzn;
+        publish(live ? s : 0.0, nblk, it + 1, slots_pq, sh_out);
+        if (!collect(slots_pq, nblk, it + 1, sh_in, &tot, &late, pq)) break;
+        ++it;
+        if (!(pq > 0.0)) break;
+        // x, r, z and r . z
+        const double al = rz / pq;
+        double zi[D];
+        s = 0.0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            xi[c] += al * pi[c];
+            ri[c] = ri[c] - al * qi[c];
+            zi[c] = ri[c] * di;
+            s += ri[c] * zi[c];
+            if (live) store_agent(&z[i * D + c], zi[c]);
+        }
+        publish(live ? s : 0.0, nblk, it, slots_rz, sh_out);
+        if (!collect(slots_rz, nblk, it, sh_in, &tot, &late, rzn)) break;
+        if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __syncthreads();
+        // the neighbours' z (all of a row's loads in flight together)
+        double zj[NB][D];
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (k < nb) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) zj[k][c] = z[(int64_t)cj[k] * D + c];
+            }
+        const double beta = rz > 0.0 ? rzn / rz : 0.0;
+        if (rzn <= tol2 * rz0) done = true;
+        rz = rzn;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            pi[c] = zi[c] + beta * pi[c];
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (k < nb) pj[k][c] = zj[k][c] + beta * pj[k][c];
+        }
+        for (int k = NB; k < nb; ++k) {
+            const int64_t j = (int64_t)col[first + k] * D, e = (first + k) * D;
+#pragma unroll
+            for (int c = 0; c < D; ++c) pex[e + c] = z[j + c] + beta * pex[e + c];
+        }
+    }
+    if (live) {
+#pragma unroll
+        for (int c = 0; c < D; ++c) x[i * D + c] = xi[c];
+    }
+    if (threadIdx.x == 0) {
+        if (late) scal[S_FAIL] = 1.0;
+        if (i == 0) scal[S_IT] = (double)it;
+    }
+}
+
 // moments of the vector Adam step; partial maxima of v_hat over movable vertices
 __global__ void adam_moments(const double* g, double* m, double* v, const int32_t* movable, int64_t nv, int D,
                              double b1, double b2, double c2, double* red) {
@@ -295,7 +511,13 @@ __global__ void copy(double* dst, const double* src, int64_t n) {
 
 namespace {
 
-// x := M^-1 b by preconditioned CG from the current x.  iters: used.
+const void* resident_kernel(int D) {
+    return D == 2 ? reinterpret_cast<const void*>(opt_k::cg_resident<2>)
+                  : reinterpret_cast<const void*>(opt_k::cg_resident<3>);
+}
+
+// x := M^-1 b by preconditioned CG from the current x.  iters: used, as the
+// three-launch path notices convergence (a multiple of kCheckEvery).
 dwos_status cg_solve(dwos_opt* o, const double* b, double* x, int32_t max_iters, double tol, int32_t* iters) {
     hipStream_t s = o->stream;
     const int64_t nv = o->nv, n = nv * o->D;
@@ -316,6 +538,31 @@ dwos_status cg_solve(dwos_opt* o, const double* b, double* x, int32_t max_iters,
                        r, z, p, nv, D);
     hipLaunchKernelGGL(opt_k::dot_partial, dim3(kRedBlocks), dim3(kThreads), 0, s, r, z, n, red, sc);
     hipLaunchKernelGGL(opt_k::cg_start, dim3(1), dim3(kThreads), 0, s, red, sc, tol2);
+    if (o->resident) {
+        double *pex = o->pex.as<double>(), t2 = tol2, used[2] = {0.0, 0.0};
+        uint64_t* slots_pq = reinterpret_cast<uint64_t*>(red + kRedBlocks);
+        uint64_t* slots_rz = slots_pq + 2 * nblk;
+        hipLaunchKernelGGL(opt_k::fill, dim3(blocks_for(4 * nblk, 256)), dim3(256), 0, s, red + kRedBlocks, 4 * nblk,
+                           0.0);
+        int64_t rows = nv, nb = nblk;
+        int mi = max_iters;
+        void* args[] = {&rp, &cl, &va, &dg, &x, &r, &z, &pex, &rows, &nb, &slots_pq, &slots_rz, &sc, &mi, &t2};
+        if (hipLaunchCooperativeKernel(resident_kernel(D), dim3(blocks_for(nv, opt_k::kResThreads)),
+                                       dim3(opt_k::kResThreads), args, 0, s) == hipSuccess) {
+            HIP_OK(hipMemcpyAsync(used, sc + S_IT, sizeof(used), hipMemcpyDeviceToHost, s));
+            HIP_OK(hipStreamSynchronize(s));
+            if (used[1] == 0.0) {
+                const int64_t seen = ((int64_t)used[0] + kCheckEvery - 1) / kCheckEvery * kCheckEvery;
+                if (iters) *iters = (int32_t)std::min<int64_t>(max_iters, seen);
+                return DWOS_OK;
+            }
+        } else {
+            (void)hipGetLastError();
+        }
+        // not resident after all: from the x left (a warm start like another)
+        o->resident = false;
+        return cg_solve(o, b, x, max_iters, tol, iters);
+    }
     int32_t it = 0;
     for (; it < max_iters; ++it) {
         if (it % kCheckEvery == 0) {
@@ -377,7 +624,9 @@ dwos_status dwos_opt_create(int32_t dim, int64_t nv, const int32_t* prims, int64
     std::vector<int64_t> rowptr(nv + 1, 0);
     std::vector<int32_t> col;
     std::vector<double> val, diag(nv);
+    size_t max_nb = 0;
     for (int64_t i = 0; i < nv; ++i) {
+        max_nb = std::max(max_nb, adj[i].size());
         std::sort(adj[i].begin(), adj[i].end());
         diag[i] = 1.0 + lambda * (double)adj[i].size();
         col.push_back((int32_t)i);
@@ -402,8 +651,15 @@ dwos_status dwos_opt_create(int32_t dim, int64_t nv, const int32_t* prims, int64
         const size_t vb = (size_t)nv * dim * sizeof(double);
         for (DevBuf* b : {&o->u, &o->m, &o->gu, &o->r, &o->z, &o->p, &o->q}) HIP_OK(b->reserve(vb));
         HIP_OK(o->v.reserve((size_t)nv * sizeof(double)));
-        HIP_OK(o->red.reserve((kRedBlocks + 2 * blocks_for(nv, kThreads)) * sizeof(double)));
+        HIP_OK(o->red.reserve((kRedBlocks + 4 * blocks_for(nv, kThreads)) * sizeof(double)));
         HIP_OK(o->scal.reserve(S_COUNT * sizeof(double)));
+        // the one-launch solve, if every row fits on the device at once
+        int per = 0, cus = 0;
+        HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, resident_kernel(dim), opt_k::kResThreads, 0));
+        HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, o->device));
+        o->resident = blocks_for(nv, opt_k::kResThreads) <= (int64_t)per * cus;
+        if (o->resident && max_nb > (size_t)opt_k::held_neighbours(dim))
+            HIP_OK(o->pex.reserve(o->nnz * dim * sizeof(double)));
         return DWOS_OK;
     };
     dwos_status st = up();
