@@ -330,27 +330,114 @@ __global__ void __launch_bounds__(64) jvp_kernel(JvpArgs<T> a) {
 }
 
 // ---------------------------------------------------------------------------
-// debug queries
+// Closest-point queries of a list of points
 // ---------------------------------------------------------------------------
-template <class T, int D>
-__global__ void closest_kernel(Scene<T> s, int32_t root, const double* X, int64_t P, double* out) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
+
+// DistanceToBoundary by a whole wavefront for one point (x the same in every
+// lane): each round takes the newest entries of one stack in LDS, one per lane,
+// expands nodes and tests leaves, and shares the bound.  In FP32 the answer is
+// the lowest original index at the least distance, whatever the order of the
+// visits, so it equals closest_leaf's.  A query without a starting primitive
+// visits hundreds of nodes, each a dependent load for the lane that runs it
+// alone and a wait for the other lanes of its wavefront: 4096 points around the
+// 200,000-triangle object took 1,440 us that way and take 26 us this way.
+constexpr int kWaveStack = 576;      // entries
+// When fewer than 64 + kStackSize are free, a round takes as many entries as
+// leave kStackSize free, at least one: one at a time the stack grows by less
+// than the tree's depth, so that it never overflows.
+static_assert(kWaveStack >= 128 + kStackSize, "a full round and a descent must fit");
+template <int D>
+__device__ __forceinline__ int32_t wave_closest(const Scene<float>& s, int32_t root, const float* x, int32_t warm,
+                                                float2* st, float& best) {
     const StageView<0> sv{0, -1};
-    T x[D];
+    const int lane = threadIdx.x & 63;
+    Query<float, D> q;
+    q.best = INFINITY;
+    q.bleaf = -1;
+    if (warm >= 0) {
+        float P[9], bb[3];
+        scene_prim<float, D>(s, sv, warm, P);
+        q.best = prim_closest<float, D>(P, x, bb);
+        q.bleaf = warm;
+    }
+    float lim = q.best * Slack<float>::v;
+    if (lane == 0) st[0] = make_float2(0.0f, __int_as_float(root));
+    int n = 1;
+#pragma unroll 1
+    while (n > 0) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int m = min(min(n, 64), max(1, kWaveStack - kStackSize - n));
+        n -= m;
+        int32_t cur = INT_MIN;
+        if (lane < m) {
+            const float2 e = st[n + m - 1 - lane];
+            if (!(e.x > lim)) cur = __float_as_int(e.y);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        bool near = false, both = false;
+        float dn = 0.0f, df = 0.0f;
+        int32_t cn = 0, cf = 0;
+        if (cur >= 0) {
+            NodeData<float, D> nd;
+            scene_node<float, D>(s, sv, cur, nd);
+            const float d0 = fmax(box_d2<float, D>(nd.lo0, nd.hi0, x), slab_d2<float, D>(nd.n0, nd.o0, nd.t0, x));
+            const float d1 = fmax(box_d2<float, D>(nd.lo1, nd.hi1, x), slab_d2<float, D>(nd.n1, nd.o1, nd.t1, x));
+            const bool h0 = d0 <= lim, h1 = d1 <= lim;
+            both = h0 && h1;
+            near = h0 || h1;
+            const bool first = both ? d0 <= d1 : h0;
+            cn = first ? nd.c0 : nd.c1;
+            cf = first ? nd.c1 : nd.c0;
+            dn = first ? d0 : d1;
+            df = first ? d1 : d0;
+        }
+        // the farther children below the nearer ones
+        const uint64_t bf = __ballot(both), bn = __ballot(near);
+        const uint64_t below = (uint64_t(1) << lane) - 1;
+        if (both) st[n + __popcll(bf & below)] = make_float2(df, __int_as_float(cf));
+        n += __popcll(bf);
+        if (near) st[n + __popcll(bn & below)] = make_float2(dn, __int_as_float(cn));
+        n += __popcll(bn);
+        if (__ballot(cur < 0 && cur != INT_MIN)) {
+            if (cur < 0 && cur != INT_MIN) {
+                const int32_t v = -1 - cur;
+                const int32_t start = v >> 3, c = (v & 7) + 1;
+                for (int32_t i = start; i < start + c; ++i) {
+                    float P[9];
+                    scene_prim<float, D>(s, sv, i, P);
+                    query_test_prim<float, D, 0>(s, P, x, i, q);
+                }
+            }
+            float b = q.best;
 #pragma unroll
-    for (int c = 0; c < D; ++c) x[c] = T(X[p * D + c]);
-    T d2;
-    QueryCount qc{0, 0, 0};
-    PrivateStack<T> stack;
-    const int32_t leaf = closest_leaf<T, D>(s, sv, root, x, -1, d2, qc, stack);
-    double* o = out + p * 8;
+            for (int o = 32; o > 0; o >>= 1) b = fminf(b, __shfl_xor(b, o));
+            lim = b * Slack<float>::v;
+        }
+    }
+    // the lowest (distance, original index) of the lanes
+    uint64_t key = (uint64_t)__float_as_uint(q.best) << 32 | (q.bleaf < 0 ? 0xffffffffu : (uint32_t)s.orig[q.bleaf]);
+    const uint64_t own = key;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint64_t k = __shfl_xor((unsigned long long)key, o);
+        key = k < key ? k : key;
+    }
+    const int win = __ffsll((unsigned long long)__ballot(own == key)) - 1;
+    best = __shfl(q.best, win);
+    return __shfl(q.bleaf, win);
+}
+
+// What closest_point reports of the closest primitive (or -1) of x.
+template <class T, int D>
+__device__ __forceinline__ void write_closest(const Scene<T>& s, int32_t leaf, T d2, const T* x, double* o) {
     if (leaf < 0) {
         for (int k = 0; k < 8; ++k) o[k] = NAN;
         return;
     }
     T P9[9], bary[3];
-    scene_prim<T, D>(s, sv, leaf, P9);
+    scene_prim<T, D>(s, StageView<0>{0, -1}, leaf, P9);
     prim_closest<T, D>(P9, x, bary);
     const int32_t orig = s.orig[leaf];
     T V[9];
@@ -365,6 +452,36 @@ __global__ void closest_kernel(Scene<T> s, int32_t root, const double* X, int64_
             for (int k = 0; k < D; ++k) v += double(bary[k]) * double(V[k * D + c]);
         o[5 + c] = v;
     }
+}
+
+// One point per lane (FP64: the order of its visits decides near ties).
+template <class T, int D>
+__global__ void closest_kernel(Scene<T> s, int32_t root, const double* X, int64_t P, double* out) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= P) return;
+    T x[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) x[c] = T(X[p * D + c]);
+    T d2;
+    QueryCount qc{0, 0, 0};
+    PrivateStack<T> stack;
+    const int32_t leaf = closest_leaf<T, D>(s, StageView<0>{0, -1}, root, x, -1, d2, qc, stack);
+    write_closest<T, D>(s, leaf, d2, x, out + p * 8);
+}
+
+// One point per wavefront.
+template <int D>
+__global__ void __launch_bounds__(256) closest_wave_kernel(Scene<float> s, int32_t root, const double* X, int64_t P,
+                                                           double* out) {
+    __shared__ float2 st[4][kWaveStack];
+    const int w = threadIdx.x >> 6;
+    const int64_t p = (int64_t)blockIdx.x * 4 + w;
+    if (p >= P) return;
+    float x[D], d2;
+#pragma unroll
+    for (int c = 0; c < D; ++c) x[c] = float(X[p * D + c]);
+    const int32_t leaf = wave_closest<D>(s, root, x, -1, st[w], d2);
+    if ((threadIdx.x & 63) == 0) write_closest<float, D>(s, leaf, d2, x, out + p * 8);
 }
 
 // closest primitive of each start point (shared first query of its walks);
@@ -442,34 +559,69 @@ __global__ void order_scatter_kernel(const int32_t* cell, int64_t P, uint32_t* c
 // when it lies in the row's instance's leaf positions: prange[2 i] ..
 // prange[2 i + 1] for instance i, or (prange null, a single-instance scene
 // whose tree holds every primitive) 0 .. n_prims.
-template <class T, int D>
-__global__ void first_query_kernel(Scene<T> s, const Instance<T>* inst, int32_t n_inst, const double* X,
-                                   int64_t x_base, int64_t P, const int32_t* prange, const int32_t* warm_in,
-                                   int32_t* leaf_out, T* d2_out) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= P) return;
-    const int64_t g = x_base + r;
-    int lo = 0, hi = n_inst - 1;
+template <class T>
+struct FirstArgs {
+    Scene<T> s;
+    const Instance<T>* inst;
+    int32_t n_inst;
+    const double* X;
+    int64_t x_base, P;
+    const int32_t* prange;
+    const int32_t* warm_in;
+    int32_t* leaf_out;
+    T* d2_out;
+};
+
+template <class T>
+__device__ __forceinline__ void first_start(const FirstArgs<T>& a, int64_t r, int32_t& root, int32_t& warm) {
+    const int64_t g = a.x_base + r;
+    int lo = 0, hi = a.n_inst - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (inst[mid].point_begin <= g) lo = mid; else hi = mid - 1;
+        if (a.inst[mid].point_begin <= g) lo = mid; else hi = mid - 1;
     }
-    const StageView<0> sv{0, -1};
+    root = a.inst[lo].root;
+    warm = -1;
+    if (a.warm_in) {
+        const int32_t w = a.warm_in[r];
+        const int64_t b = a.prange ? (int64_t)a.prange[2 * lo] : 0;
+        const int64_t e = a.prange ? (int64_t)a.prange[2 * lo + 1] : a.s.n_prims;
+        if ((int64_t)w >= b && (int64_t)w < e) warm = w;
+    }
+}
+
+template <class T, int D>
+__global__ void first_query_kernel(FirstArgs<T> a) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= a.P) return;
+    int32_t root, warm;
+    first_start(a, r, root, warm);
     T x[D];
 #pragma unroll
-    for (int c = 0; c < D; ++c) x[c] = T(X[r * D + c]);
+    for (int c = 0; c < D; ++c) x[c] = T(a.X[r * D + c]);
     T d2;
     QueryCount qc{0, 0, 0};
     PrivateStack<T> stack;
-    int32_t warm = -1;
-    if (warm_in) {
-        const int32_t w = warm_in[r];
-        const int64_t b = prange ? (int64_t)prange[2 * lo] : 0;
-        const int64_t e = prange ? (int64_t)prange[2 * lo + 1] : s.n_prims;
-        if ((int64_t)w >= b && (int64_t)w < e) warm = w;
+    a.leaf_out[r] = closest_leaf<T, D>(a.s, StageView<0>{0, -1}, root, x, warm, d2, qc, stack);
+    a.d2_out[r] = d2;
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) first_query_wave_kernel(FirstArgs<float> a) {
+    __shared__ float2 st[4][kWaveStack];
+    const int w = threadIdx.x >> 6;
+    const int64_t r = (int64_t)blockIdx.x * 4 + w;
+    if (r >= a.P) return;
+    int32_t root, warm;
+    first_start(a, r, root, warm);
+    float x[D], d2;
+#pragma unroll
+    for (int c = 0; c < D; ++c) x[c] = float(a.X[r * D + c]);
+    const int32_t leaf = wave_closest<D>(a.s, root, x, warm, st[w], d2);
+    if ((threadIdx.x & 63) == 0) {
+        a.leaf_out[r] = leaf;
+        a.d2_out[r] = d2;
     }
-    leaf_out[r] = closest_leaf<T, D>(s, sv, inst[lo].root, x, warm, d2, qc, stack);
-    d2_out[r] = d2;
 }
 
 template <class T, int D>
@@ -509,9 +661,18 @@ __global__ void pack_prims_kernel(const T* verts, const int32_t* pverts, const i
     }
 }
 
-// Refit one pair node per wavefront: recompute both children's boxes and
-// slab offsets/thicknesses (normals kept) from the primitives in their
-// leaf-order ranges.  Every node is independent, so one launch refits the tree.
+// Refit: recompute both children's boxes and slab offsets/thicknesses (normals
+// kept) of every pair node from the primitives in their leaf-order ranges.  A
+// slab's offset along its own normal does not follow from the children's, so
+// every node reads its whole range; minima and maxima are exact in any order.
+// Ranges of more than kRefitPart primitives are cut into parts of a wavefront
+// each, listed when the boundary is set (RefitPart: child and its range), whose
+// results a second launch joins; the rest are one wavefront's, a node each.
+// With one wavefront per node the root's 3,125 dependent rounds were all of the
+// time: 200,000 triangles 0.97 ms, now 0.07 ms.
+constexpr int kRefitPart = 1024;
+struct RefitPart { int32_t child, begin, end, pad; };      // child: 2 node + 0 or 1
+struct RefitJoin { int32_t child, first, count, pad; };    // its parts [first, first + count)
 template <class T>
 __device__ __forceinline__ T wave_min(T v) {
 #pragma unroll
@@ -526,25 +687,21 @@ __device__ __forceinline__ T wave_max(T v) {
 }
 
 template <class T, int D>
-__global__ void __launch_bounds__(256) refit_nodes_kernel(T* nodes, const T* prims, const int32_t* ranges,
-                                                          int64_t n_nodes) {
-    const int64_t ni = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (ni >= n_nodes) return;
-    T* p = nodes + ni * node_scalars(D);
-    for (int c = 0; c < 2; ++c) {
-        const int32_t b = ranges[ni * 4 + 2 * c], e = ranges[ni * 4 + 2 * c + 1];
-        if (e <= b) continue;   // empty child keeps its sentinel bounds
-        T* lo = p + 2 * c * D;
-        T* hi = p + (2 * c + 1) * D;
-        T* slab = p + slab_offset(D) + c * (D + 2);
+struct RefitBounds {
+    T mn[D], mx[D], smin, smax;
+    __device__ __forceinline__ void clear() {
+        smin = T(INFINITY);
+        smax = T(-INFINITY);
+#pragma unroll
+        for (int k = 0; k < D; ++k) { mn[k] = T(INFINITY); mx[k] = T(-INFINITY); }
+    }
+    // the primitives [b, e) over the lanes of a wavefront
+    __device__ __forceinline__ void scan(const T* prims, int32_t b, int32_t e, const T* slab) {
         T n[D];
 #pragma unroll
         for (int k = 0; k < D; ++k) n[k] = slab[k];
-        T mn[D], mx[D], smin = T(INFINITY), smax = T(-INFINITY);
-#pragma unroll
-        for (int k = 0; k < D; ++k) { mn[k] = T(INFINITY); mx[k] = T(-INFINITY); }
-        for (int32_t i = b + lane; i < e; i += 64) {
+        clear();
+        for (int32_t i = b + (int32_t)(threadIdx.x & 63); i < e; i += 64) {
             const T* P = prims + (size_t)i * prim_scalars(D);
 #pragma unroll
             for (int v = 0; v < D; ++v) {
@@ -560,20 +717,76 @@ __global__ void __launch_bounds__(256) refit_nodes_kernel(T* nodes, const T* pri
                 smax = fmax(smax, pr);
             }
         }
+    }
+    __device__ __forceinline__ void reduce() {
 #pragma unroll
         for (int k = 0; k < D; ++k) { mn[k] = wave_min(mn[k]); mx[k] = wave_max(mx[k]); }
         smin = wave_min(smin);
         smax = wave_max(smax);
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < D; ++k) { lo[k] = mn[k]; hi[k] = mx[k]; }
-            T scale = fmax(fabs(smin), fabs(smax));
-#pragma unroll
-            for (int k = 0; k < D; ++k) scale += fmax(fabs(mn[k]), fabs(mx[k]));
-            slab[D] = T(0.5) * (smin + smax);
-            slab[D + 1] = T(0.5) * (smax - smin) + slab_pad<T>(scale);
-        }
     }
+    __device__ __forceinline__ void store(T* nodes, int64_t child) const {
+        T* p = nodes + (child >> 1) * node_scalars(D);
+        const int c = (int)(child & 1);
+        T* slab = p + slab_offset(D) + c * (D + 2);
+#pragma unroll
+        for (int k = 0; k < D; ++k) { p[2 * c * D + k] = mn[k]; p[(2 * c + 1) * D + k] = mx[k]; }
+        T scale = fmax(fabs(smin), fabs(smax));
+#pragma unroll
+        for (int k = 0; k < D; ++k) scale += fmax(fabs(mn[k]), fabs(mx[k]));
+        slab[D] = T(0.5) * (smin + smax);
+        slab[D + 1] = T(0.5) * (smax - smin) + slab_pad<T>(scale);
+    }
+};
+
+template <class T, int D>
+__device__ __forceinline__ T* slab_of(T* nodes, int64_t child) {
+    return nodes + (child >> 1) * node_scalars(D) + slab_offset(D) + (child & 1) * (D + 2);
+}
+
+// wavefronts [0, n_parts): one part each, into bounds[part]; then one node each
+template <class T, int D>
+__global__ void __launch_bounds__(256) refit_nodes_kernel(T* nodes, const T* prims, const int32_t* ranges,
+                                                          int64_t n_nodes, const RefitPart* parts, int64_t n_parts,
+                                                          RefitBounds<T, D>* bounds) {
+    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    RefitBounds<T, D> r;
+    if (w < n_parts) {
+        const RefitPart pt = parts[w];
+        r.scan(prims, pt.begin, pt.end, slab_of<T, D>(nodes, pt.child));
+        r.reduce();
+        if (lane == 0) bounds[w] = r;
+        return;
+    }
+    const int64_t ni = w - n_parts;
+    if (ni >= n_nodes) return;
+    for (int c = 0; c < 2; ++c) {
+        const int32_t b = ranges[ni * 4 + 2 * c], e = ranges[ni * 4 + 2 * c + 1];
+        if (e <= b || e - b > kRefitPart) continue;   // (an empty child keeps its sentinel bounds)
+        r.scan(prims, b, e, slab_of<T, D>(nodes, 2 * ni + c));
+        r.reduce();
+        if (lane == 0) r.store(nodes, 2 * ni + c);
+    }
+}
+
+template <class T, int D>
+__global__ void __launch_bounds__(256) refit_join_kernel(T* nodes, const RefitJoin* joins, int64_t n_joins,
+                                                         const RefitBounds<T, D>* bounds) {
+    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (w >= n_joins) return;
+    const RefitJoin j = joins[w];
+    RefitBounds<T, D> r;
+    r.clear();
+    for (int32_t i = lane; i < j.count; i += 64) {
+        const RefitBounds<T, D> o = bounds[j.first + i];
+#pragma unroll
+        for (int k = 0; k < D; ++k) { r.mn[k] = fmin(r.mn[k], o.mn[k]); r.mx[k] = fmax(r.mx[k], o.mx[k]); }
+        r.smin = fmin(r.smin, o.smin);
+        r.smax = fmax(r.smax, o.smax);
+    }
+    r.reduce();
+    if (lane == 0) r.store(nodes, j.child);
 }
 
 // V_i = V_base_i + sum_{e in row i} vel_e pi_{pid_e}

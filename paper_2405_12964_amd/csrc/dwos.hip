@@ -94,6 +94,8 @@ struct dwos_ctx {
     int64_t nv = 0, np = 0, n_nodes = 0;
     DevBuf nodes, prims, orig, verts, pverts, label, gvert, leaf_of;
     DevBuf node_ranges;   // leaf-order primitive range of each node's two children
+    DevBuf refit_parts, refit_joins, refit_bounds;   // the large ones cut into parts
+    int64_t n_refit_parts = 0, n_refit_joins = 0;
     // batch contexts: instances accumulated on the host, uploaded together
     std::vector<InstanceHost> instances;
     std::vector<double> hostV, hostG;
@@ -613,10 +615,17 @@ dwos_status upload_geometry(dwos_ctx* c, const std::vector<double>& V, const std
     const int64_t np = (int64_t)prims.size() / D, nv = (int64_t)V.size() / D;
     std::vector<T> nodes = pack_nodes<T>(D, hn);
     std::vector<int32_t> ranges((size_t)hn.size() * 4);
+    std::vector<dwos::RefitPart> parts;
+    std::vector<dwos::RefitJoin> joins;
     for (size_t i = 0; i < hn.size(); ++i)
         for (int c = 0; c < 2; ++c) {
-            ranges[i * 4 + 2 * c] = hn[i].range[c][0];
-            ranges[i * 4 + 2 * c + 1] = hn[i].range[c][1];
+            const int32_t b = hn[i].range[c][0], e = hn[i].range[c][1], child = (int32_t)(2 * i + c);
+            ranges[i * 4 + 2 * c] = b;
+            ranges[i * 4 + 2 * c + 1] = e;
+            if (e - b <= dwos::kRefitPart) continue;
+            joins.push_back({child, (int32_t)parts.size(), (e - b + dwos::kRefitPart - 1) / dwos::kRefitPart, 0});
+            for (int32_t k = b; k < e; k += dwos::kRefitPart)
+                parts.push_back({child, k, std::min(e, k + dwos::kRefitPart), 0});
         }
     std::vector<T> pr((size_t)np * PS, T(0));
     for (int64_t lp = 0; lp < np; ++lp) {
@@ -635,6 +644,11 @@ dwos_status upload_geometry(dwos_ctx* c, const std::vector<double>& V, const std
     c->first_warm = false;
     HIP_OK(upload(c->nodes, nodes.data(), nodes.size(), s));
     HIP_OK(upload(c->node_ranges, ranges.data(), ranges.size(), s));
+    HIP_OK(upload(c->refit_parts, parts.data(), parts.size(), s));
+    HIP_OK(upload(c->refit_joins, joins.data(), joins.size(), s));
+    HIP_OK(c->refit_bounds.reserve(parts.size() * (2 * D + 2) * sizeof(T)));
+    c->n_refit_parts = (int64_t)parts.size();
+    c->n_refit_joins = (int64_t)joins.size();
     HIP_OK(upload(c->prims, pr.data(), pr.size(), s));
     HIP_OK(upload(c->orig, origv.data(), origv.size(), s));
     HIP_OK(upload(c->leaf_of, leaf_of.data(), leaf_of.size(), s));
@@ -759,6 +773,55 @@ dwos_status launch_variant(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
         }
     }
     return launch_shape<T, D, MODE, 0, cv>(c, a, timed);
+}
+
+// The nodes' bounds from the current primitives.
+template <class T, int D>
+void launch_refit(dwos_ctx* c) {
+    auto* bounds = c->refit_bounds.as<dwos::RefitBounds<T, D>>();
+    hipLaunchKernelGGL((dwos::refit_nodes_kernel<T, D>), dim3(blocks_for(c->n_refit_parts + c->n_nodes, 4)), dim3(256),
+                       0, c->stream, c->nodes.as<T>(), c->prims.as<T>(), c->node_ranges.as<int32_t>(), c->n_nodes,
+                       c->refit_parts.as<dwos::RefitPart>(), c->n_refit_parts, bounds);
+    if (c->n_refit_joins > 0)
+        hipLaunchKernelGGL((dwos::refit_join_kernel<T, D>), dim3(blocks_for(c->n_refit_joins, 4)), dim3(256), 0,
+                           c->stream, c->nodes.as<T>(), c->refit_joins.as<dwos::RefitJoin>(), c->n_refit_joins, bounds);
+}
+
+// Closest-point queries of a list of points, in FP32 by a wavefront per point up
+// to the count where a lane per point fills the chip as well and does less work
+// in all.  Without starting primitives, us by wavefront / by lane, at 4,096,
+// 65,536 and 262,144 points: 200,000 triangles, points in the volume 114 / 2044,
+// 535 / 2476, 2032 / 4026, on the box around 26 / 1461, 123 / 1927, 434 / 2233;
+// 8,000 triangles, volume 53 / 400, 257 / 496, 969 / 606; 4,096 segments 41 /
+// 169, 261 / 192, 1027 / 232 (16,384: 88 / 169).  From the primitives of a
+// previous query, 65,536 points: 312 / 1474, 86 / 16, 209 / 286, 126 / 94.
+constexpr int64_t kWavePoints2 = 16384, kWavePoints3 = 65536;
+template <class T, int D>
+bool wave_per_point(int64_t P) { return sizeof(T) == 4 && P <= (D == 2 ? kWavePoints2 : kWavePoints3); }
+
+template <class T, int D>
+void launch_first(hipStream_t s, const dwos::FirstArgs<T>& a) {
+    if constexpr (sizeof(T) == 4) {
+        if (wave_per_point<T, D>(a.P)) {
+            hipLaunchKernelGGL((dwos::first_query_wave_kernel<D>), dim3(blocks_for(a.P, 4)), dim3(256), 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((dwos::first_query_kernel<T, D>), dim3(blocks_for(a.P, 64)), dim3(64), 0, s, a);
+}
+
+template <class T, int D>
+void launch_closest(dwos_ctx* c, const double* X, int64_t P, double* out) {
+    const dwos::Scene<T> scene = make_scene<T>(c);
+    if constexpr (sizeof(T) == 4) {
+        if (wave_per_point<T, D>(P)) {
+            hipLaunchKernelGGL((dwos::closest_wave_kernel<D>), dim3(blocks_for(P, 4)), dim3(256), 0, c->stream, scene,
+                               0, X, P, out);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((dwos::closest_kernel<T, D>), dim3(blocks_for(P, 64)), dim3(64), 0, c->stream, scene, 0, X, P,
+                       out);
 }
 
 // Launch the persistent walk kernel over `total` walks.  `tot` (cumulative
@@ -1294,10 +1357,9 @@ dwos_status run_op(dwos_ctx* c, Op op, const OpArgs& o, dwos_stats* st) {
         HIP_OK(c->first_leaf.reserve(Pc * sizeof(int32_t)));
         if (c->first_leaf.ptr != fl_old) c->first_warm = false;
         HIP_OK(c->first_d2.reserve(Pc * sizeof(T)));
-        hipLaunchKernelGGL((dwos::first_query_kernel<T, D>), dim3(blocks_for(Pc, 64)), dim3(64), 0, s, scene,
-                           c->instbuf.as<dwos::Instance<T>>(), 1, o.X + p0 * D, p0, Pc, nullptr,
-                           c->first_warm ? c->first_leaf.as<int32_t>() : nullptr, c->first_leaf.as<int32_t>(),
-                           c->first_d2.as<T>());
+        launch_first<T, D>(s, {scene, c->instbuf.as<dwos::Instance<T>>(), 1, o.X + p0 * D, p0, Pc, nullptr,
+                               c->first_warm ? c->first_leaf.as<int32_t>() : nullptr, c->first_leaf.as<int32_t>(),
+                               c->first_d2.as<T>()});
         c->first_warm = true;
         a.first_leaf = c->first_leaf.as<int32_t>();
         a.first_d2 = c->first_d2.as<T>();
@@ -1467,8 +1529,7 @@ dwos_status run_solve_noalloc(dwos_ctx* c, const double* X, int64_t P, int32_t W
     const dwos::Scene<T> scene = make_scene<T>(c);
     auto* leaf = reinterpret_cast<int32_t*>(base + L.leaf);
     auto* d2 = reinterpret_cast<T*>(base + L.d2);
-    hipLaunchKernelGGL((dwos::first_query_kernel<T, D>), dim3(blocks_for(P, 64)), dim3(64), 0, s, scene, inst, 1, X,
-                       (int64_t)0, P, nullptr, nullptr, leaf, d2);
+    launch_first<T, D>(s, {scene, inst, 1, X, 0, P, nullptr, nullptr, leaf, d2});
     dwos::WalkArgs<T> a = base_args<T>(c, X, W, seed);
     a.inst = inst;
     a.n_inst = 1;
@@ -1803,15 +1864,13 @@ dwos_status dwos_update_vertices(dwos_ctx* c, const double* Vdev) {
                                Vdev, c->nv, c->verts.as<T>());
             hipLaunchKernelGGL((dwos::pack_prims_kernel<T, 2>), dim3(blocks_for(c->np, 256)), dim3(256), 0, s,
                                c->verts.as<T>(), c->pverts.as<int32_t>(), c->orig.as<int32_t>(), c->np, c->prims.as<T>());
-            hipLaunchKernelGGL((dwos::refit_nodes_kernel<T, 2>), dim3(blocks_for(c->n_nodes, 4)), dim3(256), 0, s,
-                               c->nodes.as<T>(), c->prims.as<T>(), c->node_ranges.as<int32_t>(), c->n_nodes);
+            launch_refit<T, 2>(c);
         } else {
             hipLaunchKernelGGL((dwos::pack_vertices_kernel<T, 3>), dim3(blocks_for(c->nv * 3, 256)), dim3(256), 0, s,
                                Vdev, c->nv, c->verts.as<T>());
             hipLaunchKernelGGL((dwos::pack_prims_kernel<T, 3>), dim3(blocks_for(c->np, 256)), dim3(256), 0, s,
                                c->verts.as<T>(), c->pverts.as<int32_t>(), c->orig.as<int32_t>(), c->np, c->prims.as<T>());
-            hipLaunchKernelGGL((dwos::refit_nodes_kernel<T, 3>), dim3(blocks_for(c->n_nodes, 4)), dim3(256), 0, s,
-                               c->nodes.as<T>(), c->prims.as<T>(), c->node_ranges.as<int32_t>(), c->n_nodes);
+            launch_refit<T, 3>(c);
         }
         HIP_OK(hipGetLastError());
         return DWOS_OK;
@@ -2184,15 +2243,10 @@ dwos_status dwos_closest(dwos_ctx* c, const double* X, int64_t P, double* out) {
     if (P < 0 || (P > 0 && (!X || !out))) return fail(DWOS_EINVAL, "closest: bad arguments");
     if (P == 0) return DWOS_OK;
     HIP_OK(hipSetDevice(c->device));
-    hipStream_t s = c->stream;
     auto run = [&](auto tag) {
         using T = decltype(tag);
-        if (c->D == 2)
-            hipLaunchKernelGGL((dwos::closest_kernel<T, 2>), dim3(blocks_for(P, 64)), dim3(64), 0, s,
-                               make_scene<T>(c), 0, X, P, out);
-        else
-            hipLaunchKernelGGL((dwos::closest_kernel<T, 3>), dim3(blocks_for(P, 64)), dim3(64), 0, s,
-                               make_scene<T>(c), 0, X, P, out);
+        if (c->D == 2) launch_closest<T, 2>(c, X, P, out);
+        else launch_closest<T, 3>(c, X, P, out);
     };
     if (c->prec == DWOS_FP32) run(float{}); else run(double{});
     HIP_OK(hipGetLastError());
@@ -2782,9 +2836,8 @@ dwos_status run_batch(dwos_ctx* c, const double* X, const int64_t* P, int32_t W,
     HIP_OK(c->first_leaf.reserve(std::max<int64_t>(1, pts) * sizeof(int32_t)));
     HIP_OK(c->first_d2.reserve(std::max<int64_t>(1, pts) * sizeof(T)));
     c->first_warm = false;   // batch leaves are positions in the instances' trees
-    hipLaunchKernelGGL((dwos::first_query_kernel<T, D>), dim3(blocks_for(pts, 64)), dim3(64), 0, s, scene,
-                       c->instbuf.as<dwos::Instance<T>>(), n, X, (int64_t)0, pts, c->inst_prange.as<int32_t>(),
-                       c->first_leaf.as<int32_t>(), c->first_leaf.as<int32_t>(), c->first_d2.as<T>());
+    launch_first<T, D>(s, {scene, c->instbuf.as<dwos::Instance<T>>(), n, X, 0, pts, c->inst_prange.as<int32_t>(),
+                           c->first_leaf.as<int32_t>(), c->first_leaf.as<int32_t>(), c->first_d2.as<T>()});
     dwos::WalkArgs<T> a = base_args<T>(c, X, W, seed);
     a.inst = c->instbuf.as<dwos::Instance<T>>();
     a.n_inst = n;
@@ -2840,10 +2893,9 @@ dwos_status run_batch_grad(dwos_ctx* c, const double* X, const int64_t* P, const
         HIP_OK(c->first_leaf.reserve(pts * sizeof(int32_t)));
         HIP_OK(c->first_d2.reserve(pts * sizeof(T)));
         c->first_warm = false;   // batch leaves are positions in the instances' trees
-        hipLaunchKernelGGL((dwos::first_query_kernel<T, D>), dim3(blocks_for(pts, 64)), dim3(64), 0, s, scene,
-                           c->instbuf.as<dwos::Instance<T>>(), n, X, (int64_t)0, pts,
-                           c->inst_prange.as<int32_t>(), c->first_leaf.as<int32_t>(), c->first_leaf.as<int32_t>(),
-                           c->first_d2.as<T>());
+        launch_first<T, D>(s, {scene, c->instbuf.as<dwos::Instance<T>>(), n, X, 0, pts,
+                               c->inst_prange.as<int32_t>(), c->first_leaf.as<int32_t>(),
+                               c->first_leaf.as<int32_t>(), c->first_d2.as<T>()});
         dwos::WalkArgs<T> a = base_args<T>(c, X, W, seed);
         a.inst = c->instbuf.as<dwos::Instance<T>>();
         a.n_inst = n;

@@ -248,9 +248,10 @@ __global__ void cg_direction_beta(double* p, const double* z, int64_t nv, int D,
 // direction z_j + beta p_j is formed by every thread that needs it, with the
 // same rounding as by its owner.  Registers hold the first NB neighbours (a
 // closed triangle mesh has 6 on average); the rest of a row's directions are
-// kept in pex.  8.4 us an iteration (a counter as grid barrier, with every
-// wavefront writing the L2 back and invalidating it: 61 us; gathering past the
-// L2 instead of invalidating it once a block: 8.9 us).  Launched cooperatively,
+// kept in pex.  A solve of some 110 iterations takes 1.15 ms, 2.6 ms before (with
+// a counter as grid barrier and every wavefront writing the L2 back and
+// invalidating it: 6.9 ms).  Gathering past the L2 instead of invalidating it
+// once a block costs 0.06 ms of it more.  Launched cooperatively,
 // so that all blocks are resident; a wait gives up after kWaitTicks all the same.
 // ---------------------------------------------------------------------------
 constexpr int kResThreads = 512;                  // threads per block: two groups of kThreads rows
