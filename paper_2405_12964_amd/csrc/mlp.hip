@@ -8,13 +8,13 @@
 //   D (16 x 16, FP32):         lane holds rows 4 g + r, column i, r = 0..3
 // The K slot (kc, g, e) of K chunk kc is mapped to the hidden unit
 //   16 (2 kc + e / 4) + 4 g + e % 4,
-// which is exactly the set of units a lane holds in D after a layer (tile
-// t = 2 kc + e / 4, row 4 g + e % 4).  With the weights packed in that order,
-// a layer's output fragments become the next layer's B operands in the same
-// lane: no cross-lane exchange and no LDS round trip between layers.  Points
-// are the 16 columns of a tile; each wave streams 16-point tiles.
+// which is the set of units the lanes of one column hold in D after a layer
+// (tile t = 2 kc + e / 4, row 4 g + e % 4): with the weights packed in that
+// order, the four units a lane holds go to the next layer's operand as they are.
+// Points are the 16 columns of a tile.
 #include "mlp.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -70,84 +70,144 @@ __global__ void pack_kernel(const float* __restrict__ theta, u32x4* __restrict__
     packed[at + 1] = __builtin_bit_cast(u32x4, lo);
 }
 
-// Input features of the lane's 16 slots: feature 16 t + 4 g + r for tile t,
-// row r.  ch 0 = value, ch 1..D = d/dx_c, ch D+1 = Laplacian.
-template <int D, int NC>
-__device__ inline void features(const float* __restrict__ B, int F, const float x[D], int g,
-                                float act[NC][4][4]) {
-    constexpr float kTwoPi = 6.28318530717958647692f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
+// Input features of a lane's units 16 t + 4 g + r (r = 0..3).
+template <int D>
+struct FeatureRows {
+    float b[4][D], bb[4];      // frequency (0 unless a Fourier feature) and its square
+    int kind[4];               // 0 sine, 1 cosine, 2 + c coordinate c, -1 zero
+    __device__ inline void load(const float* __restrict__ B, int F, int t, int g) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int f = 16 * t + 4 * g + r;
+            kind[r] = f < F ? 0 : f < 2 * F ? 1 : f < 2 * F + D ? 2 + f - 2 * F : -1;
+            bb[r] = 0.f;
 #pragma unroll
-            for (int ch = 0; ch < NC; ++ch) act[ch][t][r] = 0.f;
-            if (f < 2 * F) {
-                const int j = f < F ? f : f - F;
-                float th = 0.f, bb = 0.f, b[D];
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    b[c] = B[j * D + c];
-                    th += b[c] * x[c];
-                    bb += b[c] * b[c];
-                }
-                float sn, cs;
-                sincosf(kTwoPi * th, &sn, &cs);
-                const float v = f < F ? sn : cs;     // value
-                const float dv = f < F ? cs : -sn;   // derivative of the value in th
-                act[0][t][r] = v;
-                if constexpr (NC > 1) {
-#pragma unroll
-                    for (int c = 0; c < D; ++c) act[1 + c][t][r] = kTwoPi * b[c] * dv;
-                    act[D + 1][t][r] = -(kTwoPi * kTwoPi) * bb * v;
-                }
-            } else if (f < 2 * F + D) {
-                const int c0 = f - 2 * F;
-                act[0][t][r] = x[c0];
-                if constexpr (NC > 1) {
-#pragma unroll
-                    for (int c = 0; c < D; ++c) act[1 + c][t][r] = c == c0 ? 1.f : 0.f;
-                }
+            for (int c = 0; c < D; ++c) {
+                b[r][c] = f < 2 * F ? B[(f < F ? f : f - F) * D + c] : 0.f;
+                bb[r] += b[r][c] * b[r][c];
             }
         }
     }
-}
-
-// B operands (hi, lo) of the two K chunks from a lane's 16 activations
-template <int NC>
-__device__ inline void to_operands(const float act[NC][4][4], bf16x8 bh[NC][2], bf16x8 bl[NC][2]) {
+    // ch 0 = value, ch 1..D = d/dx_c, ch D+1 = Laplacian
+    template <int NC>
+    __device__ inline void eval(const float x[D], float act[NC][4]) const {
+        constexpr float kTwoPi = 6.28318530717958647692f;
 #pragma unroll
-    for (int ch = 0; ch < NC; ++ch)
+        for (int r = 0; r < 4; ++r) {
+            float th = 0.f, sn, cs;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+            for (int c = 0; c < D; ++c) th += b[r][c] * x[c];
+            sincosf(kTwoPi * th, &sn, &cs);
+            const float v = kind[r] == 0 ? sn : kind[r] == 1 ? cs : 0.f;    // value
+            const float dv = kind[r] == 0 ? cs : kind[r] == 1 ? -sn : 0.f;  // its derivative in th
+            act[0][r] = v;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                __bf16 h, o;
-                split(act[ch][t][r], h, o);
-                bh[ch][t >> 1][((t & 1) << 2) | r] = h;
-                bl[ch][t >> 1][((t & 1) << 2) | r] = o;
+            for (int c = 0; c < D; ++c) act[0][r] = kind[r] == 2 + c ? x[c] : act[0][r];
+            if constexpr (NC > 1) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) act[1 + c][r] = kind[r] == 2 + c ? 1.f : kTwoPi * b[r][c] * dv;
+                act[D + 1][r] = -(kTwoPi * kTwoPi) * bb[r] * v;
             }
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------
+// A block of four wavefronts takes the same 16 points through the network (a
+// column set is one channel of 16 points; S of them are in flight), each
+// wavefront computing 16 of the 64 units of every layer.  What a wavefront
+// keeps of a point -- pre-activations of all layers, its rows of all weight
+// gradients -- then fits its registers, and the layers meet in LDS.
+//
+// LDS holds activations as the MFMA operands: [set][hi, lo][unit tile], a tile
+// being 64 slots of four units of a point in BF16.  A lane writes its four units
+// of a point; a layer product reads them back as K slots, and the
+// weight-gradient products, which contract over points and channels, read the
+// same tile transposed (ds_read_b64_tr_b16: of the 16 slots that the lanes of
+// one g name, rows of four in lane order, lane i gets element i of each row).
+// Unit group c of point p is in slot 16 c + (p ^ 4 c): the 16 lanes that LDS
+// serves at a time then touch every bank once in either access (with the 16
+// units of a point next to each other it took four times as long: 64 of the
+// 120 us of an evaluation, 121 of the 297 us of a gradient).
+// ---------------------------------------------------------------------------
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+constexpr int kTileBytes = 16 * 16 * 2;
+constexpr int kSetBytes = 2 * 4 * kTileBytes;
+constexpr int kNetWaves = 4;
+
+__device__ inline bf16x8 join(bf16x4 a, bf16x4 b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// acc[ch][mt] = (W packed at w) x B for every channel
-template <int NC>
-__device__ inline void layer_product(const u32x4* w, int lane, const bf16x8 bh[NC][2],
-                                     const bf16x8 bl[NC][2], f32x4 acc[NC][4]) {
+__device__ inline int slot_bytes(int c, int p) { return 8 * (16 * c + (p ^ (4 * c))); }
+
+// this lane's four units (of the wavefront's tile w) of set q; at = slot_bytes(g, i)
+__device__ inline void put_set(lds_char* buf, int q, int w, int at, const float v[4]) {
+    bf16x4 hi, lo;
 #pragma unroll
-    for (int ch = 0; ch < NC; ++ch)
+    for (int r = 0; r < 4; ++r) {
+        __bf16 h, o;
+        split(v[r], h, o);
+        hi[r] = h;
+        lo[r] = o;
+    }
+    lds_char* to = buf + q * kSetBytes + w * kTileBytes + at;
+    *(lds_bf16x4*)to = hi;
+    *(lds_bf16x4*)(to + 4 * kTileBytes) = lo;
+}
+
+// K slots of chunk kc of set q, as a B operand; at = slot_bytes(g, i)
+__device__ inline bf16x8 get_slots(const lds_char* buf, int q, int part, int kc, int at) {
+    const lds_char* from = buf + q * kSetBytes + (4 * part + 2 * kc) * kTileBytes + at;
+    return join(*(const lds_bf16x4*)from, *(const lds_bf16x4*)(from + kTileBytes));
+}
+
+// unit i of points 4 g .. 4 g + 3 of unit tile t of set q; at = slot_bytes(i % 4, 4 g + i / 4)
+__device__ inline bf16x4 get_points(lds_char* buf, int q, int part, int t, int at) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+        (lds_bf16x4*)(buf + q * kSetBytes + (4 * part + t) * kTileBytes + at));
+}
+
+struct RowWeights { bf16x8 h[2], l[2]; };      // K chunks of 16 rows of a layer
+__device__ inline RowWeights load_rows(const u32x4* __restrict__ layer, int w, int lane) {
+    RowWeights o;
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[ch][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kc = 0; kc < 2; ++kc) {
+        const int fr = (w * 2 + kc) * 64 + lane;
+        o.h[kc] = __builtin_bit_cast(bf16x8, layer[2 * fr]);
+        o.l[kc] = __builtin_bit_cast(bf16x8, layer[2 * fr + 1]);
+    }
+    return o;
+}
+
+template <int S>
+__device__ inline void rows_product(const RowWeights& wt, const lds_char* buf, int at, f32x4 acc[S]) {
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+    for (int q = 0; q < S; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const int fr = (mt * 2 + kc) * 64 + lane;
-            const bf16x8 ah = __builtin_bit_cast(bf16x8, w[2 * fr]);
-            const bf16x8 al = __builtin_bit_cast(bf16x8, w[2 * fr + 1]);
+    for (int kc = 0; kc < 2; ++kc)
 #pragma unroll
-            for (int ch = 0; ch < NC; ++ch) acc[ch][mt] = mma3(ah, al, bh[ch][kc], bl[ch][kc], acc[ch][mt]);
+        for (int q = 0; q < S; ++q)
+            acc[q] = mma3(wt.h[kc], wt.l[kc], get_slots(buf, q, 0, kc, at), get_slots(buf, q, 1, kc, at), acc[q]);
+}
+
+// Layer outputs of NC channels from the pre-activation derivatives z[1..] and
+// h = tanh(z[0]) (h' = 1 - h^2, h'' = -2 h (1 - h^2))
+template <int D, int NC>
+__device__ inline void outputs(const float h, const float* z, float* out) {
+    out[0] = h;
+    if constexpr (NC > 1) {
+        const float s = 1.f - h * h;
+        float zz = 0.f;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            zz += z[1 + c] * z[1 + c];
+            out[1 + c] = s * z[1 + c];
         }
+        out[D + 1] = s * z[D + 1] - 2.f * h * s * zz;
     }
 }
 
@@ -168,78 +228,95 @@ struct EvalArgs {
 
 // ---------------------------------------------------------------------------
 // evaluation: N, and with LAP the gradient and Laplacian channels, carried
-// through each layer by the chain rule (h = tanh z: h' = 1 - h^2,
-// h'' = -2 h (1 - h^2)).  The forward weights (64 KB) are staged in LDS.
+// through each layer by the chain rule.  A wavefront keeps its rows of all
+// four layers in registers.  (With 64 KB of weights staged in LDS and a tile
+// of points to each wavefront, every block of the 1024 staged them for one
+// tile per wavefront: 65,536 points with derivatives 115 us, now 78 us, of which
+// issuing the vector arithmetic of tanh, sincos and the BF16 splits is 45.)
 // ---------------------------------------------------------------------------
 template <int D, bool LAP, class TX>
-__global__ void __launch_bounds__(256) eval_kernel(EvalArgs<TX> a) {
-    constexpr int NC = LAP ? D + 2 : 1;
-    __shared__ u32x4 s_w[kPackDirU4];
-    for (int i = threadIdx.x; i < kPackDirU4; i += blockDim.x) s_w[i] = a.packed[i];
-    __syncthreads();
-    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int waves = blockDim.x >> 6;
-    const float* w5 = a.theta + (size_t)kLayers * kLayerSize;
-    for (int64_t tile = (int64_t)blockIdx.x * waves + (threadIdx.x >> 6); tile * 16 < a.n;
-         tile += (int64_t)gridDim.x * waves) {
-        const int64_t p = tile * 16 + col;
-        bool valid = p < a.n;
-        if (valid && a.mask) valid = a.mask[p / a.mask_div] >= a.mask_min;
-        if (__ballot(valid) == 0ull) continue;   // wave-uniform
-        float x[D];
+__global__ void __launch_bounds__(64 * kNetWaves, 2) eval_kernel(EvalArgs<TX> a) {
+    constexpr int NC = LAP ? D + 2 : 1, NT = LAP ? 1 : 4, S = NC * NT;
+    __shared__ __align__(16) char s_act[2][S * kSetBytes];
+    __shared__ float s_out[kNetWaves][S * 16];
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4, w = threadIdx.x >> 6;
+    const int at = slot_bytes(g, i);
+    lds_char* buf[2] = {(lds_char*)s_act[0], (lds_char*)s_act[1]};
+    FeatureRows<D> fr;
+    fr.load(a.B, a.F, w, g);
+    RowWeights wt[kLayers];
+    float bias[kLayers][4], w5[4];
 #pragma unroll
-        for (int c = 0; c < D; ++c) x[c] = valid ? (float)a.X[p * D + c] : 0.f;
-        float act[NC][4][4];
-        features<D, NC>(a.B, a.F, x, g, act);
-        bf16x8 bh[NC][2], bl[NC][2];
-        f32x4 acc[NC][4];
-#pragma unroll 1
+    for (int l = 0; l < kLayers; ++l) {
+        wt[l] = load_rows(a.packed + (size_t)l * kPackLayerU4, w, lane);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bias[l][r] = a.theta[l * kLayerSize + kWidth * kWidth + 16 * w + 4 * g + r];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w5[r] = a.theta[kLayers * kLayerSize + 16 * w + 4 * g + r];
+    const float b5 = a.theta[kLayers * kLayerSize + kWidth];
+    for (int64_t it = blockIdx.x; it * (16 * NT) < a.n; it += gridDim.x) {
+        bool any = false;
+        float x[NT][D];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int64_t p = (it * NT + nt) * 16 + i;
+            bool valid = p < a.n;
+            if (valid && a.mask) valid = a.mask[p / a.mask_div] >= a.mask_min;
+            any |= valid;
+#pragma unroll
+            for (int c = 0; c < D; ++c) x[nt][c] = valid ? (float)a.X[p * D + c] : 0.f;
+        }
+        if (__ballot(any) == 0ull) continue;   // the same in the four wavefronts
+        float act[S][4];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) fr.template eval<NC>(x[nt], act + nt * NC);
+#pragma unroll
+        for (int q = 0; q < S; ++q) put_set(buf[0], q, w, at, act[q]);
+        __syncthreads();
+#pragma unroll
         for (int l = 0; l < kLayers; ++l) {
-            to_operands<NC>(act, bh, bl);
-            layer_product<NC>(s_w + (size_t)l * kPackLayerU4, lane, bh, bl, acc);
-            const float* bias = a.theta + (size_t)l * kLayerSize + kWidth * kWidth;
+            f32x4 acc[S];
+            rows_product<S>(wt[l], buf[l & 1], at, acc);
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float z = acc[0][mt][r] + bias[16 * mt + 4 * g + r];
-                    const float h = tanhf(z), s = 1.f - h * h;
-                    act[0][mt][r] = h;
-                    if constexpr (LAP) {
-                        float zz = 0.f;
+                    float z[NC], out[NC];
 #pragma unroll
-                        for (int c = 0; c < D; ++c) {
-                            const float zg = acc[1 + c][mt][r];
-                            zz += zg * zg;
-                            act[1 + c][mt][r] = s * zg;
-                        }
-                        act[D + 1][mt][r] = s * acc[D + 1][mt][r] - 2.f * h * s * zz;
-                    }
+                    for (int ch = 0; ch < NC; ++ch) z[ch] = acc[nt * NC + ch][r];
+                    outputs<D, NC>(tanhf(z[0] + bias[l][r]), z, out);
+#pragma unroll
+                    for (int ch = 0; ch < NC; ++ch) act[nt * NC + ch][r] = out[ch];
                 }
-        }
-        float o[NC];
+            if (l + 1 < kLayers) {
 #pragma unroll
-        for (int ch = 0; ch < NC; ++ch) o[ch] = 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float w = w5[16 * t + 4 * g + r];
-#pragma unroll
-                for (int ch = 0; ch < NC; ++ch) o[ch] += w * act[ch][t][r];
+                for (int q = 0; q < S; ++q) put_set(buf[(l + 1) & 1], q, w, at, act[q]);
+                __syncthreads();
             }
-#pragma unroll
-        for (int ch = 0; ch < NC; ++ch) {
-            o[ch] += __shfl_xor(o[ch], 16);
-            o[ch] += __shfl_xor(o[ch], 32);
         }
-        if (g == 0 && valid) {
-            a.N[p] = o[0] + w5[kWidth];
-            if constexpr (LAP) {
-                if (a.G)
 #pragma unroll
-                    for (int c = 0; c < D; ++c) a.G[p * D + c] = o[1 + c];
-                if (a.L) a.L[p] = o[D + 1];
+        for (int q = 0; q < S; ++q) {
+            float o = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o += w5[r] * act[q][r];
+            o += __shfl_xor(o, 16);
+            o += __shfl_xor(o, 32);
+            if (g == 0) s_out[w][q * 16 + i] = o;
+        }
+        __syncthreads();
+        if (threadIdx.x < S * 16) {
+            const int q = threadIdx.x >> 4, nt = q / NC, ch = q - nt * NC;
+            const int64_t p = (it * NT + nt) * 16 + (threadIdx.x & 15);
+            bool valid = p < a.n;
+            if (valid && a.mask) valid = a.mask[p / a.mask_div] >= a.mask_min;
+            if (valid) {
+                float o = 0.f;
+#pragma unroll
+                for (int k = 0; k < kNetWaves; ++k) o += s_out[k][threadIdx.x];
+                if (ch == 0) a.N[p] = o + b5;
+                else if (ch <= D) { if (a.G) a.G[p * D + ch - 1] = o; }
+                else if (a.L) a.L[p] = o;
             }
         }
     }
@@ -260,317 +337,267 @@ struct TrainArgs {
     const float* B;
     int F;
     const float* X;
-    const float* T;
-    const float* w;
+    const float* nbar;   // LOSS: targets; else adjoints of N
+    const float* lbar;   // LOSS: weights or null (1); else adjoints of Lap N, or null
     int64_t n;
-    float* grad;
-    float* loss;
-    __bf16* ws;       // [layer][tile of 16 points][dh, dl, ah, al][64 units][16 points]
-    int64_t pad;      // batch rounded up to 32 points
+    float* part;         // kPartial sums per block
 };
+constexpr int kPartial = kThetaSize + 1;      // the parameters' gradient and the loss
 
 // ---------------------------------------------------------------------------
-// squared-loss backward, part 1: forward, output-layer and bias gradients,
-// back-propagated deltas; writes each layer's delta and input activation
-// (hi/lo BF16, unit-major) for the weight-gradient products.
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256) loss_grad_kernel(TrainArgs a) {
-    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int waves = blockDim.x >> 6;
-    const float* w5 = a.theta + (size_t)kLayers * kLayerSize;
-    const u32x4* fwd = a.packed;
-    const u32x4* bwd = a.packed + kPackDirU4;
-    float loss_acc = 0.f;
-    for (int64_t tile = (int64_t)blockIdx.x * waves + (threadIdx.x >> 6); tile * 16 < a.pad;
-         tile += (int64_t)gridDim.x * waves) {
-        const int64_t p = tile * 16 + col;
-        const bool valid = p < a.n;
-        float x[D];
-#pragma unroll
-        for (int c = 0; c < D; ++c) x[c] = valid ? a.X[p * D + c] : 0.f;
-        const float om = valid ? (a.w ? a.w[p] : 1.f) : 0.f;
-        const float tg = valid ? a.T[p] : 0.f;
-        float cur[1][4][4];
-        features<D, 1>(a.B, a.F, x, g, cur);
-        bf16x8 bh[1][2], bl[1][2];
-        f32x4 acc[1][4];
-        // forward; each layer's input activation goes to the workspace (hi,
-        // lo), where the weight-gradient product and the backward pass read it
-        const int64_t ntiles = a.pad / 16;
-        // this lane's slot in a tile block: unit 4 g (+ 16 t + r), point col
-        const int lane_off = (4 * g) * 16 + col;
-#pragma unroll 1
-        for (int l = 0; l < kLayers; ++l) {
-            __bf16* base = a.ws + ((size_t)l * ntiles + tile) * 4 * kWidth * 16 + lane_off;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int uo = (16 * t + r) * 16;
-                    __bf16 h, lo;
-                    split(cur[0][t][r], h, lo);
-                    base[2 * kWidth * 16 + uo] = h;
-                    base[3 * kWidth * 16 + uo] = lo;
-                }
-            to_operands<1>(cur, bh, bl);
-            layer_product<1>(fwd + (size_t)l * kPackLayerU4, lane, bh, bl, acc);
-            const float* bias = a.theta + (size_t)l * kLayerSize + kWidth * kWidth;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) cur[0][mt][r] = tanhf(acc[0][mt][r] + bias[16 * mt + 4 * g + r]);
-        }
-        float o = 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o += w5[16 * t + 4 * g + r] * cur[0][t][r];
-        o += __shfl_xor(o, 16);
-        o += __shfl_xor(o, 32);
-        const float N = o + w5[kWidth];
-        const float res = om * (N - tg);
-        if (g == 0) loss_acc += 0.5f * om * (N - tg) * (N - tg);
-        // output layer
-        float delta[1][4][4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int u = 16 * t + 4 * g + r;
-                const float h = cur[0][t][r];
-                const float gw = col_sum(res * h);
-                if (col == 0) atomicAdd(&a.grad[(size_t)kLayers * kLayerSize + u], gw);
-                delta[0][t][r] = res * w5[u] * (1.f - h * h);
-            }
-        {
-            const float gb = col_sum(g == 0 ? res : 0.f);
-            if (lane == 0) atomicAdd(&a.grad[(size_t)kLayers * kLayerSize + kWidth], gb);
-        }
-#pragma unroll 1
-        for (int l = kLayers - 1; l >= 0; --l) {
-            __bf16* base = a.ws + ((size_t)l * ntiles + tile) * 4 * kWidth * 16 + lane_off;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int u = 16 * t + 4 * g + r;
-                    const float gb = col_sum(delta[0][t][r]);
-                    if (col == 0) atomicAdd(&a.grad[(size_t)l * kLayerSize + kWidth * kWidth + u], gb);
-                    const int uo = (16 * t + r) * 16;
-                    __bf16 h, lo;
-                    split(delta[0][t][r], h, lo);
-                    base[uo] = h;
-                    base[kWidth * 16 + uo] = lo;
-                }
-            if (l == 0) break;
-            // delta_{l-1} = (W_l^T delta_l) (1 - a_l^2), a_l read back (hi + lo)
-            to_operands<1>(delta, bh, bl);
-            layer_product<1>(bwd + (size_t)l * kPackLayerU4, lane, bh, bl, acc);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int uo = (16 * mt + r) * 16;
-                    const float h = (float)base[2 * kWidth * 16 + uo] + (float)base[3 * kWidth * 16 + uo];
-                    delta[0][mt][r] = acc[0][mt][r] * (1.f - h * h);
-                }
-        }
-    }
-    // loss: wave sum, one atomic per wave
-    loss_acc += __shfl_xor(loss_acc, 1);
-    loss_acc += __shfl_xor(loss_acc, 2);
-    loss_acc += __shfl_xor(loss_acc, 4);
-    loss_acc += __shfl_xor(loss_acc, 8);
-    loss_acc += __shfl_xor(loss_acc, 16);
-    loss_acc += __shfl_xor(loss_acc, 32);
-    if (lane == 0 && a.loss) atomicAdd(a.loss, loss_acc);
-}
-
-// ---------------------------------------------------------------------------
-// squared-loss backward, part 2: dW_l = delta_l a_l^T over the batch, one
-// 16x16 output tile per wave and a slice of the batch per blockIdx.y
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) wgrad_kernel(const __bf16* __restrict__ ws, int64_t pad,
-                                                   int64_t chunks_per_split, float* __restrict__ grad) {
-    const int lane = threadIdx.x, i = lane & 15, g = lane >> 4;
-    const int l = blockIdx.x >> 4, mo = (blockIdx.x >> 2) & 3, mi = blockIdx.x & 3;
-    const int64_t ntiles = pad / 16, n_chunks = pad / 32;
-    const int64_t c0 = (int64_t)blockIdx.y * chunks_per_split;
-    const int64_t c1 = c0 + chunks_per_split < n_chunks ? c0 + chunks_per_split : n_chunks;
-    if (c0 >= c1) return;
-    // K slot (g, e) of chunk ck is point 32 ck + 8 g + e: tile 2 ck + g / 2,
-    // column 8 (g & 1) + e
-    const int a_off = (16 * mo + i) * 16 + 8 * (g & 1);
-    const int b_off = (16 * mi + i) * 16 + 8 * (g & 1);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int64_t ck = c0; ck < c1; ++ck) {
-        const __bf16* blk = ws + ((size_t)l * ntiles + 2 * ck + (g >> 1)) * 4 * kWidth * 16;
-        const bf16x8 Ah = *reinterpret_cast<const bf16x8*>(blk + a_off);
-        const bf16x8 Al = *reinterpret_cast<const bf16x8*>(blk + kWidth * 16 + a_off);
-        const bf16x8 Bh = *reinterpret_cast<const bf16x8*>(blk + 2 * kWidth * 16 + b_off);
-        const bf16x8 Bl = *reinterpret_cast<const bf16x8*>(blk + 3 * kWidth * 16 + b_off);
-        acc = mma3(Ah, Al, Bh, Bl, acc);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        atomicAdd(&grad[(size_t)l * kLayerSize + (16 * mo + 4 * g + r) * kWidth + 16 * mi + i], acc[r]);
-}
-
-struct VjpArgs {
-    const u32x4* packed;
-    const float* theta;
-    const float* B;
-    int F;
-    const float* X;
-    const float* Nbar;
-    const float* Lbar;
-    int64_t n;
-    int64_t pad;
-    float* grad;
-    __bf16* ws;       // [layer][virtual tile = tile * NC + channel][zh, zl, ah, al][64][16]
-    float* zs;        // [layer][tile][channel][64][16] pre-activations
-};
-
-// ---------------------------------------------------------------------------
-// grad += d/dtheta sum_i (Nbar_i N(x_i) + Lbar_i Lap N(x_i)), part 1.  The
-// forward pass carries the value, gradient and Laplacian channels (as in
-// eval_kernel) and keeps each layer's pre-activations; the backward pass
-// turns the output adjoints into pre-activation adjoints per layer
-// (h = tanh z, s = 1 - h^2, Q = sum_c z_c^2):
+// Parameter gradients.  LOSS: of sum 1/2 w (N - t)^2 over the points (value
+// channel, four tiles of points at a time); else of sum Nbar N + Lbar Lap N
+// with the value, gradient and Laplacian channels of one tile.  Backward, with
+// h = tanh z, s = 1 - h^2, Q = sum_c z_c^2:
 //   zbar_L = s abar_L,  zbar_c = s abar_c - 4 h s z_c abar_L,
 //   zbar = s abar - 2 h s sum_c z_c abar_c - (2 h s z_L + 2 s (s - 2 h^2) Q) abar_L
-// and sends every channel back through W^T on the matrix cores.  Each
-// layer's channel inputs and pre-activation adjoints go to the workspace for
-// the weight-gradient products, which contract over points and channels.
+// Every channel goes back through W^T, and dW = sum over points and channels of
+// zbar a^T, all on the matrix cores in one pass; the blocks' sums are added by
+// sum_kernel in one order.  (As one kernel that left every layer's operands and
+// pre-activations in memory, 1 GB for 65,536 points, added each tile's bias
+// gradients with atomics, and was followed by a product over that memory:
+// 0.78 + 0.29 ms, now 0.22 + 0.01.  One block per CU: two, at 256 registers a
+// lane, spill 125 of them and take 0.24 ms.)
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256) vjp_kernel(VjpArgs a) {
-    constexpr int NC = D + 2;
-    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const int waves = blockDim.x >> 6;
-    const float* w5 = a.theta + (size_t)kLayers * kLayerSize;
-    const u32x4* fwd = a.packed;
-    const u32x4* bwd = a.packed + kPackDirU4;
-    const int64_t ntiles = a.pad / 16;
-    const int lane_off = (4 * g) * 16 + col;
-    for (int64_t tile = (int64_t)blockIdx.x * waves + (threadIdx.x >> 6); tile < ntiles;
-         tile += (int64_t)gridDim.x * waves) {
-        const int64_t p = tile * 16 + col;
-        const bool valid = p < a.n;
-        float x[D];
+template <int D, bool LOSS>
+__global__ void __launch_bounds__(64 * kNetWaves, 1) grad_kernel(TrainArgs a) {
+    constexpr int NC = LOSS ? 1 : D + 2, NT = LOSS ? 4 : 1, S = NC * NT;
+    __shared__ __align__(16) char s_act[3][S * kSetBytes];
+    __shared__ float s_out[kNetWaves][S * 16];
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4, w = threadIdx.x >> 6;
+    const int at = slot_bytes(g, i), att = slot_bytes(i & 3, 4 * g + (i >> 2));
+    __shared__ float s_bias[kLayers + 1][kWidth];       // and the output layer's weights
+    lds_char *feat = (lds_char*)s_act[0], *abuf = (lds_char*)s_act[1], *dbuf = (lds_char*)s_act[2];
+    const int u0 = 16 * w + 4 * g;             // the lane's units u0 + r
+    s_bias[w][lane] = a.theta[w * kLayerSize + kWidth * kWidth + lane];
+    if (w == 0) s_bias[kLayers][lane] = a.theta[kLayers * kLayerSize + lane];
+    const float b5 = a.theta[kLayers * kLayerSize + kWidth];
+    FeatureRows<D> fr;
+    fr.load(a.B, a.F, w, g);
+    __syncthreads();
+    f32x4 dW[kLayers][4];
+    float gb[kLayers][4], gw5[4], gb5 = 0.f, loss = 0.f;
 #pragma unroll
-        for (int c = 0; c < D; ++c) x[c] = valid ? a.X[p * D + c] : 0.f;
-        const float nb = valid ? a.Nbar[p] : 0.f;
-        const float lb = (valid && a.Lbar) ? a.Lbar[p] : 0.f;
-        float act[NC][4][4];
-        features<D, NC>(a.B, a.F, x, g, act);
-        bf16x8 bh[NC][2], bl[NC][2];
-        f32x4 acc[NC][4];
-#pragma unroll 1
+    for (int l = 0; l < kLayers; ++l)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { dW[l][k] = f32x4{0.f, 0.f, 0.f, 0.f}; gb[l][k] = 0.f; }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) gw5[k] = 0.f;
+    // the next layer's weights and the next points are loaded while a layer is computed
+    RowWeights wn = load_rows(a.packed, w, lane);
+    float xn[NT][D], nbn[NT], lbn[NT];
+    auto fetch = [&](int64_t it) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int64_t p = (it * NT + nt) * 16 + i;
+            const bool valid = p < a.n;
+#pragma unroll
+            for (int c = 0; c < D; ++c) xn[nt][c] = valid ? a.X[p * D + c] : 0.f;
+            nbn[nt] = valid ? a.nbar[p] : 0.f;
+            lbn[nt] = valid ? (a.lbar ? a.lbar[p] : (LOSS ? 1.f : 0.f)) : 0.f;
+        }
+    };
+    fetch(blockIdx.x);
+    for (int64_t it = blockIdx.x; it * (16 * NT) < a.n; it += gridDim.x) {
+        float act[S][4], z[kLayers][S][4];     // z: tanh z of the value channel, z of the others
+        float nb[NT], lb[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            nb[nt] = nbn[nt];
+            lb[nt] = lbn[nt];
+            fr.template eval<NC>(xn[nt], act + nt * NC);
+        }
+        fetch(it + gridDim.x);
+#pragma unroll
+        for (int q = 0; q < S; ++q) put_set(feat, q, w, at, act[q]);
+        f32x4 acc[S];
+#pragma unroll
         for (int l = 0; l < kLayers; ++l) {
-            __bf16* wsl = a.ws + ((size_t)l * ntiles + tile) * NC * 4 * kWidth * 16 + lane_off;
-            float* zsl = a.zs + (((size_t)l * ntiles + tile) * NC) * kWidth * 16 + lane_off;
+            const RowWeights wt = wn;
+            wn = load_rows(a.packed + (l + 1 < kLayers ? (size_t)(l + 1) * kPackLayerU4
+                                                       : kPackDirU4 + (size_t)l * kPackLayerU4), w, lane);
+            __syncthreads();
+            rows_product<S>(wt, l == 0 ? feat : (l & 1) ? abuf : dbuf, at, acc);
 #pragma unroll
-            for (int ch = 0; ch < NC; ++ch)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        __bf16 h, lo;
-                        split(act[ch][t][r], h, lo);
-                        const int uo = ch * 4 * kWidth * 16 + (16 * t + r) * 16;
-                        wsl[2 * kWidth * 16 + uo] = h;
-                        wsl[3 * kWidth * 16 + uo] = lo;
-                    }
-            to_operands<NC>(act, bh, bl);
-            layer_product<NC>(fwd + (size_t)l * kPackLayerU4, lane, bh, bl, acc);
-            const float* bias = a.theta + (size_t)l * kLayerSize + kWidth * kWidth;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float z = acc[0][mt][r] + bias[16 * mt + 4 * g + r];
-                    const int uo = (16 * mt + r) * 16;
-                    zsl[uo] = z;
+                    float zz[NC], out[NC];
 #pragma unroll
-                    for (int ch = 1; ch < NC; ++ch) zsl[ch * kWidth * 16 + uo] = acc[ch][mt][r];
-                    const float h = tanhf(z), s = 1.f - h * h;
-                    float zz = 0.f;
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        const float zg = acc[1 + c][mt][r];
-                        zz += zg * zg;
-                        act[1 + c][mt][r] = s * zg;
-                    }
-                    act[0][mt][r] = h;
-                    act[D + 1][mt][r] = s * acc[D + 1][mt][r] - 2.f * h * s * zz;
-                }
-        }
-        // output layer: N = w5 . a_v + b5, Lap N = w5 . a_L
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int u = 16 * t + 4 * g + r;
-                const float gw = col_sum(nb * act[0][t][r] + lb * act[D + 1][t][r]);
-                if (col == 0) atomicAdd(&a.grad[(size_t)kLayers * kLayerSize + u], gw);
-#pragma unroll
-                for (int ch = 0; ch < NC; ++ch) act[ch][t][r] = 0.f;   // becomes abar
-                act[0][t][r] = nb * w5[u];
-                act[D + 1][t][r] = lb * w5[u];
-            }
-        {
-            const float gb = col_sum(g == 0 ? nb : 0.f);
-            if (lane == 0) atomicAdd(&a.grad[(size_t)kLayers * kLayerSize + kWidth], gb);
-        }
-        // act now holds the adjoints abar of the current layer's outputs
-#pragma unroll 1
-        for (int l = kLayers - 1; l >= 0; --l) {
-            __bf16* wsl = a.ws + ((size_t)l * ntiles + tile) * NC * 4 * kWidth * 16 + lane_off;
-            const float* zsl = a.zs + (((size_t)l * ntiles + tile) * NC) * kWidth * 16 + lane_off;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int uo = (16 * t + r) * 16;
-                    const float z = zsl[uo];
-                    const float zL = zsl[(D + 1) * kWidth * 16 + uo];
-                    const float h = tanhf(z), s = 1.f - h * h;
-                    const float aL = act[D + 1][t][r];
-                    float Q = 0.f, za = 0.f;
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        const float zc = zsl[(1 + c) * kWidth * 16 + uo];
-                        Q += zc * zc;
-                        za += zc * act[1 + c][t][r];
-                        act[1 + c][t][r] = s * act[1 + c][t][r] - 4.f * h * s * zc * aL;
-                    }
-                    act[0][t][r] = s * act[0][t][r] - 2.f * h * s * za -
-                                   (2.f * h * s * zL + 2.f * s * (s - 2.f * h * h) * Q) * aL;
-                    act[D + 1][t][r] = s * aL;
-                    const int u = 16 * t + 4 * g + r;
-                    const float gb = col_sum(act[0][t][r]);
-                    if (col == 0) atomicAdd(&a.grad[(size_t)l * kLayerSize + kWidth * kWidth + u], gb);
+                    for (int ch = 0; ch < NC; ++ch) zz[ch] = acc[nt * NC + ch][r];
+                    zz[0] = tanhf(zz[0] + s_bias[l][u0 + r]);
+                    outputs<D, NC>(zz[0], zz, out);
 #pragma unroll
                     for (int ch = 0; ch < NC; ++ch) {
-                        __bf16 hh, lo;
-                        split(act[ch][t][r], hh, lo);
-                        const int o = ch * 4 * kWidth * 16 + uo;
-                        wsl[o] = hh;
-                        wsl[kWidth * 16 + o] = lo;
+                        z[l][nt * NC + ch][r] = zz[ch];
+                        act[nt * NC + ch][r] = out[ch];
                     }
                 }
-            if (l == 0) break;
-            to_operands<NC>(act, bh, bl);
-            layer_product<NC>(bwd + (size_t)l * kPackLayerU4, lane, bh, bl, acc);
+            if (l + 1 < kLayers) {
 #pragma unroll
-            for (int ch = 0; ch < NC; ++ch)
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) act[ch][mt][r] = acc[ch][mt][r];
+                for (int q = 0; q < S; ++q) put_set((l & 1) ? dbuf : abuf, q, w, at, act[q]);
+            }
         }
+        // output layer: the adjoints of N and Lap N, then of the last layer's outputs
+        float w5[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w5[r] = s_bias[kLayers][u0 + r];
+        if constexpr (LOSS) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                float o = 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o += w5[r] * act[nt][r];
+                o += __shfl_xor(o, 16);
+                o += __shfl_xor(o, 32);
+                if (g == 0) s_out[w][nt * 16 + i] = o;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                float o = 0.f;
+#pragma unroll
+                for (int k = 0; k < kNetWaves; ++k) o += s_out[k][nt * 16 + i];
+                const float e = o + b5 - nb[nt];
+                loss += 0.5f * lb[nt] * e * e;
+                nb[nt] = lb[nt] * e;
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            gb5 += nb[nt];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                gw5[r] += nb[nt] * act[nt * NC][r];
+                if constexpr (!LOSS) gw5[r] += lb[nt] * act[D + 1][r];
+#pragma unroll
+                for (int ch = 0; ch < NC; ++ch) act[nt * NC + ch][r] = 0.f;   // becomes abar
+                act[nt * NC][r] = nb[nt] * w5[r];
+                if constexpr (!LOSS) act[D + 1][r] = lb[nt] * w5[r];
+            }
+        }
+#pragma unroll
+        for (int l = kLayers - 1; l >= 0; --l) {
+            if (l < kLayers - 1) __syncthreads();   // abuf and dbuf are read
+            // the layer's inputs (the last layer's are there from the forward pass)
+            if (l > 0 && l < kLayers - 1) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    float in[NC][4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float zz[NC], out[NC];
+#pragma unroll
+                        for (int ch = 0; ch < NC; ++ch) zz[ch] = z[l > 0 ? l - 1 : 0][nt * NC + ch][r];
+                        outputs<D, NC>(zz[0], zz, out);
+#pragma unroll
+                        for (int ch = 0; ch < NC; ++ch) in[ch][r] = out[ch];
+                    }
+#pragma unroll
+                    for (int ch = 0; ch < NC; ++ch) put_set(abuf, nt * NC + ch, w, at, in[ch]);
+                }
+            }
+            // pre-activation adjoints
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float h = z[l][nt * NC][r], s = 1.f - h * h;
+                    if constexpr (LOSS) {
+                        act[nt][r] *= s;
+                    } else {
+                        const float aL = act[D + 1][r], zL = z[l][D + 1][r];
+                        float Q = 0.f, za = 0.f;
+#pragma unroll
+                        for (int c = 0; c < D; ++c) {
+                            const float zc = z[l][1 + c][r];
+                            Q += zc * zc;
+                            za += zc * act[1 + c][r];
+                            act[1 + c][r] = s * act[1 + c][r] - 4.f * h * s * zc * aL;
+                        }
+                        act[0][r] = s * act[0][r] - 2.f * h * s * za -
+                                    (2.f * h * s * zL + 2.f * s * (s - 2.f * h * h) * Q) * aL;
+                        act[D + 1][r] = s * aL;
+                    }
+                    gb[l][r] += act[nt * NC][r];
+                }
+#pragma unroll
+            for (int q = 0; q < S; ++q) put_set(dbuf, q, w, at, act[q]);
+            const RowWeights wt = wn;
+            if (l > 0) wn = load_rows(a.packed + (l > 1 ? kPackDirU4 + (size_t)(l - 1) * kPackLayerU4 : 0), w, lane);
+            __syncthreads();
+            // dW rows of this wavefront: K = points of two sets at a time
+            lds_char* in = l == 0 ? feat : abuf;
+#pragma unroll
+            for (int q = 0; q + 1 < S; q += 2) {
+                const bf16x8 dh = join(get_points(dbuf, q, 0, w, att), get_points(dbuf, q + 1, 0, w, att));
+                const bf16x8 dl = join(get_points(dbuf, q, 1, w, att), get_points(dbuf, q + 1, 1, w, att));
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    dW[l][t] = mma3(dh, dl, join(get_points(in, q, 0, t, att), get_points(in, q + 1, 0, t, att)),
+                                    join(get_points(in, q, 1, t, att), get_points(in, q + 1, 1, t, att)), dW[l][t]);
+            }
+            if constexpr (S & 1) {
+                const s16x4 dh = __builtin_bit_cast(s16x4, get_points(dbuf, S - 1, 0, w, att));
+                const s16x4 dl = __builtin_bit_cast(s16x4, get_points(dbuf, S - 1, 1, w, att));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const s16x4 ih = __builtin_bit_cast(s16x4, get_points(in, S - 1, 0, t, att));
+                    const s16x4 il = __builtin_bit_cast(s16x4, get_points(in, S - 1, 1, t, att));
+                    dW[l][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(dh, ih, dW[l][t], 0, 0, 0);
+                    dW[l][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(dh, il, dW[l][t], 0, 0, 0);
+                    dW[l][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(dl, ih, dW[l][t], 0, 0, 0);
+                }
+            }
+            if (l > 0) {
+                rows_product<S>(wt, dbuf, at, acc);
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) act[q][r] = acc[q][r];
+            }
+        }
+        __syncthreads();                       // the buffers are free for the next points
+    }
+    float* out = a.part + (size_t)blockIdx.x * kPartial;
+#pragma unroll
+    for (int l = 0; l < kLayers; ++l)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) out[l * kLayerSize + (u0 + r) * kWidth + 16 * t + i] = dW[l][t][r];
+            const float b = col_sum(gb[l][r]);
+            if (i == 0) out[l * kLayerSize + kWidth * kWidth + u0 + r] = b;
+        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float b = col_sum(gw5[r]);
+        if (i == 0) out[kLayers * kLayerSize + u0 + r] = b;
+    }
+    gb5 = col_sum(gb5);
+    loss = col_sum(loss);
+    if (threadIdx.x == 0) {
+        out[kLayers * kLayerSize + kWidth] = gb5;
+        out[kThetaSize] = loss;
+    }
+}
+
+// grad (and the loss, if asked for) = the blocks' sums
+__global__ void __launch_bounds__(256) sum_kernel(const float* __restrict__ part, int blocks, float* __restrict__ grad,
+                                                  float* __restrict__ loss) {
+    __shared__ double s[4][64];
+    const int k = blockIdx.x * 64 + (threadIdx.x & 63), slice = threadIdx.x >> 6;
+    double v = 0.0;
+    if (k < kPartial) {
+#pragma unroll 8
+        for (int b = slice; b < blocks; b += 4) v += (double)part[(size_t)b * kPartial + k];
+    }
+    s[slice][threadIdx.x & 63] = v;
+    __syncthreads();
+    if (slice == 0 && k < kPartial) {
+        const float t = (float)((s[0][threadIdx.x] + s[1][threadIdx.x]) + (s[2][threadIdx.x] + s[3][threadIdx.x]));
+        if (k < kThetaSize) grad[k] = t;
+        else if (loss) *loss = t;
     }
 }
 
@@ -611,11 +638,10 @@ hipError_t zero(float* p, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-unsigned grid_for_tiles(int64_t n, int max_blocks) {
-    const int64_t tiles = (n + 15) / 16;
-    int64_t b = (tiles + 3) / 4;
-    if (b > max_blocks) b = max_blocks;
-    return (unsigned)(b < 1 ? 1 : b);
+// Blocks of a persistent launch over groups of `points` points: at most
+// `per_cu` per CU.
+unsigned net_grid(const dwos_mlp* m, int64_t n, int points, int per_cu) {
+    return (unsigned)std::min<int64_t>((n + points - 1) / points, (int64_t)per_cu * m->cu_count);
 }
 
 template <class TX>
@@ -626,7 +652,7 @@ hipError_t mlp_eval_launch(const dwos_mlp* m, hipStream_t s, const TX* X, int64_
     EvalArgs<TX> a{m->packed.as<u32x4>(), m->theta.as<float>(), m->B.as<float>(), m->F, X, n,
                    mask, mask_div < 1 ? 1 : mask_div, mask_min, N, G, L};
     const bool lap = G || L;
-    const dim3 grid(grid_for_tiles(n, 2048)), block(256);
+    const dim3 grid(net_grid(m, n, lap ? 16 : 64, 2)), block(64 * kNetWaves);
     if (m->dim == 2) {
         if (lap) hipLaunchKernelGGL((eval_kernel<2, true, TX>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((eval_kernel<2, false, TX>), grid, block, 0, s, a);
@@ -642,56 +668,35 @@ template hipError_t mlp_eval_launch<float>(const dwos_mlp*, hipStream_t, const f
 template hipError_t mlp_eval_launch<double>(const dwos_mlp*, hipStream_t, const double*, int64_t,
                                             const int32_t*, int, int, float*, float*, float*);
 
+// grad (and *loss) from TrainArgs without its workspace
+template <bool LOSS>
+hipError_t grad_launch(dwos_mlp* m, hipStream_t s, TrainArgs a, float* loss) {
+    hipError_t e;
+    if (a.n <= 0) {
+        if (loss && (e = zero(loss, 1, s)) != hipSuccess) return e;
+        return zero(m->grad.as<float>(), kThetaSize, s);
+    }
+    const unsigned grid = net_grid(m, a.n, LOSS ? 64 : 16, 1);
+    if ((e = m->ws.reserve((size_t)m->cu_count * kPartial * sizeof(float))) != hipSuccess) return e;
+    a.part = m->ws.as<float>();
+    if (m->dim == 2) hipLaunchKernelGGL((grad_kernel<2, LOSS>), dim3(grid), dim3(64 * kNetWaves), 0, s, a);
+    else hipLaunchKernelGGL((grad_kernel<3, LOSS>), dim3(grid), dim3(64 * kNetWaves), 0, s, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(sum_kernel, dim3(blocks_for(kPartial, 64)), dim3(256), 0, s, a.part, (int)grid,
+                       m->grad.as<float>(), loss);
+    return hipGetLastError();
+}
+
 hipError_t mlp_loss_grad_launch(dwos_mlp* m, hipStream_t s, const float* X, const float* T,
                                 const float* w, int64_t n, float* loss) {
-    hipError_t e;
-    if ((e = zero(m->grad.as<float>(), kThetaSize, s)) != hipSuccess) return e;
-    if (loss && (e = zero(loss, 1, s)) != hipSuccess) return e;
-    if (n <= 0) return hipSuccess;
-    const int64_t pad = (n + 31) / 32 * 32;
-    if ((e = m->ws.reserve((size_t)kLayers * 4 * kWidth * pad * sizeof(__bf16))) != hipSuccess) return e;
-    m->ws_pad = pad;
-    TrainArgs a{m->packed.as<u32x4>(), m->theta.as<float>(), m->B.as<float>(), m->F, X, T, w, n,
-                m->grad.as<float>(), loss, m->ws.as<__bf16>(), pad};
-    // the kernel walks every tile up to pad, so each workspace column is
-    // written (padding points carry a zero delta)
-    const dim3 grid(grid_for_tiles(pad, 1024)), block(256);
-    if (m->dim == 2) hipLaunchKernelGGL(loss_grad_kernel<2>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(loss_grad_kernel<3>, grid, block, 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int64_t chunks = pad / 32;
-    int64_t splits = chunks < 128 ? chunks : 128;
-    const int64_t per = (chunks + splits - 1) / splits;
-    splits = (chunks + per - 1) / per;
-    hipLaunchKernelGGL(wgrad_kernel, dim3(kLayers * 16, (unsigned)splits), dim3(64), 0, s,
-                       m->ws.as<__bf16>(), pad, per, m->grad.as<float>());
-    return hipGetLastError();
+    return grad_launch<true>(m, s, {m->packed.as<u32x4>(), m->theta.as<float>(), m->B.as<float>(), m->F, X, T, w, n,
+                                    nullptr}, loss);
 }
 
 hipError_t mlp_vjp_launch(dwos_mlp* m, hipStream_t s, const float* X, const float* Nbar,
                           const float* Lbar, int64_t n) {
-    hipError_t e;
-    if ((e = zero(m->grad.as<float>(), kThetaSize, s)) != hipSuccess) return e;
-    if (n <= 0) return hipSuccess;
-    const int NC = m->dim + 2;
-    const int64_t pad = (n + 31) / 32 * 32;
-    if ((e = m->ws.reserve((size_t)kLayers * NC * 4 * kWidth * pad * sizeof(__bf16))) != hipSuccess) return e;
-    if ((e = m->zs.reserve((size_t)kLayers * NC * kWidth * pad * sizeof(float))) != hipSuccess) return e;
-    VjpArgs a{m->packed.as<u32x4>(), m->theta.as<float>(), m->B.as<float>(), m->F, X, Nbar, Lbar, n, pad,
-              m->grad.as<float>(), m->ws.as<__bf16>(), m->zs.as<float>()};
-    const dim3 grid(grid_for_tiles(pad, 1024)), block(256);
-    if (m->dim == 2) hipLaunchKernelGGL(vjp_kernel<2>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(vjp_kernel<3>, grid, block, 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // weight gradients: contraction over the pad * NC (point, channel) pairs
-    const int64_t padv = pad * NC;
-    const int64_t chunks = padv / 32;
-    int64_t splits = chunks < 128 ? chunks : 128;
-    const int64_t per = (chunks + splits - 1) / splits;
-    splits = (chunks + per - 1) / per;
-    hipLaunchKernelGGL(wgrad_kernel, dim3(kLayers * 16, (unsigned)splits), dim3(64), 0, s,
-                       m->ws.as<__bf16>(), padv, per, m->grad.as<float>());
-    return hipGetLastError();
+    return grad_launch<false>(m, s, {m->packed.as<u32x4>(), m->theta.as<float>(), m->B.as<float>(), m->F, X, Nbar, Lbar,
+                                     n, nullptr}, nullptr);
 }
 
 hipError_t mlp_adam_launch(dwos_mlp* m, hipStream_t s, float lr, float beta1, float beta2, float eps) {
@@ -733,7 +738,9 @@ dwos_status dwos_mlp_create(int32_t dim, int32_t F, const float* B, void* stream
     m->dim = dim;
     m->F = F;
     m->stream = static_cast<hipStream_t>(stream);
-    if (hipGetDevice(&m->device) != hipSuccess) return bail(fail(DWOS_EDEVICE, "mlp_create: hipGetDevice"));
+    if (hipGetDevice(&m->device) != hipSuccess ||
+        hipDeviceGetAttribute(&m->cu_count, hipDeviceAttributeMultiprocessorCount, m->device) != hipSuccess)
+        return bail(fail(DWOS_EDEVICE, "mlp_create: hipGetDevice"));
     using namespace dwos_mlp_k;
     const size_t tb = (size_t)kThetaSize * sizeof(float);
     if (m->theta.reserve(tb) || m->m.reserve(tb) || m->v.reserve(tb) || m->grad.reserve(tb) ||

@@ -37,11 +37,8 @@ struct dwos_mlp {
     hipStream_t stream = nullptr;
     dwos_host::DevBuf theta, m, v, grad, B, packed, loss;
     int64_t step = 0;
-    // training workspace: per layer delta and input activations, hi/lo BF16,
-    // unit-major with the batch padded to a multiple of 32
-    dwos_host::DevBuf ws;
-    int64_t ws_pad = 0;
-    dwos_host::DevBuf zs;   // pre-activations of every layer and channel (vjp)
+    int cu_count = 0;
+    dwos_host::DevBuf ws;   // per block of a gradient launch, its sums
 };
 
 namespace dwos_host {
