@@ -1460,8 +1460,10 @@ dwos_status run_op(dwos_ctx* c, Op op, const OpArgs& o, dwos_stats* st) {
             ja.udot = op == Op::Jvp ? o.udot : nullptr;
             ja.udot_var = op == Op::Jvp ? o.udot_var : nullptr;
             ja.walk_udot = op == Op::Records ? o.rec_udot_out + p0 * W * c->N : nullptr;
-            dim3 grid((unsigned)Pc, (unsigned)((c->N + 63) / 64));
-            hipLaunchKernelGGL((dwos::jvp_kernel<T, D>), grid, dim3(64), 0, s, ja);
+            int lanes = 1;
+            while (lanes < 64 && lanes < c->N) lanes *= 2;
+            dim3 grid((unsigned)Pc, (unsigned)((c->N + lanes - 1) / lanes));
+            hipLaunchKernelGGL((dwos::jvp_kernel<T, D>), grid, dim3(dwos::kJvpThreads), 0, s, ja, lanes);
         }
         if (op == Op::Records) {
             hipLaunchKernelGGL(copy_records_kernel<T>, dim3(blocks_for(walks, 256)), dim3(256), 0, s,
