@@ -839,6 +839,28 @@ dwos_status launch_walks(dwos_ctx* c, dwos::WalkArgs<T>& a, dwos::Counters* tot 
     return launch_variant<T, D, MODE, false>(c, a, timed);
 }
 
+// Launch attributes and occupancy of a kernel, computed once per LDS size (no
+// runtime queries on later, possibly captured, calls).
+template <auto KERN>
+dwos_status shape_ready(int block, size_t smem, int& per_cu) {
+    static size_t attr_smem = 0;
+    static size_t occ_smem = ~size_t(0);
+    static int occ_per_cu = 1;
+    if (smem > attr_smem) {
+        HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+        attr_smem = smem;
+    }
+    if (occ_smem != smem) {
+        int per = 0;
+        HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, KERN, block, smem));
+        occ_per_cu = std::max(1, per);
+        occ_smem = smem;
+    }
+    per_cu = occ_per_cu;
+    return DWOS_OK;
+}
+
 template <class T, int D, int MODE, int STAGE, bool cv>
 dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     hipStream_t s = c->stream;
@@ -849,25 +871,26 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     a.stack_off = (uint32_t)staged;
     a.stack_lds = (int32_t)std::min<size_t>(kMaxStack, room);
     const size_t smem = staged + (size_t)a.stack_lds * block * entry;
-    auto kern = dwos::walk_kernel<T, D, MODE, STAGE, cv>;
-    // launch attributes and occupancy are computed once per kernel and LDS
-    // size (no runtime queries on later, possibly captured, calls)
-    static size_t attr_smem = 0;
-    static size_t occ_smem = ~size_t(0);
-    static int occ_per_cu = 1;
-    if (smem > attr_smem) {
-        HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-        attr_smem = smem;
-    }
-    if (occ_smem != smem) {
-        int per = 0;
-        HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, block, smem));
-        occ_per_cu = std::max(1, per);
-        occ_smem = smem;
-    }
-    const int per_cu = occ_per_cu;
+    // FP32 launches of few walks give each walk two or four of the lanes that
+    // would idle: they share its leaf tests, a wavefront's longest loop when few
+    // lanes of it work.  Without / with, us: 128-gon probe, 32,768 walks, 474 /
+    // 416; 4096-segment forward mode, 131,072 walks (two lanes), 1795 / 1498;
+    // 19,220 triangles, 73,963 walks, 2490 / 2082.  A launch that fills the
+    // wavefronts has no such lanes; the control variate's build is left alone.
+    constexpr bool can_group = sizeof(T) == 4 && !cv;
+    auto kern = dwos::walk_kernel<T, D, MODE, STAGE, cv, false>;
+    int per_cu = 0;
+    dwos_status st = shape_ready<dwos::walk_kernel<T, D, MODE, STAGE, cv, false>>(block, smem, per_cu);
+    if (st) return st;
     const Split sp = split_walks(a.total, block, per_cu, c->cu_count, c->chunk, 16);
+    if constexpr (can_group) {
+        if (sp.lanes <= 32) {
+            kern = dwos::walk_kernel<T, D, MODE, STAGE, cv, true>;
+            st = shape_ready<dwos::walk_kernel<T, D, MODE, STAGE, cv, true>>(block, smem, per_cu);
+            if (st) return st;
+            a.group = sp.lanes <= 16 ? 4 : 2;
+        }
+    }
     set_div(a);
     a.lanes = sp.lanes;
     a.chunk = sp.chunk;
@@ -1086,6 +1109,7 @@ dwos::WalkArgs<T> base_args(dwos_ctx* c, const double* X, int32_t W, uint64_t se
     a.park = c->park;
     a.chunk = (uint32_t)c->chunk;
     a.lanes = 64;
+    a.group = 1;
     a.cnt = c->counters.as<dwos::Counters>();
     a.tot = c->totals.as<dwos::Counters>();
     a.rec_u = c->rec_u.as<T>();

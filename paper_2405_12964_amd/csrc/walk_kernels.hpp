@@ -101,7 +101,8 @@ struct WalkArgs {
     unsigned long long* queue;
     int32_t park;            // lanes answered before a wavefront takes its step (1..64)
     uint32_t chunk;          // walk ids taken per wavefront refill (at least `lanes`)
-    int32_t lanes;           // lanes of each wavefront that take walks (1..64)
+    int32_t lanes;           // walks of each wavefront (1..64)
+    int32_t group;           // lanes per walk: 1, 2 or 4 (lanes * group <= 64)
     int32_t stack_lds;       // traversal-stack entries of a lane kept in LDS ...
     uint32_t stack_off;      // ... from this byte of the block's dynamic LDS on
     Counters* cnt;           // this call
@@ -348,6 +349,25 @@ __device__ __forceinline__ void scene_node(const Scene<T>& s, const StageView<ST
     load_node<T, D>(s.nodes, i, nd);
 }
 
+// Box, slab and references of one child of a 2D node, the child's into lo0 ... t0
+template <int STAGE>
+__device__ __forceinline__ void scene_child(const Scene<float>& s, const StageView<STAGE>& v, int32_t i, bool second,
+                                            NodeData<float, 2>& nd) {
+    auto take = [&](const float4* q) {
+        const float4 a = q[second], c = q[2 + second], e = q[4];
+        nd.lo0[0] = a.x; nd.lo0[1] = a.y; nd.hi0[0] = a.z; nd.hi0[1] = a.w;
+        nd.n0[0] = c.x; nd.n0[1] = c.y; nd.o0 = c.z; nd.t0 = c.w;
+        nd.c0 = __float_as_int(e.x); nd.c1 = __float_as_int(e.y);
+    };
+    if constexpr (STAGE > 0) {
+        if (STAGE == 2 || i < v.n_lnodes) {
+            take(g_stage + i * (node_scalars(2) / 4));
+            return;
+        }
+    }
+    take(reinterpret_cast<const float4*>(s.nodes + (size_t)i * node_scalars(2)));
+}
+
 template <class T, int D, int STAGE>
 __device__ __forceinline__ void scene_prim(const Scene<T>& s, const StageView<STAGE>& v, int32_t i, T* P) {
     if constexpr (sizeof(T) == 4 && STAGE > 0) {
@@ -487,6 +507,22 @@ __device__ __forceinline__ void query_test_prim(const Scene<T>& s, const T* P, c
     }
 }
 
+// v of the lane that the permutation CTRL of four lanes names
+template <int CTRL>
+__device__ __forceinline__ float lane_swap(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// The better of this lane's answer and that lane's
+template <int CTRL, int D>
+__device__ __forceinline__ void query_merge(const Scene<float>& s, Query<float, D>& q) {
+    const float d = lane_swap<CTRL>(q.best);
+    const int32_t leaf = __builtin_amdgcn_mov_dpp(q.bleaf, CTRL, 0xf, 0xf, true);
+    bool take = d < q.best;
+    if (d == q.best && leaf != q.bleaf) take = q.bleaf < 0 || (leaf >= 0 && s.orig[leaf] < s.orig[q.bleaf]);
+    if (take) { q.best = d; q.bleaf = leaf; }
+}
+
 template <class T, int D, int STAGE, class Stack>
 __device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView<STAGE>& sv, int32_t root,
                                             const T* x, int32_t warm, Query<T, D>& q, Stack& st) {
@@ -510,6 +546,11 @@ __device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView<S
 // descending lanes keep their position and go on in the next round.  A round
 // in which no lane holds a leaf always expands at least one node per
 // descending lane, so every query progresses.
+// With GROUP (FP32), `group` lanes share a walk: they hold the same query and
+// descend together, a lane computing the distance to one child (2D) and testing
+// every group-th primitive of a leaf, and exchange the distances and the least
+// (distance, original index).  That is the answer of the tests in turn: equal
+// distances go to the lowest index in any order.
 // Measured on the 200,000-triangle icosphere (65536 points x 1024 walks):
 // a tail of 8 lanes cuts the forward launch from 150 to 124 ms and the
 // differential launch from 171 to 141 ms (tails of 4 to 24 lanes give
@@ -519,9 +560,9 @@ __device__ __forceinline__ void query_begin(const Scene<T>& s, const StageView<S
 #define DWOS_DESCEND_TAIL 8
 #endif
 constexpr int kDescendTail = DWOS_DESCEND_TAIL;
-template <class T, int D, int STAGE, class Stack>
+template <class T, int D, bool GROUP = false, int STAGE, class Stack>
 __device__ __forceinline__ void query_round(const Scene<T>& s, const StageView<STAGE>& sv, const T* x,
-                                            Query<T, D>& q, QueryCount& qc, Stack& st, int tail) {
+                                            Query<T, D>& q, QueryCount& qc, Stack& st, int tail, int group = 1) {
     using Q = Query<T, D>;
     const T lim = q.best * Slack<T>::v;
     // phase 1: expand nodes until this lane holds a leaf or is finished
@@ -538,10 +579,20 @@ __device__ __forceinline__ void query_round(const Scene<T>& s, const StageView<S
         }
         if (q.cur >= 0) {
             NodeData<T, D> nd;
-            scene_node<T, D>(s, sv, q.cur, nd);
+            T d0, d1;
             qc.nodes++;
-            const T d0 = fmax(box_d2<T, D>(nd.lo0, nd.hi0, x), slab_d2<T, D>(nd.n0, nd.o0, nd.t0, x));
-            const T d1 = fmax(box_d2<T, D>(nd.lo1, nd.hi1, x), slab_d2<T, D>(nd.n1, nd.o1, nd.t1, x));
+            if constexpr (GROUP && D == 2) {
+                const bool odd = threadIdx.x & 1;
+                scene_child(s, sv, q.cur, odd, nd);       // into child 0's fields
+                const T own = fmax(box_d2<T, D>(nd.lo0, nd.hi0, x), slab_d2<T, D>(nd.n0, nd.o0, nd.t0, x));
+                const T other = lane_swap<0xB1>(own);
+                d0 = odd ? other : own;
+                d1 = odd ? own : other;
+            } else {
+                scene_node<T, D>(s, sv, q.cur, nd);
+                d0 = fmax(box_d2<T, D>(nd.lo0, nd.hi0, x), slab_d2<T, D>(nd.n0, nd.o0, nd.t0, x));
+                d1 = fmax(box_d2<T, D>(nd.lo1, nd.hi1, x), slab_d2<T, D>(nd.n1, nd.o1, nd.t1, x));
+            }
             const bool h0 = d0 <= lim, h1 = d1 <= lim, near0 = d0 <= d1;
             const bool both = h0 && h1;
             const bool first = (both && near0) || (h0 && !h1);   // child 0 is next
@@ -557,22 +608,27 @@ __device__ __forceinline__ void query_round(const Scene<T>& s, const StageView<S
         const int32_t v = -1 - q.cur;
         const int32_t start = v >> 3, n = (v & 7) + 1;
         qc.prims += n;
+        const int32_t mine = start + (int32_t)(threadIdx.x & (unsigned)(group - 1));
         if constexpr (D == 3) {   // the next primitive is loaded while one is tested
             T P[9];
-            scene_prim<T, D>(s, sv, start, P);
-            for (int32_t i = start; i < start + n; ++i) {
+            scene_prim<T, D>(s, sv, mine < start + n ? mine : start, P);
+            for (int32_t i = mine; i < start + n; i += group) {
                 T N[9];
-                scene_prim<T, D>(s, sv, i + 1 < start + n ? i + 1 : i, N);
+                scene_prim<T, D>(s, sv, i + group < start + n ? i + group : i, N);
                 query_test_prim<T, D, STAGE>(s, P, x, i, q);
 #pragma unroll
                 for (int k = 0; k < 9; ++k) P[k] = N[k];
             }
         } else {
-            for (int32_t i = start; i < start + n; ++i) {
+            for (int32_t i = mine; i < start + n; i += group) {
                 T P[4];
                 scene_prim<T, D>(s, sv, i, P);
                 query_test_prim<T, D, STAGE>(s, P, x, i, q);
             }
+        }
+        if constexpr (GROUP) {
+            query_merge<0xB1>(s, q);                   // lane ^ 1
+            if (group > 2) query_merge<0x4E>(s, q);    // lane ^ 2
         }
         q.cur = Q::kPop;
     }
@@ -715,12 +771,13 @@ __device__ __forceinline__ WalkPool first_pool(const WalkArgs<T>& a) {
     return q;
 }
 
-// A walk id for every lane of `mask` (at least a.total: none left).
+// A walk id for every group of lanes in `mask` (at least a.total: none left).
 template <class T>
 __device__ __forceinline__ unsigned long long take_walks(const WalkArgs<T>& a, WalkPool& q,
-                                                         unsigned long long mask, int lane) {
+                                                         unsigned long long mask, int lane, int group = 1) {
+    if (group > 1) mask &= group == 2 ? 0x5555555555555555ull : 0x1111111111111111ull;   // their first lanes
     const int n = __popcll(mask);
-    const int rank = __popcll(mask & ((1ull << lane) - 1ull));
+    const int rank = __popcll(mask & ((1ull << (lane & -group)) - 1ull));
     const unsigned long long avail = q.end - q.next;
     unsigned long long id;
     if (avail >= (unsigned long long)n) {
@@ -813,7 +870,8 @@ struct WalkWaves {
 // CV: the build with the control variate's bookkeeping (MODE >= 1 with
 // a.cv_run set); without it the kernel carries none of that state.
 // STAGE: see StageView.
-template <class T, int D, int MODE, int STAGE, bool CV = false>
+// GROUP: the build for launches of few walks, with a.group lanes per walk.
+template <class T, int D, int MODE, int STAGE, bool CV = false, bool GROUP = false>
 __global__ void __launch_bounds__(STAGE ? kBlockStaged : kBlock) __attribute__((amdgpu_waves_per_eu(WalkWaves<T, D, MODE, STAGE>::v)))
 walk_kernel(WalkArgs<T> a) {
     const int lane = threadIdx.x & 63;
@@ -843,7 +901,9 @@ walk_kernel(WalkArgs<T> a) {
         key1 = (uint32_t)(sd >> 32);
     }
     WalkPool pool = first_pool(a);
-    bool done = lane >= a.lanes;
+    const int group = GROUP ? a.group : 1;
+    const bool lead = !GROUP || (lane & (group - 1)) == 0;   // of the lanes that share a walk
+    bool done = lane >= a.lanes * group;
     int64_t wid = -1;          // logical walk id (relative to wid_offset)
     // walk state
     T x[D], xoff[D];
@@ -874,6 +934,7 @@ walk_kernel(WalkArgs<T> a) {
     // rare: each goes to the device totals when it happens)
     uint32_t c_walks = 0, c_nested = 0, c_steps = 0, c_term = 0, c_nodes = 0, c_prims = 0;
     auto count_rare = [&](unsigned long long Counters::*field, unsigned long long v) {
+        if (!lead) return;
         atomicAdd(&(a.cnt->*field), v);
         atomicAdd(&(a.tot->*field), v);
     };
@@ -883,7 +944,7 @@ walk_kernel(WalkArgs<T> a) {
         const bool need = (wid < 0) && !done;
         const unsigned long long mask = __ballot(need);
         if (mask) {
-            const unsigned long long myid = take_walks(a, pool, mask, lane);
+            const unsigned long long myid = take_walks(a, pool, mask, lane, group);
             if (need) {
                 if (myid >= (unsigned long long)a.total) {
                     done = true;
@@ -953,13 +1014,13 @@ walk_kernel(WalkArgs<T> a) {
             while (true) {
                 const unsigned long long sm = __ballot(!q.done());
                 if (sm == 0ull || present - __popcll(sm) >= park) break;
-                query_round<T, D>(a.s, sv, x, q, qc, stack, tail);
+                query_round<T, D, GROUP>(a.s, sv, x, q, qc, stack, tail, group);
             }
             c_nodes += qc.nodes; c_prims += qc.prims;
             if (qc.overflow) count_rare(&Counters::overflow, qc.overflow);
             if ((c_nodes | c_prims | c_steps) >= 0x80000000u) {   // rare: move to the totals
                 Counters* dst[2] = {a.cnt, a.tot};
-                for (int t = 0; t < 2; ++t) {
+                for (int t = 0; t < 2 && lead; ++t) {
                     atomicAdd(&dst[t]->nodes, (unsigned long long)c_nodes);
                     atomicAdd(&dst[t]->prims, (unsigned long long)c_prims);
                     atomicAdd(&dst[t]->steps, (unsigned long long)c_steps);
@@ -1214,6 +1275,7 @@ walk_kernel(WalkArgs<T> a) {
             }
         }
     }
+    if (!lead) c_walks = c_nested = c_steps = c_term = c_nodes = c_prims = 0;
     add_counts(a, lane, c_walks, c_nested, c_steps, c_term, c_nodes, c_prims);
 }
 
