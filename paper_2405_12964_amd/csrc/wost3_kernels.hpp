@@ -362,11 +362,14 @@ template <> struct BaryTol<float> { static constexpr float v = 1e-6f; };
 template <> struct BaryTol<double> { static constexpr double v = 1e-13; };
 
 // First reflecting triangle (leaf position) entered from its domain side by
-// x + t dir, 0 <= t < tmax, skipping leaf `skip`; -1 if none.  t_out: its t,
-// or tmax.  Equal t go to the lowest original index.
+// x + t dir, 0 <= t < tmax, skipping leaf `skip`; -1 if none (also for a
+// negative tmax or one that is not a number).  t_out: its t, or tmax.  Equal t
+// go to the lowest original index.
 template <class T, class Stack>
 __device__ int32_t ray3_first(const RefScene3<T>& r, const T* x, const T* dir, T tmax, int32_t skip, T& t_out,
                               QueryCount& qc, Stack& st, int tail = 0) {
+    t_out = tmax;
+    if (!(tmax >= T(0))) return -1;
     T inv[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) inv[k] = dir[k] != T(0) ? T(1) / dir[k] : T(0);

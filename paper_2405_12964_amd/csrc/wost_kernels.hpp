@@ -306,7 +306,10 @@ struct SilQuery {
 
 template <class T, class Stack>
 __device__ __forceinline__ void sil_begin(SilQuery<T>& q, T best, int32_t bsil, Stack& st) {
-    q.cur = 0;   // the root pair node
+    // the root pair node; answered at once when nothing is nearer than the
+    // bound (a pop relies on a bound above the last entry's -1, so a bound
+    // that is not a number must not start a traversal)
+    q.cur = best > T(0) ? 0 : SilQuery<T>::kDone;
     unsigned none = 0;
     st.put(0, SilQuery<T>::kDone, T(-1), none);
     q.sp = 1;
@@ -440,10 +443,14 @@ __device__ __forceinline__ T ray_child(const T* lo, const T* hi, const T* n, T o
 
 // First reflecting segment (leaf position) entered from its domain side
 // (its left) by x + t dir with 0 <= t < tmax, skipping leaf `skip`; -1 if
-// none.  t_out: its t, or tmax.  Equal t go to the lowest original index.
+// none (also for a negative tmax or one that is not a number, which the pops
+// below must not meet).  t_out: its t, or tmax.  Equal t go to the lowest
+// original index.
 template <class T, class Stack>
 __device__ int32_t ray_first(const RefScene<T>& r, const T* x, const T* dir, T tmax, int32_t skip, T& t_out,
                              QueryCount& qc, Stack& st, int tail = 0) {
+    t_out = tmax;
+    if (!(tmax >= T(0))) return -1;
     T inv[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) inv[k] = dir[k] != T(0) ? T(1) / dir[k] : T(0);
