@@ -919,9 +919,12 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
 
 // Walk on stars: traversal-stack entries of a lane in LDS (8 bytes each, 2 KB
 // per entry and block), within the 40 KB of a block that leave four blocks per
-// CU.  2D: 10 entries and 32 staged reflecting nodes 144.8 ms per thermal step,
-// 8 and 64 149 ms, 6 and 128 (three blocks per CU) 166 ms; 3D: 8 entries
-// 420-440 ms, 6 447 ms.
+// CU, whatever the boundaries' sizes.  2D: 10 entries and 32 staged reflecting
+// nodes 144.8 ms per thermal step, 8 and 64 149 ms, 6 and 128 (three blocks per
+// CU) 166 ms; 3D: 8 entries 420-440 ms, 6 447 ms.  With the 2D Dirichlet tree
+// staged beyond the 40 KB (up to 256 nodes and 16 KB of primitives), 65,536
+// walks took at 804 / 1,004 / 1,284 / 4,004 segments 25.9 / 35.9 / 26.7 / 31.4
+// ms at three, two, three and three blocks per CU; now 22.9 / 24.7 / 25.0 / 28.7.
 constexpr int kStarStack2 = 10, kStarStack3 = 8, kStarRefNodes = 32;
 
 // Launch the persistent walk-on-stars kernel (2D, reflecting boundary).
@@ -936,12 +939,16 @@ dwos_status launch_wost(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
     dwos::RefScene<T> ref = make_ref<T>(c);
     size_t lds = 0;
     if constexpr (sizeof(T) == 4) {
-        // LDS per block (a few blocks per CU): up to 256 Dirichlet nodes, its
-        // primitives up to 16 KB, the reflecting BVH's first nodes, the stacks
-        a.s.n_stage_nodes = (int32_t)std::min<int64_t>(c->n_nodes, 256);
-        a.s.stage_prims = c->np * (int64_t)(dwos::prim_scalars(2) * sizeof(T)) <= 16384 ? 1 : 0;
+        // LDS per block: the stacks, the reflecting BVH's first nodes with their
+        // cones and, in what is left of the 40 KB, the Dirichlet BVH with its
+        // primitives if both fit, else its first nodes
         ref.n_stage = (int32_t)std::min<int64_t>(c->ref_nn, kStarRefNodes);
         const int64_t w_nodes = dwos::node_scalars(2) / 4;
+        const int64_t left4 = (40 * 1024 - (int64_t)kStarStack2 * block * (int64_t)sizeof(dwos::StackEntry<T>)) / 16 -
+                              ref.n_stage * (w_nodes + 2 * dwos::kRefCone / 4);
+        a.s.stage_prims = c->n_nodes * w_nodes + c->np <= left4 ? 1 : 0;
+        a.s.n_stage_nodes = (int32_t)std::min<int64_t>(c->n_nodes, left4 / w_nodes);
+        if (c->stage_cap >= 0) a.s.n_stage_nodes = std::min<int32_t>(a.s.n_stage_nodes, c->stage_cap);
         ref.stage_off4 = (int64_t)a.s.n_stage_nodes * w_nodes + (a.s.stage_prims ? c->np : 0);
         lds = (size_t)(ref.stage_off4 + (int64_t)ref.n_stage * (w_nodes + 2 * dwos::kRefCone / 4)) * 16;
         a.stack_lds = kStarStack2;
