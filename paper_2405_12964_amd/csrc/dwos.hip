@@ -870,7 +870,8 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     const size_t room = STAGE ? (c->max_smem - 512 - staged) / (block * entry) : kMaxStack * 8 / entry;
     a.stack_off = (uint32_t)staged;
     a.stack_lds = (int32_t)std::min<size_t>(kMaxStack, room);
-    const size_t smem = staged + (size_t)a.stack_lds * block * entry;
+    a.count_off = a.stack_off + (uint32_t)((size_t)a.stack_lds * block * entry);
+    const size_t smem = a.count_off + dwos::kCountBytes;
     // FP32 launches of few walks give each walk two or four of the lanes that
     // would idle: they share its leaf tests, a wavefront's longest loop when few
     // lanes of it work.  Without / with, us: 128-gon probe, 32,768 walks, 474 /
@@ -944,7 +945,8 @@ dwos_status launch_wost(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         // primitives if both fit, else its first nodes
         ref.n_stage = (int32_t)std::min<int64_t>(c->ref_nn, kStarRefNodes);
         const int64_t w_nodes = dwos::node_scalars(2) / 4;
-        const int64_t left4 = (40 * 1024 - (int64_t)kStarStack2 * block * (int64_t)sizeof(dwos::StackEntry<T>)) / 16 -
+        const int64_t left4 = (40 * 1024 - dwos::kCountBytes -
+                               (int64_t)kStarStack2 * block * (int64_t)sizeof(dwos::StackEntry<T>)) / 16 -
                               ref.n_stage * (w_nodes + 2 * dwos::kRefCone / 4);
         a.s.stage_prims = c->n_nodes * w_nodes + c->np <= left4 ? 1 : 0;
         a.s.n_stage_nodes = (int32_t)std::min<int64_t>(c->n_nodes, left4 / w_nodes);
@@ -960,7 +962,8 @@ dwos_status launch_wost(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         ref.stage_off4 = 0;
     }
     a.stack_off = (uint32_t)lds;
-    lds += (size_t)a.stack_lds * block * sizeof(dwos::StackEntry<T>);
+    a.count_off = a.stack_off + (uint32_t)((size_t)a.stack_lds * block * sizeof(dwos::StackEntry<T>));
+    lds = a.count_off + dwos::kCountBytes;
     static size_t occ_lds = ~size_t(0);
     static int occ_per_cu = 1;
     if (occ_lds != lds) {
@@ -1019,7 +1022,7 @@ dwos_status launch_wost3(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         lds = (size_t)a.s.n_stage_nodes * dwos::node_scalars(3) * sizeof(T) +
               (a.s.stage_prims ? (size_t)c->np * dwos::prim_scalars(3) * sizeof(T) : 0);
         const size_t per_edge = (size_t)(dwos::node_scalars(3) + 2 * dwos::kEdgeCone) * sizeof(T);
-        const size_t budget = 40 * 1024 - (size_t)kStarStack3 * block * sizeof(dwos::StackEntry<float>);
+        const size_t budget = 40 * 1024 - dwos::kCountBytes - (size_t)kStarStack3 * block * sizeof(dwos::StackEntry<float>);
         lds = (lds + 15) & ~size_t(15);
         ref.n_estage = lds < budget ? (int32_t)std::min<int64_t>(c->ref_enn, (int64_t)((budget - lds) / per_edge)) : 0;
         if (c->stage_cap >= 0) ref.n_estage = std::min<int32_t>(ref.n_estage, c->stage_cap);
@@ -1032,7 +1035,8 @@ dwos_status launch_wost3(dwos_ctx* c, dwos::WalkArgs<T>& a0) {
         a.stack_lds = kStarStack3 / 2;
     }
     a.stack_off = (uint32_t)lds;
-    lds += (size_t)a.stack_lds * block * sizeof(dwos::StackEntry<T>);
+    a.count_off = a.stack_off + (uint32_t)((size_t)a.stack_lds * block * sizeof(dwos::StackEntry<T>));
+    lds = a.count_off + dwos::kCountBytes;
     static size_t occ_lds = ~size_t(0);
     static int occ_per_cu = 1;
     if (occ_lds != lds) {
@@ -1594,7 +1598,9 @@ dwos_status launch_imp(dwos_ctx* c, dwos::WalkArgs<T>& a) {
     hipLaunchKernelGGL(dwos::fill_u64_kernel, dim3(1), dim3(64), 0, s, a.queue, (int64_t)1);
     constexpr int block = dwos::kBlock;
     auto kern = dwos::implicit_kernel<T, MODE>;
-    const size_t lds = (size_t)std::max<int64_t>(c->imp_n, dwos::kImpRegs) * 3 * sizeof(T);
+    size_t lds = (size_t)std::max<int64_t>(c->imp_n, dwos::kImpRegs) * 3 * sizeof(T);
+    a.count_off = (uint32_t)((lds + 15) & ~size_t(15));
+    lds = a.count_off + dwos::kCountBytes;
     int per = 0;
     HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, block, lds));
     per = std::max(1, per);

@@ -173,6 +173,7 @@ template <class T, int MODE>
 __global__ void __launch_bounds__(kBlock) implicit_kernel(WalkArgs<T> a, ImpArgs<T> im) {
     constexpr int D = 2;
     T* smono = reinterpret_cast<T*>(g_stage);
+    begin_counts(a.count_off);
     const int npad = im.n < kImpRegs ? kImpRegs : im.n;   // zero scales past n
     for (int i = threadIdx.x; i < 3 * npad; i += blockDim.x) smono[i] = i < 3 * im.n ? im.mono[i] : T(0);
     __syncthreads();
@@ -327,20 +328,11 @@ __global__ void __launch_bounds__(kBlock) implicit_kernel(WalkArgs<T> a, ImpArgs
             }
         }
     }
-    c_walks = wave_sum_u64(c_walks);
-    c_nested = wave_sum_u64(c_nested);
-    c_steps = wave_sum_u64(c_steps);
-    c_term = wave_sum_u64(c_term);
+    add_counts(a, lane, c_walks, c_nested, c_steps, c_term, 0ull, 0ull);
     c_trunc = wave_sum_u64(c_trunc);
     c_invalid = wave_sum_u64(c_invalid);
     if (lane == 0) {
-        Counters* dst[2] = {a.cnt, a.tot};
-        for (int q = 0; q < 2; ++q) {
-            Counters* cc = dst[q];
-            atomicAdd(&cc->walks, c_walks);
-            atomicAdd(&cc->nested, c_nested);
-            atomicAdd(&cc->steps, c_steps);
-            atomicAdd(&cc->terminal, c_term);
+        for (Counters* cc : {a.cnt, a.tot}) {
             if (c_trunc) atomicAdd(&cc->truncated, c_trunc);
             if (c_invalid) atomicAdd(&cc->invalid, c_invalid);
         }

@@ -560,6 +560,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
     StackSpill<T> spill;
     LaneStack<T> stack(a.stack_lds, a.stack_off, spill);
     StageView<sizeof(T) == 4 ? 1 : 0> sv{0, -1};
+    begin_counts(a.count_off);
     if constexpr (sizeof(T) == 4) {
         // LDS: the Dirichlet BVH's first nodes (and its primitives when they fit)
         const int64_t nn4 = (int64_t)a.s.n_stage_nodes * (node_scalars(D) / 4);
@@ -579,10 +580,10 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
             for (int64_t i = threadIdx.x; i < en4; i += blockDim.x) g_stage[ref.estage_off4 + i] = ge[i];
             for (int64_t i = threadIdx.x; i < ec4; i += blockDim.x) g_stage[ref.estage_off4 + en4 + i] = gc[i];
         }
-        __syncthreads();
         sv.n_lnodes = a.s.n_stage_nodes;
         sv.prim_off4 = a.s.stage_prims ? nn4 : -1;
     }
+    __syncthreads();
     uint32_t key0 = a.key0, key1 = a.key1;
     if (a.seed_ptr) {
         const unsigned long long sd = *a.seed_ptr + (((unsigned long long)a.key1 << 32) | a.key0);

@@ -579,6 +579,7 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
     StackSpill<T> spill;
     LaneStack<T> stack(a.stack_lds, a.stack_off, spill);
     StageView<sizeof(T) == 4 ? 1 : 0> sv{0, -1};
+    begin_counts(a.count_off);
     if constexpr (sizeof(T) == 4) {
         // LDS: the Dirichlet BVH's first nodes (and its primitives when they
         // fit), then the reflecting BVH's top nodes and their cones
@@ -596,10 +597,10 @@ wost_kernel(WalkArgs<T> a, RefScene<T> ref, const int32_t* start_seg) {
         const float4* rc = reinterpret_cast<const float4*>(ref.cones);
         for (int64_t i = threadIdx.x; i < (2 * kRefCone / 4) * (int64_t)ref.n_stage; i += blockDim.x)
             g_stage[ref.stage_off4 + rn4 + i] = rc[i];
-        __syncthreads();
         sv.n_lnodes = a.s.n_stage_nodes;
         sv.prim_off4 = a.s.stage_prims ? nn4 : -1;
     }
+    __syncthreads();
     uint32_t key0 = a.key0, key1 = a.key1;
     if (a.seed_ptr) {
         const unsigned long long sd = *a.seed_ptr + (((unsigned long long)a.key1 << 32) | a.key0);
