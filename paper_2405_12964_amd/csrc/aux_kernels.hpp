@@ -643,6 +643,57 @@ __global__ void __launch_bounds__(256) first_query_wave_kernel(FirstArgs<float> 
     }
 }
 
+// Queries that start from a primitive, in two launches: a lane per point for
+// kWarmNodes nodes, which is all that a point needs whose last answer still is
+// the closest; then a wavefront per point for those still open, points far from
+// many primitives alike.  leaf_out of an open one is open_mark of the best leaf so
+// far (or -1).
+constexpr uint32_t kWarmNodes = 16;
+__device__ __forceinline__ int32_t open_mark(int32_t leaf) { return -3 - leaf; }
+
+template <int D>
+__global__ void __launch_bounds__(64) first_query_warm_kernel(FirstArgs<float> a) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= a.P) return;
+    int32_t root, warm;
+    first_start(a, r, root, warm);
+    float x[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) x[c] = float(a.X[r * D + c]);
+    PrivateStack<float> stack;
+    QueryCount qc{0, 0, 0};
+    Query<float, D> q;
+    query_begin<float, D>(a.s, StageView<0>{0, -1}, root, x, warm, q, stack);
+#pragma unroll 1
+    while (!q.done() && qc.nodes < kWarmNodes)
+        query_round<float, D>(a.s, StageView<0>{0, -1}, x, q, qc, stack, a.s.tail);
+    a.leaf_out[r] = q.done() ? q.bleaf : open_mark(q.bleaf);
+    a.d2_out[r] = q.best;
+}
+
+// `per` points (1..64) for a wavefront to look through
+template <int D>
+__global__ void __launch_bounds__(256) first_query_open_kernel(FirstArgs<float> a, int per) {
+    __shared__ float2 st[4][kWaveStack];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t r0 = ((int64_t)blockIdx.x * 4 + w) * per;
+    const int32_t mark = lane < per && r0 + lane < a.P ? a.leaf_out[r0 + lane] : 0;
+    for (unsigned long long open = __ballot(mark < -1); open; open &= open - 1) {
+        const int l = __ffsll(open) - 1;
+        const int64_t r = r0 + l;
+        int32_t root, warm;
+        first_start(a, r, root, warm);
+        float x[D], d2;
+#pragma unroll
+        for (int c = 0; c < D; ++c) x[c] = float(a.X[r * D + c]);
+        const int32_t leaf = wave_closest<D>(a.s, root, x, open_mark(__shfl(mark, l)), st[w], d2);
+        if (lane == 0) {
+            a.leaf_out[r] = leaf;
+            a.d2_out[r] = d2;
+        }
+    }
+}
+
 template <class T, int D>
 __global__ void ball_kernel_eval(const double* r, const double* R, int64_t n, T kappa, double* GB,
                                  double* alpha) {

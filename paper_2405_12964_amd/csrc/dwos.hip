@@ -789,22 +789,47 @@ void launch_refit(dwos_ctx* c) {
 
 // Closest-point queries of a list of points, in FP32 by a wavefront per point up
 // to the count where a lane per point fills the chip as well and does less work
-// in all.  Without starting primitives, us by wavefront / by lane, at 4,096,
-// 65,536 and 262,144 points: 200,000 triangles, points in the volume 114 / 2044,
-// 535 / 2476, 2032 / 4026, on the box around 26 / 1461, 123 / 1927, 434 / 2233;
-// 8,000 triangles, volume 53 / 400, 257 / 496, 969 / 606; 4,096 segments 41 /
-// 169, 261 / 192, 1027 / 232 (16,384: 88 / 169).  From the primitives of a
-// previous query, 65,536 points: 312 / 1474, 86 / 16, 209 / 286, 126 / 94.
+// in all; small trees are a lane's work sooner.  Without starting primitives, us
+// by wavefront / by lane, at 4,096, 65,536 and 262,144 points: 200,000 triangles,
+// points in the volume 114 / 2044, 535 / 2476, 2032 / 4026, on the box around 26 /
+// 1461, 123 / 1927, 434 / 2233; 8,000 triangles, volume 53 / 400, 257 / 496, 969 /
+// 606; 4,096 segments 41 / 169, 261 / 192, 1027 / 232 (16,384: 88 / 169); 332
+// triangles, box, 8,192 points 20 / 77, 65,536: 109 / 71; 32 triangles, 8,192
+// points 24 / 31, 65,536: 127 / 34; 24 segments, 4,096 points 9 / 14, 16,384: 19 /
+// 14; 128 segments, 16,384: 27 / 34.
+// From the primitives of a previous query a lane has next to nothing to do where
+// they still are the closest, and as much as without where many are as far: by
+// wavefront / by lane / a lane first and a wavefront for what is left, 65,536
+// points on the box around 200,000 triangles 83 / 16 / 17, in the volume 231 /
+// 1448 / 288; 16,384 points 25 / 14 / 17 and 77 / 1194 / 134; 8,192 points 14 / 14
+// and 52 / 1151.
 constexpr int64_t kWavePoints2 = 16384, kWavePoints3 = 65536;
-template <class T, int D>
-bool wave_per_point(int64_t P) { return sizeof(T) == 4 && P <= (D == 2 ? kWavePoints2 : kWavePoints3); }
+constexpr int64_t kWavePerPrim2 = 256, kWavePerPrim3 = 128;
+constexpr int64_t kWarmWavePoints = 16384;
+constexpr int64_t kOpenWaves = 32768;     // wavefronts that look for points left open
+template <int D>
+bool wave_per_point(int64_t P, int64_t n_prims) {
+    return P <= (D == 2 ? std::min(kWavePoints2, kWavePerPrim2 * n_prims)
+                        : std::min(kWavePoints3, kWavePerPrim3 * n_prims));
+}
 
 template <class T, int D>
 void launch_first(hipStream_t s, const dwos::FirstArgs<T>& a) {
     if constexpr (sizeof(T) == 4) {
-        if (wave_per_point<T, D>(a.P)) {
+        if (a.warm_in ? a.P <= kWarmWavePoints : wave_per_point<D>(a.P, a.s.n_prims)) {
             hipLaunchKernelGGL((dwos::first_query_wave_kernel<D>), dim3(blocks_for(a.P, 4)), dim3(256), 0, s, a);
             return;
+        }
+        if constexpr (D == 3) {
+            if (a.warm_in && a.P <= kWavePoints3) {
+                const int per = (int)((a.P + kOpenWaves - 1) / kOpenWaves);
+                dwos::FirstArgs<T> rest = a;
+                rest.warm_in = nullptr;     // (leaf_out by now)
+                hipLaunchKernelGGL((dwos::first_query_warm_kernel<D>), dim3(blocks_for(a.P, 64)), dim3(64), 0, s, a);
+                hipLaunchKernelGGL((dwos::first_query_open_kernel<D>), dim3(blocks_for(a.P, 4 * per)), dim3(256), 0, s,
+                                   rest, per);
+                return;
+            }
         }
     }
     hipLaunchKernelGGL((dwos::first_query_kernel<T, D>), dim3(blocks_for(a.P, 64)), dim3(64), 0, s, a);
@@ -814,7 +839,7 @@ template <class T, int D>
 void launch_closest(dwos_ctx* c, const double* X, int64_t P, double* out) {
     const dwos::Scene<T> scene = make_scene<T>(c);
     if constexpr (sizeof(T) == 4) {
-        if (wave_per_point<T, D>(P)) {
+        if (wave_per_point<D>(P, c->np)) {
             hipLaunchKernelGGL((dwos::closest_wave_kernel<D>), dim3(blocks_for(P, 4)), dim3(256), 0, c->stream, scene,
                                0, X, P, out);
             return;

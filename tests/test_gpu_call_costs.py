@@ -90,3 +90,23 @@ def test_statistics_add_up(kind):
         assert (st["nodes"] > 0) == (kind != "implicit")
         total = s.walk_timing(0)[-1]
         assert total["walks"] == 2 * P * W and total["steps"] == 2 * st["steps"]
+
+
+def test_repeated_first_queries():
+    """65,536 one-step walks again from the same points around 200,000 triangles:
+    109 us, the first queries 17 of them (83 by a wavefront per point, 678 in all
+    with the statistics by wavefront)."""
+    from paper_2405_12964_amd import Solver
+    s = Solver.from_scene(scenes.c3_icosphere(nu=100, n_basis=64, h=0.4).with_(eps=1e3, delta=1e2), "fp32")
+    X = torch.as_tensor(scenes.points_on_box_faces(65536, 3), device="cuda").contiguous()
+    assert best_us(lambda: s.solve(X, 1, 3, var=False)) < 165
+
+
+def test_queries_of_a_small_tree():
+    """65,536 points and 32 triangles: a lane per point, 34 us (127 by a wavefront)."""
+    from paper_2405_12964_amd import Solver
+    V, prims = scenes.icosphere(1)
+    s = Solver(3)
+    s.set_boundary(V, prims)
+    X = torch.as_tensor(np.random.default_rng(1).uniform(-1.9, 1.9, (65536, 3)), device="cuda")
+    assert best_us(lambda: s.closest(X)) < 80
