@@ -284,13 +284,18 @@ __global__ void __launch_bounds__(256) spmv_kernel(ParamCSR J, const double* A, 
 
 // ---------------------------------------------------------------------------
 // forward mode: a block per point p and group of 64 parameters.  A lane takes
-// one parameter and every (256 / lanes)-th walk; with N <= 32 parameters a
+// one parameter and every (threads / lanes)-th walk; with N <= 32 parameters a
 // wavefront takes several walks at once.  Each walk is a chain of six dependent
 // loads (record, vertices, Jacobian row and entry), so what counts is how many
 // chains are in flight: with one wavefront per point over all walks in turn,
-// 23 parameters, 512 points x 256 walks took 650 us, now 129.
+// 23 parameters, 512 points x 256 walks took 650 us, with four 129.  A point of
+// few walks gets as many threads as its walks need, one wavefront at least:
+// 65,536 points of one walk, 64 parameters, 245 us with four wavefronts, 65 with
+// one; 1,024 points x 64 walks, one parameter, 38 and 6.
+// A launch holds less than 2^32 threads, so blocks take further points in turn.
 // ---------------------------------------------------------------------------
-constexpr int kJvpThreads = 256;
+constexpr int kJvpThreads = 256;             // most threads of a block
+constexpr int64_t kJvpBlocks = 1 << 22;      // most blocks a launch
 template <class T>
 struct JvpArgs {
     Scene<T> s;
@@ -313,39 +318,43 @@ struct JvpArgs {
 template <class T, int D>
 __global__ void __launch_bounds__(kJvpThreads) jvp_kernel(JvpArgs<T> a, int lanes) {
     __shared__ double sum[2][kJvpThreads];
-    const int64_t pl = blockIdx.x;
-    const int strip = threadIdx.x / lanes, strips = kJvpThreads / lanes;   // lanes: a power of two
+    // lanes: a power of two, 64 at most
+    const int strip = threadIdx.x / lanes, strips = blockDim.x / lanes;
     const int64_t j = (int64_t)blockIdx.y * lanes + (threadIdx.x & (lanes - 1));
-    double s1 = 0.0, s2 = 0.0;
-    if (j < a.J.N) {
-        for (int m = strip; m < a.W; m += strips) {
-            const int64_t i = pl * a.W + m;
-            const int32_t code = a.rec_prim[i];
-            double v = 0.0;
-            if (code >= 0) {
-                Terminal<T, D> t;
-                terminal_term<T, D>(a.s, a.prm, a.delta, code, a.rec_b + i * (D - 1), a.rec_uoff[i], t);
-                v = udot_component<T, D>(a.J, t, (int32_t)j);
-                if (a.rec_w) v *= double(a.rec_w[i]);
+    for (int64_t pl = blockIdx.x; pl < a.P; pl += gridDim.x) {
+        double s1 = 0.0, s2 = 0.0;
+        if (j < a.J.N) {
+            for (int m = strip; m < a.W; m += strips) {
+                const int64_t i = pl * a.W + m;
+                const int32_t code = a.rec_prim[i];
+                double v = 0.0;
+                if (code >= 0) {
+                    Terminal<T, D> t;
+                    terminal_term<T, D>(a.s, a.prm, a.delta, code, a.rec_b + i * (D - 1), a.rec_uoff[i], t);
+                    v = udot_component<T, D>(a.J, t, (int32_t)j);
+                    if (a.rec_w) v *= double(a.rec_w[i]);
+                }
+                if (a.walk_udot) a.walk_udot[i * a.J.N + j] = v;
+                s1 += v;
+                s2 += v * v;
             }
-            if (a.walk_udot) a.walk_udot[i * a.J.N + j] = v;
-            s1 += v;
-            s2 += v * v;
         }
+        sum[0][threadIdx.x] = s1;
+        sum[1][threadIdx.x] = s2;
+        __syncthreads();
+        if (strip == 0 && j < a.J.N && a.udot) {
+            for (int k = 1; k < strips; ++k) {
+                s1 += sum[0][k * lanes + threadIdx.x];
+                s2 += sum[1][k * lanes + threadIdx.x];
+            }
+            const int64_t p = pl + a.p_offset;
+            const double mu = s1 / a.W;
+            a.udot[p * a.J.N + j] = mu;
+            if (a.udot_var)
+                a.udot_var[p * a.J.N + j] = a.W > 1 ? fmax(0.0, (s2 - a.W * mu * mu) / (a.W - 1)) / a.W : 0.0;
+        }
+        __syncthreads();
     }
-    sum[0][threadIdx.x] = s1;
-    sum[1][threadIdx.x] = s2;
-    __syncthreads();
-    if (strip > 0 || j >= a.J.N || !a.udot) return;
-    for (int k = 1; k < strips; ++k) {
-        s1 += sum[0][k * lanes + threadIdx.x];
-        s2 += sum[1][k * lanes + threadIdx.x];
-    }
-    const int64_t p = pl + a.p_offset;
-    const double mu = s1 / a.W;
-    a.udot[p * a.J.N + j] = mu;
-    if (a.udot_var)
-        a.udot_var[p * a.J.N + j] = a.W > 1 ? fmax(0.0, (s2 - a.W * mu * mu) / (a.W - 1)) / a.W : 0.0;
 }
 
 // ---------------------------------------------------------------------------

@@ -1522,8 +1522,10 @@ dwos_status run_op(dwos_ctx* c, Op op, const OpArgs& o, dwos_stats* st) {
             ja.walk_udot = op == Op::Records ? o.rec_udot_out + p0 * W * c->N : nullptr;
             int lanes = 1;
             while (lanes < 64 && lanes < c->N) lanes *= 2;
-            dim3 grid((unsigned)Pc, (unsigned)((c->N + lanes - 1) / lanes));
-            hipLaunchKernelGGL((dwos::jvp_kernel<T, D>), grid, dim3(dwos::kJvpThreads), 0, s, ja, lanes);
+            int threads = 64;
+            while (threads < dwos::kJvpThreads && threads < (int64_t)lanes * W) threads *= 2;
+            dim3 grid((unsigned)std::min(Pc, dwos::kJvpBlocks), (unsigned)((c->N + lanes - 1) / lanes));
+            hipLaunchKernelGGL((dwos::jvp_kernel<T, D>), grid, dim3(threads), 0, s, ja, lanes);
         }
         if (op == Op::Records) {
             hipLaunchKernelGGL(copy_records_kernel<T>, dim3(blocks_for(walks, 256)), dim3(256), 0, s,

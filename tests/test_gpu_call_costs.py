@@ -110,3 +110,15 @@ def test_queries_of_a_small_tree():
     s.set_boundary(V, prims)
     X = torch.as_tensor(np.random.default_rng(1).uniform(-1.9, 1.9, (65536, 3)), device="cuda")
     assert best_us(lambda: s.closest(X)) < 80
+
+
+def test_forward_mode_of_few_walks():
+    """65,536 points of one walk and one parameter: a wavefront per point, 173 us
+    in all (with four, three of them without a walk, the reduction alone takes
+    245 instead of 65)."""
+    from paper_2405_12964_amd import Solver
+    n = 128
+    s = Solver.from_scene(scenes.c1_polygon(n).with_(eps=1e3, delta=1e2), "fp32")
+    s.set_parameters(1, np.arange(n + 1), np.zeros(n, np.int32), np.ones((n, 2)))
+    X = torch.as_tensor(scenes.points_in_disk(65536, 0.8, 1), device="cuda").contiguous()
+    assert best_us(lambda: s.jvp(X, 1, 3)) < 260
