@@ -240,7 +240,8 @@ dwos_status dwos_jvp(dwos_ctx* ctx, const double* X, int64_t P, int32_t W, uint6
  * primitive array (in the working precision, Sec. 6 layout), [3] pair nodes
  * the FP32 walk kernel stages in LDS (the breadth-first prefix), [4] 1 if it
  * stages every primitive as well, [5] primitives, [6] vertices, [7] LDS bytes
- * per block of the staged launch.  Errors: EINVAL (NULL), ESTATE (no mesh
+ * per block of the staged launch (the tree's, the traversal stacks' and the
+ * statistics').  Errors: EINVAL (NULL), ESTATE (no mesh
  * boundary). */
 dwos_status dwos_scene_info(dwos_ctx* ctx, int64_t* info);
 

@@ -206,6 +206,15 @@ dwos::Params<T> make_params(const dwos_problem& p) {
 // kernel its occupancy (15 entries of 8 bytes are 30 KB per 256-thread block:
 // five blocks, five wavefronts per SIMD, in the CU's 160 KB).
 constexpr int kStagedStack = 5, kMaxStack = 15;
+// LDS of a block that is neither the tree's nor the stacks'
+constexpr size_t kStageRest = 512;
+
+// Entries per lane beside `staged` bytes of the tree.
+template <class T>
+int32_t staged_stack(const dwos_ctx* c, size_t staged) {
+    const size_t per = dwos::kBlockStaged * sizeof(dwos::StackEntry<T>);
+    return (int32_t)std::min<size_t>(kMaxStack, (c->max_smem - kStageRest - staged) / per);
+}
 
 template <class T>
 dwos::Scene<T> make_scene(dwos_ctx* c) {
@@ -220,8 +229,11 @@ dwos::Scene<T> make_scene(dwos_ctx* c) {
     s.n_prims = c->np;
     // LDS staging plan: the whole BVH and all primitives if they fit beside
     // the traversal stacks, else a prefix of the (breadth-first ordered) nodes
-    const size_t stacks = (size_t)kStagedStack * dwos::kBlockStaged * sizeof(dwos::StackEntry<T>);
-    const size_t budget = c->max_smem >= 1024 + stacks ? c->max_smem - 512 - stacks : 0;
+    const auto beside = [&](int entries) {
+        const size_t rest = kStageRest + (size_t)entries * dwos::kBlockStaged * sizeof(dwos::StackEntry<T>);
+        return c->max_smem > rest ? c->max_smem - rest : 0;
+    };
+    const size_t budget = beside(kStagedStack);
     const size_t nb = (size_t)dwos::node_scalars(c->D) * sizeof(T);
     const size_t pb = (size_t)dwos::prim_scalars(c->D) * sizeof(T);
     const size_t all_nodes = (size_t)c->n_nodes * nb, all_prims = (size_t)c->np * pb;
@@ -892,9 +904,8 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     constexpr int block = STAGE ? dwos::kBlockStaged : dwos::kBlock;
     constexpr size_t entry = sizeof(dwos::StackEntry<T>);
     const size_t staged = STAGE ? stage_bytes<T>(a.s, D) : 0;
-    const size_t room = STAGE ? (c->max_smem - 512 - staged) / (block * entry) : kMaxStack * 8 / entry;
     a.stack_off = (uint32_t)staged;
-    a.stack_lds = (int32_t)std::min<size_t>(kMaxStack, room);
+    a.stack_lds = STAGE ? staged_stack<T>(c, staged) : (int32_t)(kMaxStack * 8 / entry);
     a.count_off = a.stack_off + (uint32_t)((size_t)a.stack_lds * block * entry);
     const size_t smem = a.count_off + dwos::kCountBytes;
     // FP32 launches of few walks give each walk two or four of the lanes that
@@ -2537,7 +2548,9 @@ dwos_status dwos_scene_info(dwos_ctx* c, int64_t* info) {
         const dwos::Scene<float> sc = make_scene<float>(c);
         stage_nodes = sc.n_stage_nodes;
         stage_prims = sc.stage_prims;
-        lds = (int64_t)stage_bytes<float>(sc, c->D);
+        const size_t staged = stage_bytes<float>(sc, c->D);
+        lds = (int64_t)(staged + staged_stack<float>(c, staged) * dwos::kBlockStaged * sizeof(dwos::StackEntry<float>) +
+                        dwos::kCountBytes);
     }
     info[0] = c->n_nodes;
     info[1] = c->n_nodes * nb;
