@@ -201,11 +201,15 @@ dwos::Params<T> make_params(const dwos_problem& p) {
 }
 
 // Traversal-stack entries a lane keeps in LDS: beside the staged tree (block
-// of 1024 threads) at least kStagedStack (the 4096-segment star: 2.73 ms a
-// step at 5 entries, 2.81 at 3, 2.84 at 2); without it as many as leave the
-// kernel its occupancy (15 entries of 8 bytes are 30 KB per 256-thread block:
-// five blocks, five wavefronts per SIMD, in the CU's 160 KB).
-constexpr int kStagedStack = 5, kMaxStack = 15;
+// of 1024 threads) kStagedStack, or down to kFullStack where that lets the whole
+// tree in, or up to kMaxStack where there is room; without a staged tree as many
+// as leave the kernel its occupancy (15 entries of 8 bytes are 30 KB per
+// 256-thread block: five blocks, five wavefronts per SIMD, in the CU's 160 KB).
+// The 4096-segment star: 2.73 ms a step at 5 entries, 2.81 at 3, 2.84 at 2.
+// The whole tree beside fewer entries against its first nodes beside 5 and the
+// primitives in global memory: 4,300 segments (4 entries) 2.72 against 2.87 ms a
+// step, 4,600 (2 entries, the last that fit) 2.86 against 2.98.
+constexpr int kStagedStack = 5, kFullStack = 2, kMaxStack = 15;
 // LDS of a block that is neither the tree's nor the stacks'
 constexpr size_t kStageRest = 512;
 
@@ -241,7 +245,7 @@ dwos::Scene<T> make_scene(dwos_ctx* c) {
         // batches: every instance has its own tree, so no common prefix
         s.n_stage_nodes = 0;
         s.stage_prims = 0;
-    } else if (all_nodes + all_prims <= budget) {
+    } else if (all_nodes + all_prims <= beside(kFullStack)) {
         s.n_stage_nodes = (int32_t)c->n_nodes;
         s.stage_prims = 1;
     } else {
