@@ -766,8 +766,9 @@ void dwos_mesh_destroy(dwos_mesh* m);
  * stopped when the preconditioned residual norm falls below tol times its
  * starting value (or after max_iters).  Device arrays x and g are nv x dim,
  * row-major; calls are asynchronous on the stream given at creation except
- * for one small device-to-host read of a convergence flag every 16
- * iterations.
+ * for small device-to-host reads: of a convergence flag every 16 iterations,
+ * or, where every row of M fits on the device at once and the solve is one
+ * launch, of its outcome at the end.
  * ------------------------------------------------------------------------- */
 typedef struct dwos_opt dwos_opt;
 
@@ -793,6 +794,14 @@ dwos_status dwos_opt_step(dwos_opt* opt, const double* g, double* x, double lr, 
  * CG iterations used. */
 dwos_status dwos_opt_solve(dwos_opt* opt, const double* b, double* x, int32_t max_iters, double tol,
                            int32_t* iters);
+
+/* How long the blocks of a one-launch solve wait for each other (seconds,
+ * 0..3600; 10 at creation) before the solve is given up and finished by a
+ * launch per part of an iteration, to the same residual and within the same
+ * max_iters; later solves then are done that way too, until the next call of
+ * this function.  0: always that way.  Both ways give the same iterates bit
+ * for bit.  Errors: EINVAL. */
+dwos_status dwos_opt_set_wait(dwos_opt* opt, double seconds);
 
 #ifdef __cplusplus
 }

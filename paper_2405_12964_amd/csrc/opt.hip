@@ -53,6 +53,8 @@ struct dwos_opt {
     int D = 0;
     int64_t nv = 0, nnz = 0;
     bool resident = false;    // solves run as one launch of cg_resident
+    bool fits = false;        // every row fits on the device at once
+    uint64_t wait_ticks = 0;  // how long its blocks wait for each other (100 MHz clock)
     int device = 0;
     hipStream_t stream = nullptr;
     DevBuf rowptr, col, val, diag, movable;
@@ -125,14 +127,14 @@ __global__ void residual(const int64_t* rowptr, const int32_t* col, const double
     }
 }
 
-// start: rz0 = rz = (r . z); done if r is already zero
-__global__ void cg_start(const double* red, double* scal, double tol2) {
+// start: rz = (r . z), rz0 too unless a solve goes on (resume: rz0 stays what it
+// was); done if r is already zero, or small enough against the rz0 kept
+__global__ void cg_start(const double* red, double* scal, double tol2, int resume) {
     const double s = final_sum(red);
     if (threadIdx.x == 0) {
         scal[S_RZ] = s;
-        scal[S_RZ0] = s;
-        scal[S_DONE] = (s <= 0.0) ? 1.0 : 0.0;
-        (void)tol2;
+        if (!resume) scal[S_RZ0] = s;
+        scal[S_DONE] = (s <= 0.0 || (resume && s <= tol2 * scal[S_RZ0])) ? 1.0 : 0.0;
     }
 }
 
@@ -252,11 +254,11 @@ __global__ void cg_direction_beta(double* p, const double* z, int64_t nv, int D,
 // a counter as grid barrier and every wavefront writing the L2 back and
 // invalidating it: 6.9 ms).  Gathering past the L2 instead of invalidating it
 // once a block costs 0.06 ms of it more.  Launched cooperatively,
-// so that all blocks are resident; a wait gives up after kWaitTicks all the same.
+// so that all blocks are resident; a wait gives up after wait_ticks all the same.
 // ---------------------------------------------------------------------------
 constexpr int kResThreads = 512;                  // threads per block: two groups of kThreads rows
 constexpr int kGroups = kResThreads / kThreads;
-constexpr uint64_t kWaitTicks = 1000000000ull;    // 10 s of the 100 MHz clock
+constexpr double kWaitSeconds = 10.0, kTicksPerSecond = 1e8;   // wall_clock64 runs at 100 MHz
 constexpr int held_neighbours(int D) { return D == 2 ? 2 : 8; }
 
 __device__ __forceinline__ void store_agent(double* p, double v) {
@@ -294,14 +296,14 @@ __device__ __forceinline__ void publish(double s, int64_t nblk, uint32_t epoch, 
 // order: a grid barrier and its reduction in one round trip.  False for every
 // thread of the block if a partial did not come.
 __device__ __forceinline__ bool collect(const uint64_t* slots, int64_t nblk, uint32_t epoch, double* sh, double* tot,
-                                        int* late, double& sum) {
+                                        int* late, uint64_t wait_ticks, double& sum) {
     double s = 0.0;
     if (threadIdx.x < kThreads) {
         const uint64_t t0 = wall_clock64();
         for (int64_t i = threadIdx.x; i < nblk; i += kThreads) {
             uint64_t lo = load_agent(&slots[2 * i]), hi = load_agent(&slots[2 * i + 1]);
             while ((uint32_t)(lo >> 32) != epoch || (uint32_t)(hi >> 32) != epoch) {
-                if (wall_clock64() - t0 > kWaitTicks) {
+                if (wall_clock64() - t0 > wait_ticks) {
                     *late = 1;
                     break;
                 }
@@ -331,7 +333,7 @@ __global__ void __launch_bounds__(kResThreads) cg_resident(const int64_t* rowptr
                                                            const double* diag, double* x, const double* r0, double* z,
                                                            double* pex, int64_t nv, int64_t nblk, uint64_t* slots_pq,
                                                            uint64_t* slots_rz, double* scal, int max_iters,
-                                                           double tol2) {
+                                                           double tol2, uint64_t wait_ticks) {
     constexpr int NB = held_neighbours(D);
     __shared__ double sh_out[kResThreads / 64], sh_in[kResThreads / 64];
     __shared__ double tot;
@@ -394,7 +396,7 @@ __global__ void __launch_bounds__(kResThreads) cg_resident(const int64_t* rowptr
         for (int c = 0; c < D; ++c) s += pi[c] * qi[c];
         double pq, rzn;
         publish(live ? s : 0.0, nblk, it + 1, slots_pq, sh_out);
-        if (!collect(slots_pq, nblk, it + 1, sh_in, &tot, &late, pq)) break;
+        if (!collect(slots_pq, nblk, it + 1, sh_in, &tot, &late, wait_ticks, pq)) break;
         ++it;
         if (!(pq > 0.0)) break;
         // x, r, z and r . z
@@ -410,7 +412,7 @@ __global__ void __launch_bounds__(kResThreads) cg_resident(const int64_t* rowptr
             if (live) store_agent(&z[i * D + c], zi[c]);
         }
         publish(live ? s : 0.0, nblk, it, slots_rz, sh_out);
-        if (!collect(slots_rz, nblk, it, sh_in, &tot, &late, rzn)) break;
+        if (!collect(slots_rz, nblk, it, sh_in, &tot, &late, wait_ticks, rzn)) break;
         if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         __syncthreads();
         // the neighbours' z (all of a row's loads in flight together)
@@ -534,11 +536,15 @@ dwos_status cg_solve(dwos_opt* o, const double* b, double* x, int32_t max_iters,
     const double* dg = o->diag.as<double>();
     double *r = o->r.as<double>(), *z = o->z.as<double>(), *p = o->p.as<double>(), *q = o->q.as<double>();
     const double tol2 = tol * tol;
+    auto start = [&](int resume) {
+        hipLaunchKernelGGL(opt_k::residual, dim3(blocks_for(nv, kThreads)), dim3(kThreads), 0, s, rp, cl, va, dg, b, x,
+                           r, z, p, nv, D);
+        hipLaunchKernelGGL(opt_k::dot_partial, dim3(kRedBlocks), dim3(kThreads), 0, s, r, z, n, red, sc);
+        hipLaunchKernelGGL(opt_k::cg_start, dim3(1), dim3(kThreads), 0, s, red, sc, tol2, resume);
+    };
     hipLaunchKernelGGL(opt_k::fill, dim3(1), dim3(64), 0, s, sc, (int64_t)S_COUNT, 0.0);
-    hipLaunchKernelGGL(opt_k::residual, dim3(blocks_for(nv, kThreads)), dim3(kThreads), 0, s, rp, cl, va, dg, b, x,
-                       r, z, p, nv, D);
-    hipLaunchKernelGGL(opt_k::dot_partial, dim3(kRedBlocks), dim3(kThreads), 0, s, r, z, n, red, sc);
-    hipLaunchKernelGGL(opt_k::cg_start, dim3(1), dim3(kThreads), 0, s, red, sc, tol2);
+    start(0);
+    int32_t spent = 0;        // iterations of a resident solve that was given up
     if (o->resident) {
         double *pex = o->pex.as<double>(), t2 = tol2, used[2] = {0.0, 0.0};
         uint64_t* slots_pq = reinterpret_cast<uint64_t*>(red + kRedBlocks);
@@ -547,7 +553,8 @@ dwos_status cg_solve(dwos_opt* o, const double* b, double* x, int32_t max_iters,
                            0.0);
         int64_t rows = nv, nb = nblk;
         int mi = max_iters;
-        void* args[] = {&rp, &cl, &va, &dg, &x, &r, &z, &pex, &rows, &nb, &slots_pq, &slots_rz, &sc, &mi, &t2};
+        uint64_t wait = o->wait_ticks;
+        void* args[] = {&rp, &cl, &va, &dg, &x, &r, &z, &pex, &rows, &nb, &slots_pq, &slots_rz, &sc, &mi, &t2, &wait};
         if (hipLaunchCooperativeKernel(resident_kernel(D), dim3(blocks_for(nv, opt_k::kResThreads)),
                                        dim3(opt_k::kResThreads), args, 0, s) == hipSuccess) {
             HIP_OK(hipMemcpyAsync(used, sc + S_IT, sizeof(used), hipMemcpyDeviceToHost, s));
@@ -557,15 +564,17 @@ dwos_status cg_solve(dwos_opt* o, const double* b, double* x, int32_t max_iters,
                 if (iters) *iters = (int32_t)std::min<int64_t>(max_iters, seen);
                 return DWOS_OK;
             }
+            // the blocks missed each other: go on from the x they left, to the
+            // residual that was asked for, within the iterations that are left
+            spent = (int32_t)used[0];
+            start(1);
         } else {
             (void)hipGetLastError();
         }
-        // not resident after all: from the x left (a warm start like another)
-        o->resident = false;
-        return cg_solve(o, b, x, max_iters, tol, iters);
+        o->resident = false;    // until dwos_opt_set_wait
     }
     int32_t it = 0;
-    for (; it < max_iters; ++it) {
+    for (; spent + it < max_iters; ++it) {
         if (it % kCheckEvery == 0) {
             double done = 0.0;
             HIP_OK(hipMemcpyAsync(&done, sc + S_DONE, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -580,7 +589,7 @@ dwos_status cg_solve(dwos_opt* o, const double* b, double* x, int32_t max_iters,
                            par, tol2);
     }
     HIP_OK(hipGetLastError());
-    if (iters) *iters = it;
+    if (iters) *iters = spent + it;
     return DWOS_OK;
 }
 
@@ -658,7 +667,8 @@ dwos_status dwos_opt_create(int32_t dim, int64_t nv, const int32_t* prims, int64
         int per = 0, cus = 0;
         HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, resident_kernel(dim), opt_k::kResThreads, 0));
         HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, o->device));
-        o->resident = blocks_for(nv, opt_k::kResThreads) <= (int64_t)per * cus;
+        o->fits = o->resident = blocks_for(nv, opt_k::kResThreads) <= (int64_t)per * cus;
+        o->wait_ticks = (uint64_t)(opt_k::kWaitSeconds * opt_k::kTicksPerSecond);
         if (o->resident && max_nb > (size_t)opt_k::held_neighbours(dim))
             HIP_OK(o->pex.reserve(o->nnz * dim * sizeof(double)));
         return DWOS_OK;
@@ -666,6 +676,14 @@ dwos_status dwos_opt_create(int32_t dim, int64_t nv, const int32_t* prims, int64
     dwos_status st = up();
     if (st) { delete o; return st; }
     *out = o;
+    return DWOS_OK;
+}
+
+dwos_status dwos_opt_set_wait(dwos_opt* o, double seconds) {
+    if (!o) return fail(DWOS_EINVAL, "NULL optimiser");
+    if (!(seconds >= 0 && seconds <= 3600)) return fail(DWOS_EINVAL, "opt_set_wait: seconds must be in 0..3600");
+    o->wait_ticks = (uint64_t)(seconds * opt_k::kTicksPerSecond);
+    o->resident = o->fits && seconds > 0;
     return DWOS_OK;
 }
 

@@ -55,3 +55,8 @@ class LargeSteps:
         it = C.c_int32()
         check(capi.dwos_opt_solve(self._o, _dev(b), _dev(x), int(max_iters), float(tol), C.byref(it)))
         return it.value
+
+    def set_wait(self, seconds: float):
+        """How long the blocks of a one-launch solve wait for each other before
+        it is finished by several launches an iteration (0: always so)."""
+        check(capi.dwos_opt_set_wait(self._o, float(seconds)))
