@@ -40,7 +40,9 @@ struct ImpArgs {
 };
 
 // a^2 + b^2 with the rounding spelled out (FP32: one fused product), so that
-// a walk does not depend on how the compiler pairs the two in a build.
+// a walk does not depend on how the compiler pairs the two in a build.  The
+// rounded square is b's: the second component at a step, the first at a terminal,
+// the orders that the walks have always had.
 template <class T>
 __device__ __forceinline__ T sq_sum(T a, T b) {
     if constexpr (std::is_same<T, float>::value) return __builtin_fmaf(a, a, b * b);

@@ -248,9 +248,13 @@ __device__ __forceinline__ void edge_node3(const RefScene3<T>& r, int32_t i, Nod
 // FIRST's square is the rounded one.  Where the closest silhouette point is a
 // vertex of the box, this bound and the distances of the edges that share the
 // vertex differ by rounding alone, so the order decides which of them is
-// tested, and the walk's next position by one unit of rounding.
+// tested, and the walk's next position by one unit of rounding.  Either order
+// is as good; each build keeps the one its walks have always had (FIRST = 0,
+// x, in the forward build and the query kernel, 1, y, in the differential
+// build: sil3_round's first argument), so that they stay the same bit for bit.
 template <int FIRST>
 __device__ __forceinline__ float box3_d2(const float* lo, const float* hi, const float* x) {
+    static_assert(FIRST == 0 || FIRST == 1, "the x or the y component");
     float e[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) e[i] = fmaxf(fmaxf(lo[i] - x[i], x[i] - hi[i]), 0.0f);
@@ -258,6 +262,7 @@ __device__ __forceinline__ float box3_d2(const float* lo, const float* hi, const
 }
 template <int FIRST>
 __device__ __forceinline__ double box3_d2(const double* lo, const double* hi, const double* x) {
+    static_assert(FIRST == 0 || FIRST == 1, "the x or the y component");
     return box_d2<double, 3>(lo, hi, x);
 }
 
@@ -748,6 +753,7 @@ wost3_kernel(WalkArgs<T> a, RefScene3<T> ref, const int32_t* start_tri) {
                 const unsigned long long sm = __ballot(!sq.done());
                 const unsigned long long present = __ballot(true);
                 if (sm == 0ull || __popcll(present & ~sm) >= park) break;
+                static_assert(MODE == 0 || MODE == 1, "sil3_round's first argument is box3_d2's");
                 sil3_round<MODE>(ref, x, on, nin, sq, qc, stack, tail);
             }
         }
