@@ -15,13 +15,17 @@ nested forward walks, reverse-mode scatter, SpMV) and an Adam update.
 
 value = walk steps (closest-point queries executed by every forward,
 differential and nested walk) per second over the timed steps.  The
-roofline object prices the dominant walk kernel's node and triangle reads
-against the HBM peak, with the project's random-gather probe at the scene's
-working-set size beside it.  After the timed window, at a pinned state (the
-initial coefficients, independent of --steps), the second half of the
-metric: shape-gradient evaluations per second at a fixed relative RMSE of
-0.1, plain walks, the paper's 16 nested walks per terminal (Table 1) and
-the learned control variate (the surrogate), and the surrogate's speedup.
+roofline object prices the dominant walk kernel's arithmetic against the
+FP32 vector peak: the kernel is bound by the issue of divergent vector
+instructions, its node and triangle reads being served by the caches.  Their
+bytes stand beside it (more than HBM could deliver), with the project's
+random-gather probe at the scene's working-set size and, where counters were
+taken on the same sources, the traffic beyond the L2.  After the timed window,
+at a pinned state (the initial coefficients, independent of --steps), the
+second half of the metric: shape-gradient evaluations per second at a fixed
+relative RMSE of 0.1, plain walks, the paper's 16 nested walks per terminal
+(Table 1) and the learned control variate (the surrogate), and the surrogate's
+speedup.
 
 --workload c2 is the 2D screened-Poisson star (4096 segments, 4096 points x
 4096 walks, K = 8); the other workloads are listed under --workload.
@@ -98,10 +102,27 @@ def sources_sha256():
     return h.hexdigest()
 
 
+def walk_kernel_name(dim, kind, stage, cv=False, group=False):
+    """The FP32 walk kernel's build: kind 0 forward or 1 differential walks; stage
+    0 for a tree read through the caches, 1 for its first nodes in LDS, 2 for all
+    of it; with the control variate's records; with lanes that share a walk."""
+    return f"walk_kernel<float,{dim},{kind},{stage},{str(cv).lower()},{str(group).lower()}>"
+
+
+def stage_of(solver):
+    """The stage of the solver's walk kernels (see walk_kernel_name)."""
+    if solver.get_tuning()["variant"] != 0:
+        return 0
+    info = solver.scene_info()
+    return 2 if info["staged_prims"] and info["staged_nodes"] == info["nodes"] else 1
+
+
 def measured_traffic(kernel, nested, workload="c2"):
     """Scaled FETCH_SIZE + WRITE_SIZE bytes per launch of `kernel` from the
     committed counter summary of the workload, or None when it is missing or
-    was taken on different kernel sources or another nested-walk count."""
+    was taken on different kernel sources or another nested-walk count.  The
+    kernel is looked up by its name or, as the workload fixes the launch's
+    shape, by its first three template arguments (type, dimension, kind)."""
     try:
         with open(TRAFFIC_FILES[workload]) as f:
             text = f.read()
@@ -110,8 +131,10 @@ def measured_traffic(kernel, nested, workload="c2"):
     kv = dict(re.findall(r"^# (\w+): (\S+)$", text, re.M))
     if kv.get("sources_sha256") != sources_sha256() or kv.get("nested_walks_per_terminal") != str(nested):
         return None
-    m = re.search(r"^traffic_bytes_per_launch +" + re.escape(kernel) + r" +(\S+)$", text, re.M)
-    return float(m.group(1)) if m else None
+    rows = re.findall(r"^traffic_bytes_per_launch +(\S+) +(\S+)$", text, re.M)
+    build = lambda name: name.split(",")[:3]  # noqa: E731
+    found = [v for name, v in rows if name == kernel] or [v for name, v in rows if build(name) == build(kernel)]
+    return float(found[0]) if found else None
 
 
 def kernel_ops(tot, has_source=True):
@@ -436,25 +459,10 @@ def run_c4(args):
     del solvers
 
     kind, ms, n, tot = (1, ms1, n1, tot1) if ms1 >= ms0 else (0, ms0, n0, tot0)
-    avg_s = ms / max(1, n) / 1e3
-    kname = f"walk_kernel<float,3,{kind},{'true' if tuning['variant'] == 0 else 'false'},false>"
-    bytes_launch = (tot["nodes"] * BYTES_NODE_3D + tot["prims"] * BYTES_PRIM_3D) / max(1, n)
-    ops_launch = (tot["nodes"] * OPS_NODE_3D + tot["prims"] * OPS_PRIM_3D + tot["steps"] * OPS_STEP_3D) / max(1, n)
-    achieved = bytes_launch / avg_s
+    # (batches stage nothing: every instance has its own tree)
+    kname = walk_kernel_name(3, kind, 1 if tuning["variant"] == 0 else 0)
     info = s.scene_info()
-    probe = probe_gather(info["node_bytes"] + info["prim_bytes"])
-    roof = {"bound": "hbm", "achieved": achieved / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
-            "frac": achieved / PEAK_HBM, "traffic": measured_traffic(kname, 1, "c4"),
-            "kernel": kname, "avg_launch_ms": ms / max(1, n), "launches": n,
-            "algorithmic_bytes_per_launch": bytes_launch,
-            "bytes_per_step": bytes_launch / max(1.0, tot["steps"] / max(1, n)),
-            "steps_per_launch": tot["steps"] / max(1, n),
-            "nodes_per_step": tot["nodes"] / max(1, tot["steps"]),
-            "prims_per_step": tot["prims"] / max(1, tot["steps"]),
-            "scene": info, "gather_probe": probe,
-            "frac_of_gather_probe": achieved / (probe["gather64_working_set_GBs"] * 1e9),
-            "alu": {"achieved_TFLOPs": ops_launch / avg_s / 1e12, "peak_TFLOPs": PEAK_FP32_VALU / 1e12,
-                    "frac": ops_launch / avg_s / PEAK_FP32_VALU}}
+    roof = roofline_3d(kname, ms, n, tot, measured_traffic(kname, 1, "c4"), info)
     out = {
         "metric": METRIC, "value": steps_total / elapsed, "unit": "walk-steps/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": 1e3 * elapsed / args.steps,
@@ -1015,6 +1023,29 @@ def probe_gather(ws_bytes):
             "stream_4GiB_GBs": run(4 << 30, 64, 1)}
 
 
+def roofline_3d(kname, ms, n, tot, traffic, info):
+    """The roofline object of a 3D walk kernel: n launches of ms in all with the
+    counters tot; traffic: bytes beyond the L2 per launch, or None; info: the
+    scene's sizes."""
+    n = max(1, n)
+    avg_s = ms / n / 1e3
+    bytes_launch = (tot["nodes"] * BYTES_NODE_3D + tot["prims"] * BYTES_PRIM_3D) / n
+    ops_launch = (tot["nodes"] * OPS_NODE_3D + tot["prims"] * OPS_PRIM_3D + tot["steps"] * OPS_STEP_3D) / n
+    # the scene's node and primitive arrays: what the traversals gather from
+    probe = probe_gather(info["node_bytes"] + info["prim_bytes"])
+    return {"bound": "alu", "achieved": ops_launch / avg_s / 1e12, "peak": PEAK_FP32_VALU / 1e12,
+            "unit": "TFLOP/s", "frac": ops_launch / avg_s / PEAK_FP32_VALU, "traffic": traffic,
+            "hbm_frac": traffic / avg_s / PEAK_HBM if traffic else None,
+            "kernel": kname, "avg_launch_ms": ms / n, "launches": n, "ops_per_launch": ops_launch,
+            "steps_per_launch": tot["steps"] / n,
+            "nodes_per_step": tot["nodes"] / max(1, tot["steps"]),
+            "prims_per_step": tot["prims"] / max(1, tot["steps"]),
+            "scene": info,
+            "cache_reads": {"algorithmic_bytes_per_launch": bytes_launch,
+                            "bytes_per_step": bytes_launch / max(1.0, tot["steps"] / n),
+                            "GBs": bytes_launch / avg_s / 1e9, "gather_probe": probe}}
+
+
 def grad_rmse_rate(solver, Xt, w, target=0.1, W_probe=256, reps=12, seed0=60000, W_time_max=4096):
     """Shape-gradient evaluations per second at a fixed relative RMSE.
 
@@ -1127,28 +1158,8 @@ def run_c3(args):
         assert t["stack_overflow"] == 0 and t["invalid"] == 0 and t["truncated"] == 0, t
     steps_total = tot0["steps"] + tot1["steps"]
     kind, ms, n, tot = (1, ms1, n1, tot1) if ms1 >= ms0 else (0, ms0, n0, tot0)
-    avg_s = ms / max(1, n) / 1e3
-    staged = model.solver.get_tuning()["variant"] == 0
-    kname = f"walk_kernel<float,3,{kind},{'true' if staged else 'false'},false>"
-    bytes_launch = (tot["nodes"] * BYTES_NODE_3D + tot["prims"] * BYTES_PRIM_3D) / max(1, n)
-    ops_launch = (tot["nodes"] * OPS_NODE_3D + tot["prims"] * OPS_PRIM_3D + tot["steps"] * OPS_STEP_3D) / max(1, n)
-    achieved = bytes_launch / avg_s
-    # the scene's node and primitive arrays: what the traversals gather from
-    info = model.solver.scene_info()
-    probe = probe_gather(info["node_bytes"] + info["prim_bytes"])
-    roof = {"bound": "hbm", "achieved": achieved / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
-            "frac": achieved / PEAK_HBM, "traffic": measured_traffic(kname, K, "c3"),
-            "kernel": kname, "avg_launch_ms": ms / max(1, n), "launches": n,
-            "algorithmic_bytes_per_launch": bytes_launch,
-            "bytes_per_step": bytes_launch / max(1.0, tot["steps"] / max(1, n)),
-            "steps_per_launch": tot["steps"] / max(1, n),
-            "nodes_per_step": tot["nodes"] / max(1, tot["steps"]),
-            "prims_per_step": tot["prims"] / max(1, tot["steps"]),
-            "scene": info,
-            "gather_probe": probe,
-            "frac_of_gather_probe": achieved / (probe["gather64_working_set_GBs"] * 1e9),
-            "alu": {"achieved_TFLOPs": ops_launch / avg_s / 1e12, "peak_TFLOPs": PEAK_FP32_VALU / 1e12,
-                    "frac": ops_launch / avg_s / PEAK_FP32_VALU}}
+    kname = walk_kernel_name(3, kind, stage_of(model.solver))
+    roof = roofline_3d(kname, ms, n, tot, measured_traffic(kname, K, "c3"), model.solver.scene_info())
     out = {
         "metric": METRIC, "value": steps_total / elapsed, "unit": "walk-steps/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": 1e3 * elapsed / args.steps,
@@ -1389,8 +1400,7 @@ def run_c2(args):
     avg_s = ms / max(1, n) / 1e3
     ops = kernel_ops(tot) / max(1, n)
     achieved = ops / avg_s
-    # the default launch shape: the LDS-staged 1024-thread walk kernel
-    kname = f"walk_kernel<float,2,{kind},true,false>"
+    kname = walk_kernel_name(2, kind, stage_of(model.solver))
     roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP32_VALU / 1e12,
             "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_VALU, "traffic": measured_traffic(kname, args.nested, "c2"),
             "kernel": kname, "avg_launch_ms": ms / max(1, n),
