@@ -252,18 +252,25 @@ dwos_status dwos_scene_info(dwos_ctx* ctx, int64_t* info);
  * execution is valid.
  *   variant      0: one 1024-thread block per CU with the top BVH levels
  *                (and, if they fit, all primitives) staged in LDS;
- *                1: 256-thread blocks, several per CU (six wavefronts per
+ *                1: 256-thread blocks, several per CU (five wavefronts per
  *                SIMD in 3D), BVH read through the caches.  Default 1 for
  *                3D contexts, 0 for 2D.  FP64 contexts always use the
  *                unstaged kernel.
  *   park         1..64: a wavefront takes its walk step once this many of
  *                its lanes have their closest-point answer; the others
- *                resume their traversal in the next iteration (default 24)
+ *                resume their traversal in the next iteration (default 24).
+ *                Given for 64 live lanes, and taken in proportion (at least
+ *                one) where a launch gives a wavefront fewer walks or walks
+ *                have ended
  *   tail         0..63: a traversal round stops descending when at most this
  *                many lanes still descend while another lane holds a leaf
- *                to test; they go on in the next round (0: off; default 8)
- *   chunk        walk ids a wavefront takes from the global queue per
- *                refill: a multiple of 64 in 64..65536 (default 128)
+ *                to test; they go on in the next round (0: off; default 8).
+ *                In proportion to the live lanes, as park
+ *   chunk        most walk ids a wavefront takes from the global queue per
+ *                refill: a multiple of 64 in 64..65536 (default 128).  A
+ *                refill is at most a quarter of a wavefront's share of the
+ *                launch, and at least a walk for each of its lanes, so that
+ *                values above that share are one launch
  *   stage_nodes  cap on the breadth-first prefix of BVH nodes staged in LDS
  *                by variant 0, and in FP32 walk on stars on the staged prefix
  *                of the Dirichlet BVH (2D) or of the reflecting mesh's edge

@@ -914,9 +914,9 @@ dwos_status launch_shape(dwos_ctx* c, dwos::WalkArgs<T>& a, bool timed) {
     const size_t smem = a.count_off + dwos::kCountBytes;
     // FP32 launches of few walks give each walk two or four of the lanes that
     // would idle: they share its leaf tests, a wavefront's longest loop when few
-    // lanes of it work.  Without / with, us: 128-gon probe, 32,768 walks, 474 /
-    // 416; 4096-segment forward mode, 131,072 walks (two lanes), 1795 / 1498;
-    // 19,220 triangles, 73,963 walks, 2490 / 2082.  A launch that fills the
+    // lanes of it work.  Without / with, us a call: 128-gon probe, 32,768 walks,
+    // 368 / 296; 4096-segment forward mode, 131,072 walks (two lanes), 1650 / 1498;
+    // 19,220 triangles, 73,963 walks, 2340 / 1955.  A launch that fills the
     // wavefronts has no such lanes; the control variate's build is left alone.
     constexpr bool can_group = sizeof(T) == 4 && !cv;
     auto kern = dwos::walk_kernel<T, D, MODE, STAGE, cv, false>;

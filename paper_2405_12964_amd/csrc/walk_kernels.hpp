@@ -100,7 +100,7 @@ struct WalkArgs {
     uint32_t key0, key1;
     const unsigned long long* seed_ptr;   // if set, the key is seed + *seed_ptr
     unsigned long long* queue;
-    int32_t park;            // lanes answered before a wavefront takes its step (1..64)
+    int32_t park;            // lanes of 64 answered before a wavefront takes its step (1..64)
     uint32_t chunk;          // walk ids taken per wavefront refill (at least `lanes`)
     int32_t lanes;           // walks of each wavefront (1..64)
     int32_t group;           // lanes per walk: 1, 2 or 4 (lanes * group <= 64)
@@ -889,9 +889,9 @@ __device__ __forceinline__ void add_counts(const WalkArgs<T>& a, int lane, unsig
 //           that estimate
 // The unstaged 3D kernel asks for five wavefronts per SIMD (at most 96
 // registers per lane, none spilled): it is bound by the issue of divergent
-// vector instructions (66% of SIMD cycles busy at 28% of lanes) and by the
-// latency of the node gathers, and five leave each lane 15 traversal-stack
-// entries in LDS.  3D diffusion step (200,000 triangles, 65536 points x 128
+// vector instructions (90% of SIMD cycles busy at 38-40% of lanes on 65536
+// points x 1024 walks, 66% at 28% on 128 walks a point) and by the latency of the
+// node gathers, and five leave each lane 15 traversal-stack entries in LDS.  3D diffusion step (200,000 triangles, 65536 points x 128
 // walks, forward and differential launch): 39.3 ms at five wavefronts and 15
 // entries, 40.5 at four and 19, 40.5 at six and 12, 45.4 at six and 6 entries,
 // 45.9 at seven and 10.  The staged kernel's 1024-thread block, the 2D
