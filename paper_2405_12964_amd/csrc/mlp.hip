@@ -19,6 +19,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 
 namespace dwos_mlp_k {
 
@@ -221,6 +222,7 @@ struct EvalArgs {
     int64_t n;
     const int32_t* mask;
     int mask_div, mask_min;
+    int chunk;           // MASKED: points a block looks through at a time, a multiple of 256
     float* N;
     float* G;
     float* L;
@@ -233,8 +235,15 @@ struct EvalArgs {
 // of points to each wavefront, every block of the 1024 staged them for one
 // tile per wavefront: 65,536 points with derivatives 115 us, now 78 us, of which
 // issuing the vector arithmetic of tanh, sincos and the BF16 splits is 45.)
+//
+// MASKED: a block looks through `chunk` points at a time and evaluates those that
+// the mask lets through, listed in LDS, in full tiles (a point's result does not
+// depend on its column).  Of the walks around an object one in ninety runs nested
+// walks: 4.2 M points took 840 us, with derivatives 950, where a block skipped
+// tiles of 64 and 16 points without any, and take 115 and 115.
 // ---------------------------------------------------------------------------
-template <int D, bool LAP, class TX>
+constexpr int kEvalChunk = 1024;      // most points a block looks through at a time
+template <int D, bool LAP, class TX, bool MASKED>
 __global__ void __launch_bounds__(64 * kNetWaves, 2) eval_kernel(EvalArgs<TX> a) {
     constexpr int NC = LAP ? D + 2 : 1, NT = LAP ? 1 : 4, S = NC * NT;
     __shared__ __align__(16) char s_act[2][S * kSetBytes];
@@ -255,20 +264,15 @@ __global__ void __launch_bounds__(64 * kNetWaves, 2) eval_kernel(EvalArgs<TX> a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) w5[r] = a.theta[kLayers * kLayerSize + 16 * w + 4 * g + r];
     const float b5 = a.theta[kLayers * kLayerSize + kWidth];
-    for (int64_t it = blockIdx.x; it * (16 * NT) < a.n; it += gridDim.x) {
-        bool any = false;
-        float x[NT][D];
+    // 16 NT points; point(j): the j-th, or -1
+    auto tiles = [&](auto point) {
+        float x[NT][D], act[S][4];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int64_t p = (it * NT + nt) * 16 + i;
-            bool valid = p < a.n;
-            if (valid && a.mask) valid = a.mask[p / a.mask_div] >= a.mask_min;
-            any |= valid;
+            const int64_t p = point(nt * 16 + i);
 #pragma unroll
-            for (int c = 0; c < D; ++c) x[nt][c] = valid ? (float)a.X[p * D + c] : 0.f;
+            for (int c = 0; c < D; ++c) x[nt][c] = p >= 0 ? (float)a.X[p * D + c] : 0.f;
         }
-        if (__ballot(any) == 0ull) continue;   // the same in the four wavefronts
-        float act[S][4];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) fr.template eval<NC>(x[nt], act + nt * NC);
 #pragma unroll
@@ -307,10 +311,8 @@ __global__ void __launch_bounds__(64 * kNetWaves, 2) eval_kernel(EvalArgs<TX> a)
         __syncthreads();
         if (threadIdx.x < S * 16) {
             const int q = threadIdx.x >> 4, nt = q / NC, ch = q - nt * NC;
-            const int64_t p = (it * NT + nt) * 16 + (threadIdx.x & 15);
-            bool valid = p < a.n;
-            if (valid && a.mask) valid = a.mask[p / a.mask_div] >= a.mask_min;
-            if (valid) {
+            const int64_t p = point(nt * 16 + (int)(threadIdx.x & 15));
+            if (p >= 0) {
                 float o = 0.f;
 #pragma unroll
                 for (int k = 0; k < kNetWaves; ++k) o += s_out[k][threadIdx.x];
@@ -319,6 +321,31 @@ __global__ void __launch_bounds__(64 * kNetWaves, 2) eval_kernel(EvalArgs<TX> a)
                 else if (a.L) a.L[p] = o;
             }
         }
+    };
+    if constexpr (MASKED) {
+        __shared__ unsigned short s_list[kEvalChunk];
+        __shared__ int s_count;
+        for (int64_t p0 = (int64_t)blockIdx.x * a.chunk; p0 < a.n; p0 += (int64_t)gridDim.x * a.chunk) {
+            __syncthreads();                       // the last chunk's list is read
+            if (threadIdx.x == 0) s_count = 0;
+            __syncthreads();
+            for (int j = threadIdx.x; j < a.chunk; j += 64 * kNetWaves) {
+                const int64_t p = p0 + j;
+                const bool in = p < a.n && a.mask[p / a.mask_div] >= a.mask_min;
+                const unsigned long long m = __ballot(in);
+                int base = 0;
+                if (lane == 0 && m) base = atomicAdd(&s_count, __popcll(m));
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (in) s_list[base + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)j;
+            }
+            __syncthreads();
+            const int count = s_count;
+            for (int t = 0; t < count; t += 16 * NT)
+                tiles([&](int j) { return t + j < count ? p0 + (int64_t)s_list[t + j] : (int64_t)-1; });
+        }
+    } else {
+        for (int64_t p0 = (int64_t)blockIdx.x * (16 * NT); p0 < a.n; p0 += (int64_t)gridDim.x * (16 * NT))
+            tiles([&](int j) { return p0 + j < a.n ? p0 + j : (int64_t)-1; });
     }
 }
 
@@ -650,16 +677,31 @@ hipError_t mlp_eval_launch(const dwos_mlp* m, hipStream_t s, const TX* X, int64_
                            float* L) {
     if (n <= 0) return hipSuccess;
     EvalArgs<TX> a{m->packed.as<u32x4>(), m->theta.as<float>(), m->B.as<float>(), m->F, X, n,
-                   mask, mask_div < 1 ? 1 : mask_div, mask_min, N, G, L};
+                   mask, mask_div < 1 ? 1 : mask_div, mask_min, 0, N, G, L};
     const bool lap = G || L;
-    const dim3 grid(net_grid(m, n, lap ? 16 : 64, 2)), block(64 * kNetWaves);
-    if (m->dim == 2) {
-        if (lap) hipLaunchKernelGGL((eval_kernel<2, true, TX>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((eval_kernel<2, false, TX>), grid, block, 0, s, a);
-    } else {
-        if (lap) hipLaunchKernelGGL((eval_kernel<3, true, TX>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((eval_kernel<3, false, TX>), grid, block, 0, s, a);
+    int points = lap ? 16 : 64;
+    if (mask) {
+        // as many points as give every resident block a share, in whole rounds
+        // of its threads
+        const int64_t share = n / (2 * m->cu_count) / 256 * 256;
+        points = a.chunk = (int)std::min<int64_t>(kEvalChunk, std::max<int64_t>(256, share));
     }
+    const dim3 grid(net_grid(m, n, points, 2)), block(64 * kNetWaves);
+    auto go = [&](auto dim, auto with_lap, auto masked) {
+        constexpr int D = decltype(dim)::value;
+        constexpr bool LAP = decltype(with_lap)::value, MASKED = decltype(masked)::value;
+        hipLaunchKernelGGL((eval_kernel<D, LAP, TX, MASKED>), grid, block, 0, s, a);
+    };
+    auto by_mask = [&](auto dim, auto with_lap) {
+        if (mask) go(dim, with_lap, std::true_type{});
+        else go(dim, with_lap, std::false_type{});
+    };
+    auto by_lap = [&](auto dim) {
+        if (lap) by_mask(dim, std::true_type{});
+        else by_mask(dim, std::false_type{});
+    };
+    if (m->dim == 2) by_lap(std::integral_constant<int, 2>{});
+    else by_lap(std::integral_constant<int, 3>{});
     return hipGetLastError();
 }
 
