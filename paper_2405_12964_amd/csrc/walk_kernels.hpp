@@ -891,12 +891,12 @@ __device__ __forceinline__ void add_counts(const WalkArgs<T>& a, int lane, unsig
 // registers per lane, none spilled): it is bound by the issue of divergent
 // vector instructions (90% of SIMD cycles busy at 38-40% of lanes on 65536
 // points x 1024 walks, 66% at 28% on 128 walks a point) and by the latency of the
-// node gathers, and five leave each lane 15 traversal-stack entries in LDS.  3D diffusion step (200,000 triangles, 65536 points x 128
-// walks, forward and differential launch): 39.3 ms at five wavefronts and 15
-// entries, 40.5 at four and 19, 40.5 at six and 12, 45.4 at six and 6 entries,
-// 45.9 at seven and 10.  The staged kernel's 1024-thread block, the 2D
-// scenes' LDS-resident trees and the FP64 reference build keep the compiler's
-// choice.
+// node gathers, and five leave each lane 15 traversal-stack entries in LDS.  3D
+// diffusion step (200,000 triangles, 65536 points x 128 walks, forward and
+// differential launch): 39.3 ms at five wavefronts and 15 entries, 40.5 at four
+// and 19, 40.5 at six and 12, 45.4 at six and 6 entries, 45.9 at seven and 10.
+// The staged kernel's 1024-thread block, the 2D scenes' LDS-resident trees and
+// the FP64 reference build keep the compiler's choice.
 template <class T, int D, int MODE, int STAGE>
 struct WalkWaves {
     static constexpr int v = (sizeof(T) == 4 && STAGE == 0 && D == 3) ? 5 : 1;
